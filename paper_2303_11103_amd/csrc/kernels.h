@@ -245,7 +245,10 @@ struct CfrArgs {
     int64_t total;            // entries of H
 };
 hipError_t launch_cfr(const CfrArgs& c, hipStream_t s);
-hipError_t launch_cfr_adjoint(const CfrArgs& c, const float* G, double* g, hipStream_t s);
+// scratch: cfr_adjoint_scratch(c) bytes of partial sums, 16-byte aligned (may
+// be null when that is 0).
+size_t cfr_adjoint_scratch(const CfrArgs& c);
+hipError_t launch_cfr_adjoint(const CfrArgs& c, const float* G, double* g, void* scratch, hipStream_t s);
 
 // Coverage-map gradient: replay of recorded rays with field tangents.
 constexpr int kCovMaxMat = 4;                 // materials with tangents
