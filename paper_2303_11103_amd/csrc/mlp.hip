@@ -7,12 +7,13 @@
 // squared error in dB.  The paper gives no network (it motivates learned
 // propagation models, Sec. I); the ray tracer supplies the training maps.
 //
-// All matrix products are one NT-GEMM kernel, C[m][n] = sum_k A[m][k] B[n][k]
-// with k contiguous in both operands, on v_mfma_f32_16x16x32_bf16:
-//   forward  H_l = gelu(H_{l-1} W_l^T + b_l)        A = H_{l-1}, B = W_l
-//   backward dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})  A = dZ_l,    B = W_l^T
-//            dW_l = dZ_l^T H_{l-1} (split over rows) A = dZ_l^T,  B = H_{l-1}^T
-// The transposed operands come from a tiled transpose kernel.
+// Matrix products run on v_mfma_f32_16x16x32_bf16 (rows of the batch are the
+// MFMA's m dimension, accumulation over k in ascending steps of 32):
+//   forward  H_l = gelu(H_{l-1} W_l^T + b_l)
+//   backward dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
+//            dW_l = dZ_l^T H_{l-1} (split over rows)
+// mlp_rows_kernel takes 64 rows through the whole forward and backward chain;
+// mlp_dw_kernel contracts what it leaves, already in operand order, over rows.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,145 +53,12 @@ __device__ __forceinline__ float prior_db(const MlpNorm& nm, float tx, float ty,
     return nm.prior_db - 3.0102999566398120f * __log2f(d2);  // 10 log10(d2) = (10 log10 2) log2(d2)
 }
 
-// ------------------------------------------------------------------ GEMM
-constexpr int BM = 128, BN = 128, BK = 32, LDT = BK + 8;
+// ------------------------------------------------------------------ training
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) bf16 As[BM][LDT];
-    __shared__ __attribute__((aligned(16))) bf16 Bs[BN][LDT];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int k_begin = blockIdx.z * g.ksplit;
-    const int k_end = min(g.K, k_begin + g.ksplit);
-    floatx4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-        for (int c = tid; c < BM * (BK / 8); c += 256) {
-            const int r = c >> 2, kc = (c & 3) * 8;
-            *reinterpret_cast<uint4*>(&As[r][kc]) =
-                *reinterpret_cast<const uint4*>(g.A + (size_t)(m0 + r) * g.lda + k0 + kc);
-            *reinterpret_cast<uint4*>(&Bs[r][kc]) =
-                *reinterpret_cast<const uint4*>(g.B + (size_t)(n0 + r) * g.ldb + k0 + kc);
-        }
-        __syncthreads();
-        bf16x8 af[4], bfr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            af[i] = *reinterpret_cast<const bf16x8*>(&As[wm * 64 + i * 16 + (lane & 15)][(lane >> 4) * 8]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            bfr[j] = *reinterpret_cast<const bf16x8*>(&Bs[wn * 64 + j * 16 + (lane & 15)][(lane >> 4) * 8]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = n0 + wn * 64 + j * 16 + (lane & 15);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + wm * 64 + i * 16 + (lane >> 4) * 4 + r;
-                const float v = acc[i][j][r];
-                const size_t at = (size_t)row * g.N + col;
-                if (g.epi == kEpiStoreF32) {
-                    g.outF[(size_t)blockIdx.z * g.M * g.N + at] = v;
-                } else if (g.epi == kEpiBiasGelu) {
-                    const float z = v + g.bias[col];
-                    g.outZ[at] = (bf16)z;
-                    g.outH[at] = (bf16)gelu(z);
-                } else {  // kEpiGeluGrad
-                    const float zp = (float)g.Zprev[at];
-                    g.outZ[at] = (bf16)(v * gelu_grad(zp));
-                }
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------ elementwise
-__global__ void features_kernel(const float* __restrict__ v, int64_t n, const float* __restrict__ ff,
-                                MlpNorm norm, bf16* __restrict__ out) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n * kFreq) return;
-    const int64_t row = idx / kFreq;
-    const int j = (int)(idx - row * kFreq);
-    float rev = 0.0f;
-    for (int i = 0; i < 5; ++i) rev += ff[j * 5 + i] * ((v[row * 5 + i] - norm.center[i]) * norm.inv_half[i]);
-    float s, c;
-    sincospif(2.0f * rev, &s, &c);
-    out[row * (2 * kFreq) + j] = (bf16)s;
-    out[row * (2 * kFreq) + kFreq + j] = (bf16)c;
-}
-
-// pred = w5 . h4 + b5; loss and dZ4 = g w5 gelu'(Z4); dw5 and db5 partial sums.
-__global__ __launch_bounds__(256) void head_kernel(const bf16* __restrict__ H4, const bf16* __restrict__ Z4,
-                                                   const float* __restrict__ w5, const float* __restrict__ b5,
-                                                   const float* __restrict__ v, MlpNorm norm,
-                                                   const float* __restrict__ t, const float* __restrict__ m,
-                                                   int64_t n, const float* __restrict__ msum, float* __restrict__ pred,
-                                                   float* __restrict__ loss, bf16* __restrict__ dZ4,
-                                                   float* __restrict__ gw5, float* __restrict__ gb5) {
-    __shared__ float sw[256];
-    __shared__ float sg[256];
-    __shared__ float acc[256];
-    const int tid = threadIdx.x;
-    sw[tid] = w5[tid];
-    acc[tid] = 0.0f;
-    __syncthreads();
-    const int64_t r0 = (int64_t)blockIdx.x * 256;
-    // one thread per row: prediction and dL/dy
-    {
-        const int64_t row = r0 + tid;
-        float gval = 0.0f;
-        if (row < n) {
-            float y = b5[0];
-            for (int k = 0; k < 256; ++k) y += sw[k] * (float)H4[row * 256 + k];
-            const float* vr = v + 5 * row;
-            y += prior_db(norm, vr[0], vr[1], vr[2], vr[3], vr[4]);
-            if (pred) pred[row] = y;
-            if (t) {
-                const float inv = 1.0f / fmaxf(msum[0], 1.0f);
-                const float e = y - t[row];
-                gval = 2.0f * m[row] * e * inv;
-                acc[tid] = m[row] * e * e * inv;  // this row's share of the loss
-            }
-        }
-        sg[tid] = gval;
-    }
-    __syncthreads();
-    if (!t) return;
-    if (tid == 0) {
-        float s = 0.0f, l = 0.0f;
-        for (int i = 0; i < 256; ++i) {
-            s += sg[i];
-            l += acc[i];
-        }
-        atomicAdd(gb5, s);
-        atomicAdd(loss, l);  // one atomic per block
-    }
-    // thread = feature column k: dw5[k] += sum_rows g h4[row][k]; dZ4 = g w5[k] gelu'(z)
-    const int k = tid;
-    float a = 0.0f;
-    for (int i = 0; i < 256; ++i) {
-        const int64_t row = r0 + i;
-        if (row >= n) break;
-        const float gi = sg[i];
-        a += gi * (float)H4[row * 256 + k];
-        dZ4[row * 256 + k] = (bf16)(gi * sw[k] * gelu_grad((float)Z4[row * 256 + k]));
-    }
-    atomicAdd(gw5 + k, a);
-}
-
-__global__ void mask_sum_kernel(const float* __restrict__ m, int64_t n, float* __restrict__ out) {
+// Sum of the row weights in kMaskParts partials (each reader adds them in order).
+__global__ __launch_bounds__(256) void mask_sum_kernel(const float* __restrict__ m, int64_t n,
+                                                       float* __restrict__ part) {
     __shared__ float s[256];
     float a = 0.0f;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -201,40 +69,327 @@ __global__ void mask_sum_kernel(const float* __restrict__ m, int64_t n, float* _
         if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicAdd(out, s[0]);
+    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
 }
 
-// out[c][r] = in[r][c] for an R x C bf16 matrix (R, C multiples of 32)
-__global__ void transpose_kernel(const bf16* __restrict__ in, int64_t R, int64_t C, bf16* __restrict__ out) {
-    __shared__ bf16 tile[32][33];
-    const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
-    for (int i = threadIdx.y; i < 32; i += 8) tile[i][threadIdx.x] = in[(r0 + i) * C + c0 + threadIdx.x];
+// Index (in bf16) of lane `lane` of the operand fragment of features [16 ft,
+// 16 ft + 16) and rows [32 rg, 32 rg + 32): lane (g, c) holds feature 16 ft + c
+// of rows 4 g + j and 16 + 4 g + j, j = 0..3, the order in which the MFMA
+// leaves two 16-row output tiles in that lane.  Both operands of a dW product
+// use the same order, so it needs no transposition.
+__device__ __forceinline__ size_t frag_at(int64_t rg, int nft, int ft, int lane) {
+    return ((size_t)(rg * nft + ft) * 64 + lane) * 8;
+}
+
+// Four fp32 values rounded to bf16, packed into two registers here and now.
+__device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
+    uint2 u = __builtin_bit_cast(uint2, (bf16x4){(bf16)a, (bf16)b, (bf16)c, (bf16)d});
+    asm volatile("" : "+v"(u.x), "+v"(u.y));
+    return __builtin_bit_cast(bf16x4, u);
+}
+
+__device__ __forceinline__ void store_frag(bf16* p, bf16x4 lo, bf16x4 hi) {
+    *reinterpret_cast<bf16x8*>(p) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// 64 rows per block through the whole network and back (TRAIN), or to the
+// prediction only.  Wave w owns features 32 w .. 32 w + 31 of every layer: its
+// weight fragments come from L2 into registers (no other wave of the block
+// uses them; the next layer's are on their way during the epilogue), the
+// activations pass from layer to layer through LDS, and Z stays in the
+// registers of the lane that needs it for gelu' on the way back.  To global
+// memory go only the operands of the dW products (features, H1..H3, dZ1..dZ4)
+// and per-block sums for the biases, the head and the loss.
+// Bound by those writes (126 MB per 32768 rows) and by the exponentials of
+// gelu and gelu'.  One GEMM launch per layer and direction, with the
+// activations, transposes and column sums through memory, took 720 us per
+// gradient of 32768 rows.
+constexpr int kRowTile = 64, kRowPitch = 264;
+template <bool TRAIN>
+__global__ __launch_bounds__(512) void mlp_rows_kernel(MlpRowsArgs a) {
+    __shared__ __attribute__((aligned(16))) bf16 hb[2][kRowTile][kRowPitch];
+    __shared__ float w5[256];
+    __shared__ float g_s[kRowTile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c = lane & 15;
+    const int64_t row0 = (int64_t)blockIdx.x * kRowTile, rg0 = row0 / 32;
+    bf16x8 w[2][8];
+    auto load_w = [&](const bf16* base, int S) {
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                if (s < S)
+                    w[nt][s] = *reinterpret_cast<const bf16x8*>(base + ((size_t)((2 * wave + nt) * S + s) * 64 + lane) * 8);
+    };
+    load_w(a.wf, 4);
+    if (tid < 256) w5[tid] = a.params[a.lay.w_off[4] + tid];
+    {  // Fourier features: one frequency and the eight rows of one fragment lane per thread
+        const int f = lane, rg = wave >> 2, gg = wave & 3;
+        float fr[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) fr[i] = a.ff[f * 5 + i];
+        bf16x4 sn[2], cs[2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = rg * 32 + (j < 4 ? 4 * gg + j : 12 + 4 * gg + j);
+            const float* v = a.v + (row0 + r) * 5;
+            float rev = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) rev += fr[i] * ((v[i] - a.norm.center[i]) * a.norm.inv_half[i]);
+            float s, co;
+            sincospif(2.0f * rev, &s, &co);
+            sn[j >> 2][j & 3] = (bf16)s;
+            cs[j >> 2][j & 3] = (bf16)co;
+            hb[0][r][f] = (bf16)s;
+            hb[0][r][kFreq + f] = (bf16)co;
+        }
+        if (TRAIN) {
+            store_frag(a.hf[0] + frag_at(rg0 + rg, 8, f >> 4, gg * 16 + c), sn[0], sn[1]);
+            store_frag(a.hf[0] + frag_at(rg0 + rg, 8, 4 + (f >> 4), gg * 16 + c), cs[0], cs[1]);
+        }
+    }
     __syncthreads();
-    for (int i = threadIdx.y; i < 32; i += 8) out[(c0 + i) * R + r0 + threadIdx.x] = tile[threadIdx.x][i];
-}
-
-// db[n] += sum_rows dZ[row][n] (dZ: rows x N, N = 256)
-// db[c] += sum_i dZt[c][i]: one block per row c of the transposed gradient
-// (contiguous), a tree reduction, no atomics.
-__global__ __launch_bounds__(256) void rowsum_kernel(const bf16* __restrict__ dZt, int64_t cols,
-                                                     float* __restrict__ db) {
-    __shared__ float part[4];
-    const bf16* p = dZt + (int64_t)blockIdx.x * cols;
-    float a = 0.0f;
-    for (int64_t i = threadIdx.x; i < cols; i += 256) a += (float)p[i];
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+    bf16x4 z[4][4][2];  // [layer][16-row tile][16-feature tile]
+    bf16x4 h[4][2];
+    int cur = 0;
+    auto product = [&](floatx4 (&acc)[4][2], int S) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        // the activations of the next k step are read during the MFMAs of this one
+        bf16x8 af[2][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) af[0][i] = *reinterpret_cast<const bf16x8*>(&hb[cur][i * 16 + c][g * 8]);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s >= S) break;
+            if (s + 1 < S) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    af[(s + 1) & 1][i] =
+                        *reinterpret_cast<const bf16x8*>(&hb[cur][i * 16 + c][(s + 1) * 32 + g * 8]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s & 1][i], w[j][s], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);  // else every step's reads move up and spill
+        }
+    };
+    // writes a tile set to the other LDS buffer and, as fragments, to global memory
+    auto emit = [&](const bf16x4 (&x)[4][2], bool to_lds, bf16* frags) {
+        if (to_lds) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) hb[cur ^ 1][i * 16 + g * 4 + r][wave * 32 + j * 16 + c] = x[i][j][r];
+        }
+        if (frags) {
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    store_frag(frags + frag_at(rg0 + rg, 16, 2 * wave + j, lane), x[2 * rg][j], x[2 * rg + 1][j]);
+        }
+    };
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        floatx4 acc[4][2];
+        product(acc, l == 0 ? 4 : 8);
+        if (l < 3) load_w(a.wf + a.lay.bf_off[l + 1], 8);
+        else if (TRAIN) load_w(a.wb + a.lay.bf_off[3], 8);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float bias = a.params[a.lay.b_off[l] + wave * 32 + j * 16 + c];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const floatx4 zv = acc[i][j] + bias;
+                if (TRAIN) z[l][i][j] = pack4(zv[0], zv[1], zv[2], zv[3]);
+                h[i][j] = pack4(gelu(zv[0]), gelu(zv[1]), gelu(zv[2]), gelu(zv[3]));
+            }
+        }
+        emit(h, true, TRAIN && l < 3 ? a.hf[l + 1] : nullptr);
+        cur ^= 1;
+        __syncthreads();
+    }
+    // head, one row per lane of the first wave
+    float* part = TRAIN ? a.part + (size_t)blockIdx.x * kRowParts : nullptr;
+    if (tid < kRowTile) {
+        const int64_t row = row0 + tid;
+        float y = a.params[a.lay.b_off[4]];
+#pragma unroll 2
+        for (int k = 0; k < 256; k += 8) {
+            const bf16x8 hv = *reinterpret_cast<const bf16x8*>(&hb[cur][tid][k]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y += w5[k + j] * (float)hv[j];
+        }
+        const float* vr = a.v + 5 * row;
+        y += prior_db(a.norm, vr[0], vr[1], vr[2], vr[3], vr[4]);
+        if (!TRAIN) {
+            a.pred[row] = y;
+        } else {
+            float msum = 0.0f;
+            for (int i = 0; i < kMaskParts; ++i) msum += a.mask_part[i];
+            const float inv = 1.0f / fmaxf(msum, 1.0f);
+            const float e = y - a.t[row];
+            const float gv = 2.0f * a.m[row] * e * inv;
+            g_s[tid] = gv;
+            float sg = gv, sl = a.m[row] * e * e * inv;
+            for (int off = 32; off > 0; off >>= 1) {
+                sg += __shfl_xor(sg, off);
+                sl += __shfl_xor(sl, off);
+            }
+            if (tid == 0) {
+                part[5 * 256] = sg;
+                part[5 * 256 + 1] = sl;
+            }
+        }
+    }
+    if (!TRAIN) return;
     __syncthreads();
-    if (threadIdx.x == 0) db[blockIdx.x] += part[0] + part[1] + part[2] + part[3];
+    // sums over the block's rows of one value per (row, feature), by feature
+    auto column = [&](float s, int at) {
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (g == 0) part[at] = s;
+    };
+    bf16x4 d[4][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int col = wave * 32 + j * 16 + c;
+        const float wk = w5[col];
+        float sw = 0.0f, sb = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float dv[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float gi = g_s[i * 16 + g * 4 + r];
+                sw += gi * (float)h[i][j][r];
+                dv[r] = gi * wk * gelu_grad((float)z[3][i][j][r]);
+            }
+            d[i][j] = pack4(dv[0], dv[1], dv[2], dv[3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sb += (float)d[i][j][r];
+        }
+        column(sw, col);
+        column(sb, 256 * 4 + col);
+    }
+    emit(d, true, a.df[3]);
+#pragma unroll
+    for (int l = 3; l >= 1; --l) {
+        cur ^= 1;
+        __syncthreads();
+        floatx4 acc[4][2];
+        product(acc, 8);
+        if (l > 1) load_w(a.wb + a.lay.bf_off[l - 1], 8);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float sb = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float dv[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dv[r] = acc[i][j][r] * gelu_grad((float)z[l - 1][i][j][r]);
+                d[i][j] = pack4(dv[0], dv[1], dv[2], dv[3]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sb += (float)d[i][j][r];
+            }
+            column(sb, 256 * l + wave * 32 + j * 16 + c);
+        }
+        emit(d, l > 1, a.df[l - 1]);
+    }
 }
 
-// grad[i] += sum_s part[s][i]
-__global__ void reduce_splits_kernel(const float* __restrict__ part, int S, int64_t n, float* __restrict__ grad) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float a = 0.0f;
-    for (int s = 0; s < S; ++s) a += part[(int64_t)s * n + i];
-    grad[i] += a;
+// dW_l = dZ_l^T H_{l-1} over a range of 32-row groups: a 256 x 128 tile of one
+// layer per block (one tile of layer 1, two of the others), four waves of 128
+// x 64.  Operand fragments are read straight from global memory, 1 KB per wave
+// and load, kDwAhead groups ahead; one wave per SIMD with its sums in 128
+// accumulation registers.  Bound by the fragments (each is read by two waves
+// and, in layers 2-4, dZ by two blocks; L2 serves the repeats) and by the
+// 128 KB of partial sums per block.
+constexpr int kDwTiles = 7, kDwAhead = 3;
+__global__ __launch_bounds__(256, 1) void mlp_dw_kernel(MlpRowsArgs a, int64_t groups, int splits,
+                                                        floatx4* __restrict__ out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+    const int tile = blockIdx.x / splits, split = blockIdx.x % splits;
+    const int l = (tile + 1) / 2, nft = l == 0 ? 8 : 16, f0 = l == 0 ? 0 : ((tile - 1) & 1) * 8;
+    const int64_t r0 = groups * split / splits, r1 = groups * (split + 1) / splits;
+    const bf16* A = a.df[l] + frag_at(0, 16, wm * 8, lane);
+    const bf16* B = a.hf[l] + frag_at(0, nft, f0 + wn * 4, lane);
+    floatx4 acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 af[kDwAhead + 1][8], bfr[kDwAhead + 1][4];
+    auto load = [&](int64_t rg, bf16x8 (&x)[8], bf16x8 (&y)[4]) {
+        rg = rg < r1 ? rg : r1 - 1;  // past the end: the last group again, unused
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const bf16x8*>(A + (rg * 16 + i) * 512);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = *reinterpret_cast<const bf16x8*>(B + (rg * nft + j) * 512);
+    };
+    if (r0 < r1) {
+#pragma unroll
+        for (int u = 0; u < kDwAhead; ++u) load(r0 + u, af[u], bfr[u]);
+        for (int64_t rg = r0; rg < r1; rg += kDwAhead + 1) {
+#pragma unroll
+            for (int u = 0; u <= kDwAhead; ++u) {
+                if (rg + u >= r1) break;
+                load(rg + u + kDwAhead, af[(u + kDwAhead) % (kDwAhead + 1)], bfr[(u + kDwAhead) % (kDwAhead + 1)]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][i], bfr[u][j], acc[i][j], 0, 0, 0);
+            }
+        }
+    }
+    floatx4* o = out + (size_t)(split * kDwTiles + tile) * 128 * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[(size_t)((wm * 8 + i) * 8 + wn * 4 + j) * 64] = acc[i][j];
+}
+
+// Adds the partial sums in a fixed order into the whole gradient vector and the
+// loss: blocks [0, kDwReduceBlocks) one float4 of a dW tile per thread, the
+// others 16 of the row kernel's columns (biases, head, loss) each.
+constexpr int kDwReduceBlocks = kDwTiles * 128 * 64 / 256, kRowReduceBlocks = (5 * 256 + 2 + 15) / 16;
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const floatx4* __restrict__ dw, int splits,
+                                                         const float* __restrict__ part, int64_t blocks,
+                                                         MlpLayout lay, float* __restrict__ grad,
+                                                         float* __restrict__ loss) {
+    const int tid = threadIdx.x;
+    if (blockIdx.x < kDwReduceBlocks) {
+        const int e = blockIdx.x * 256 + tid, tile = e / (128 * 64), sub = e / 64 % 128, lane = e & 63;
+        floatx4 s = dw[e];
+        for (int p = 1; p < splits; ++p) s += dw[(size_t)p * kDwTiles * 128 * 64 + e];
+        const int l = (tile + 1) / 2, in0 = l == 0 ? 0 : ((tile - 1) & 1) * 128;
+        const int o = sub / 8 * 16 + (lane >> 4) * 4, k = in0 + (sub & 7) * 16 + (lane & 15);
+        float* W = grad + lay.w_off[l];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) W[(int64_t)(o + r) * lay.fan_in[l] + k] = s[r];
+        return;
+    }
+    __shared__ float red[16][17];
+    const int col = (blockIdx.x - kDwReduceBlocks) * 16 + (tid & 15), rr = tid >> 4;
+    float s = 0.0f;
+    if (col < 5 * 256 + 2)
+        for (int64_t b = rr; b < blocks; b += 16) s += part[b * kRowParts + col];
+    red[rr][tid & 15] = s;
+    __syncthreads();
+    if (rr != 0 || col >= 5 * 256 + 2) return;
+    for (int i = 1; i < 16; ++i) s += red[i][tid];
+    if (col < 256) grad[lay.w_off[4] + col] = s;
+    else if (col < 5 * 256) grad[lay.b_off[col / 256 - 1] + (col & 255)] = s;
+    else if (col == 5 * 256) grad[lay.b_off[4]] = s;
+    else *loss = s;
 }
 
 __device__ __forceinline__ uint64_t splitmix(uint64_t x) {
@@ -290,19 +445,20 @@ __global__ void init_kernel(float* __restrict__ params, float* __restrict__ ff, 
     }
 }
 
-// bf16 copies: W_l [out][in] and W_l^T [in][out]
-__global__ void refresh_bf16_kernel(const float* __restrict__ params, MlpLayout lay, bf16* __restrict__ wbf,
-                                    bf16* __restrict__ wtbf) {
+// bf16 copies of W1..W4 as MFMA operand fragments (16 columns x 32 k, 1 KB, 8
+// values per lane): wf for the forward product (column = output o, k = input),
+// wb for the backward one (column = input, k = output; layers 2..4).
+__global__ void refresh_bf16_kernel(const float* __restrict__ params, MlpLayout lay, bf16* __restrict__ wf,
+                                    bf16* __restrict__ wb) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int frag = (int)(i / 512), lane = (int)(i / 8 % 64), j = (int)(i & 7);
     for (int l = 0; l < 4; ++l) {
-        const int64_t sz = lay.w_size[l];
-        if (i < sz) {
-            const int fan = lay.fan_in[l];
-            const int64_t o = i / fan, k = i - o * fan;
-            const bf16 b = (bf16)params[lay.w_off[l] + i];
-            wbf[lay.bf_off[l] + i] = b;
-            wtbf[lay.bf_off[l] + k * 256 + o] = b;
-        }
+        if (i >= lay.w_size[l]) continue;
+        const int fan = lay.fan_in[l], S = fan / 32;
+        const float* W = params + lay.w_off[l];
+        wf[lay.bf_off[l] + i] = (bf16)W[(int64_t)(frag / S * 16 + (lane & 15)) * fan + frag % S * 32 + (lane >> 4) * 8 + j];
+        if (l > 0)
+            wb[lay.bf_off[l] + i] = (bf16)W[(int64_t)(frag % 8 * 32 + (lane >> 4) * 8 + j) * fan + frag / 8 * 16 + (lane & 15)];
     }
 }
 
@@ -772,45 +928,27 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
-hipError_t launch_gemm_nt(const GemmArgs& g, int splits, hipStream_t s) {
-    if (g.M % BM || g.N % BN || g.K % BK || g.ksplit % BK) return hipErrorInvalidValue;
-    dim3 grid(g.N / BN, g.M / BM, splits);
-    hipLaunchKernelGGL(gemm_nt_kernel, grid, dim3(256), 0, s, g);
+hipError_t launch_mlp_predict_rows(const MlpRowsArgs& a, hipStream_t s) {
+    if (a.n <= 0 || a.n % kRowTile) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(mlp_rows_kernel<false>, dim3((unsigned)(a.n / kRowTile)), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_features(const float* v, int64_t n, const float* ff, const MlpNorm& norm, bf16* out, hipStream_t s) {
-    hipLaunchKernelGGL(features_kernel, dim3(blocks_for(n * kFreq, 256)), dim3(256), 0, s, v, n, ff, norm, out);
-    return hipGetLastError();
-}
+// Row splits of the dW products: seven tiles per split, so 32 splits put one
+// block on most CUs; below 4 groups per split the partial sums cost more than
+// the blocks gain.
+int mlp_dw_splits(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kDwMaxSplits, n / 32 / 4)); }
 
-hipError_t launch_head(const bf16* H4, const bf16* Z4, const float* w5, const float* b5, const float* v,
-                       const MlpNorm& norm, const float* t, const float* m, int64_t n, const float* msum, float* pred,
-                       float* loss, bf16* dZ4, float* gw5, float* gb5, hipStream_t s) {
-    hipLaunchKernelGGL(head_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, H4, Z4, w5, b5, v, norm, t, m, n, msum,
-                       pred, loss, dZ4, gw5, gb5);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_sum(const float* m, int64_t n, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(mask_sum_kernel, dim3(64), dim3(256), 0, s, m, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_transpose(const bf16* in, int64_t R, int64_t C, bf16* out, hipStream_t s) {
-    if (R % 32 || C % 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(C / 32), (unsigned)(R / 32)), dim3(32, 8), 0, s, in, R, C,
-                       out);
-    return hipGetLastError();
-}
-
-hipError_t launch_rowsum(const bf16* dZt, int64_t rows, int64_t cols, float* db, hipStream_t s) {
-    hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)rows), dim3(256), 0, s, dZt, cols, db);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_splits(const float* part, int S, int64_t n, float* grad, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, part, S, n, grad);
+hipError_t launch_mlp_gradient(const MlpRowsArgs& a, float* dw_part, float* grad, float* loss, hipStream_t s) {
+    if (a.n <= 0 || a.n % kRowTile) return hipErrorInvalidValue;
+    const int64_t blocks = a.n / kRowTile;
+    const int splits = mlp_dw_splits(a.n);
+    hipLaunchKernelGGL(mask_sum_kernel, dim3(kMaskParts), dim3(256), 0, s, a.m, a.n, const_cast<float*>(a.mask_part));
+    hipLaunchKernelGGL(mlp_rows_kernel<true>, dim3((unsigned)blocks), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(mlp_dw_kernel, dim3((unsigned)(kDwTiles * splits)), dim3(256), 0, s, a, a.n / 32, splits,
+                       (floatx4*)dw_part);
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3(kDwReduceBlocks + kRowReduceBlocks), dim3(256), 0, s,
+                       (const floatx4*)dw_part, splits, a.part, blocks, a.lay, grad, loss);
     return hipGetLastError();
 }
 
@@ -820,8 +958,8 @@ hipError_t launch_mlp_init(float* params, float* ff, uint64_t seed, const MlpFou
     return hipGetLastError();
 }
 
-hipError_t launch_refresh_bf16(const float* params, const MlpLayout& lay, bf16* wbf, bf16* wtbf, hipStream_t s) {
-    hipLaunchKernelGGL(refresh_bf16_kernel, dim3(blocks_for(256 * 256, 256)), dim3(256), 0, s, params, lay, wbf, wtbf);
+hipError_t launch_refresh_bf16(const float* params, const MlpLayout& lay, bf16* wf, bf16* wb, hipStream_t s) {
+    hipLaunchKernelGGL(refresh_bf16_kernel, dim3(blocks_for(256 * 256, 256)), dim3(256), 0, s, params, lay, wf, wb);
     return hipGetLastError();
 }
 

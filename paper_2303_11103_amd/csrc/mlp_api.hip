@@ -29,7 +29,6 @@ namespace {
     } while (0)
 
 constexpr int kHidden = 256;
-constexpr int kSplits = 64;
 
 rt::MlpLayout make_layout() {
     rt::MlpLayout L{};
@@ -61,10 +60,10 @@ struct rt_mlp {
     rt::MlpNorm norm{};
     int64_t nbf = 0;
     float *params = nullptr, *grad = nullptr, *m1 = nullptr, *m2 = nullptr, *ff = nullptr;
-    __bf16 *wbf = nullptr, *wtbf = nullptr;
+    __bf16 *wf = nullptr, *wb = nullptr;  // weight fragments, forward and backward
     // batch scratch (rows = cfg.batch)
-    __bf16 *feats = nullptr, *Z[4] = {}, *H[4] = {}, *dZa = nullptr, *dZb = nullptr, *T1 = nullptr, *T2 = nullptr;
-    float *part = nullptr, *scal = nullptr, *pred = nullptr, *vin = nullptr;  // scal: [0] mask sum, [1] loss
+    __bf16 *hf[4] = {}, *df[4] = {};
+    float *row_part = nullptr, *dw_part = nullptr, *mask_part = nullptr, *loss = nullptr;
     _Float16* wfrag = nullptr;  // map inference: fragment-major f16 weights
     int num_cu = 256;
     int64_t step = 0;
@@ -93,82 +92,32 @@ rt_status check_rows(const rt_mlp* h, int64_t n) {
     return RT_OK;
 }
 
-// Forward pass over n rows whose raw inputs are in v (device, [n][5]).
-rt_status forward(rt_mlp* h, const float* v, int64_t n, hipStream_t s) {
-    MLP_HIP(rt::launch_features(v, n, h->ff, h->norm, h->feats, s));
-    const __bf16* in = h->feats;
-    for (int l = 0; l < 4; ++l) {
-        rt::GemmArgs g{};
-        g.A = in;
-        g.lda = h->lay.fan_in[l];
-        g.B = h->wbf + h->lay.bf_off[l];
-        g.ldb = h->lay.fan_in[l];
-        g.M = (int)n;
-        g.N = kHidden;
-        g.K = h->lay.fan_in[l];
-        g.ksplit = g.K;
-        g.epi = rt::kEpiBiasGelu;
-        g.bias = h->params + h->lay.b_off[l];
-        g.outZ = h->Z[l];
-        g.outH = h->H[l];
-        MLP_HIP(rt::launch_gemm_nt(g, 1, s));
-        in = h->H[l];
-    }
-    return RT_OK;
+rt::MlpRowsArgs rows_args(const rt_mlp* h, const float* v, int64_t n) {
+    rt::MlpRowsArgs a{};
+    a.v = v;
+    a.n = n;
+    a.ff = h->ff;
+    a.norm = h->norm;
+    a.lay = h->lay;
+    a.params = h->params;
+    a.wf = h->wf;
+    a.wb = h->wb;
+    return a;
 }
 
-// Gradient of the masked MSE over n rows into h->grad (zeroed first); loss
-// into h->scal[1].
-rt_status gradient(rt_mlp* h, const float* v, const float* t, const float* m, int64_t n, hipStream_t s) {
-    rt_status st = forward(h, v, n, s);
-    if (st != RT_OK) return st;
-    const rt::MlpLayout& L = h->lay;
-    MLP_HIP(hipMemsetAsync(h->grad, 0, (size_t)L.total * sizeof(float), s));
-    MLP_HIP(hipMemsetAsync(h->scal, 0, 2 * sizeof(float), s));
-    MLP_HIP(rt::launch_mask_sum(m, n, h->scal, s));
-    MLP_HIP(rt::launch_head(h->H[3], h->Z[3], h->params + L.w_off[4], h->params + L.b_off[4], v, h->norm, t, m, n,
-                            h->scal, h->pred, h->scal + 1, h->dZa, h->grad + L.w_off[4], h->grad + L.b_off[4], s));
-    __bf16* dz = h->dZa;
-    __bf16* dz_next = h->dZb;
-    for (int l = 3; l >= 0; --l) {
-        const int K = L.fan_in[l];
-        // dW_l = dZ_l^T H_{l-1}: both operands transposed so that rows are the reduction axis
-        MLP_HIP(rt::launch_transpose(dz, n, kHidden, h->T1, s));
-        MLP_HIP(rt::launch_rowsum(h->T1, kHidden, n, h->grad + L.b_off[l], s));  // db_l = column sums of dZ_l
-        const __bf16* hp = l ? h->H[l - 1] : h->feats;
-        MLP_HIP(rt::launch_transpose(hp, n, K, h->T2, s));
-        int S = kSplits;
-        while (S > 1 && (n / S) % 32) S >>= 1;
-        rt::GemmArgs g{};
-        g.A = h->T1;
-        g.lda = (int)n;
-        g.B = h->T2;
-        g.ldb = (int)n;
-        g.M = kHidden;
-        g.N = K;
-        g.K = (int)n;
-        g.ksplit = (int)(n / S);
-        g.epi = rt::kEpiStoreF32;
-        g.outF = h->part;
-        MLP_HIP(rt::launch_gemm_nt(g, S, s));
-        MLP_HIP(rt::launch_reduce_splits(h->part, S, (int64_t)kHidden * K, h->grad + L.w_off[l], s));
-        if (l > 0) {
-            rt::GemmArgs d{};
-            d.A = dz;
-            d.lda = kHidden;
-            d.B = h->wtbf + L.bf_off[l];
-            d.ldb = kHidden;
-            d.M = (int)n;
-            d.N = K;
-            d.K = kHidden;
-            d.ksplit = kHidden;
-            d.epi = rt::kEpiGeluGrad;
-            d.Zprev = h->Z[l - 1];
-            d.outZ = dz_next;
-            MLP_HIP(rt::launch_gemm_nt(d, 1, s));
-            std::swap(dz, dz_next);
-        }
+// Gradient of the masked MSE over n rows into grad; loss into *loss.
+rt_status gradient(rt_mlp* h, const float* v, const float* t, const float* m, int64_t n, float* grad, float* loss,
+                   hipStream_t s) {
+    rt::MlpRowsArgs a = rows_args(h, v, n);
+    a.t = t;
+    a.m = m;
+    a.mask_part = h->mask_part;
+    for (int l = 0; l < 4; ++l) {
+        a.hf[l] = h->hf[l];
+        a.df[l] = h->df[l];
     }
+    a.part = h->row_part;
+    MLP_HIP(rt::launch_mlp_gradient(a, h->dw_part, grad, loss, s));
     return RT_OK;
 }
 
@@ -222,21 +171,16 @@ rt_status rt_mlp_create(rt_ctx* c, const rt_mlp_config* cfg, rt_mlp** out) {
     A(&h->m1, P);
     A(&h->m2, P);
     A(&h->ff, rt::kFreq * 5);
-    A(&h->wbf, h->nbf);
-    A(&h->wtbf, h->nbf);
-    A(&h->feats, B * 2 * rt::kFreq);
+    A(&h->wf, h->nbf);
+    A(&h->wb, h->nbf);
     for (int l = 0; l < 4; ++l) {
-        A(&h->Z[l], B * kHidden);
-        A(&h->H[l], B * kHidden);
+        A(&h->hf[l], B * h->lay.fan_in[l]);
+        A(&h->df[l], B * kHidden);
     }
-    A(&h->dZa, B * kHidden);
-    A(&h->dZb, B * kHidden);
-    A(&h->T1, B * kHidden);
-    A(&h->T2, B * kHidden);
-    A(&h->part, (size_t)kSplits * kHidden * kHidden);
-    A(&h->scal, 4);
-    A(&h->pred, B);
-    A(&h->vin, B * 5);
+    A(&h->row_part, B / 64 * rt::kRowParts);
+    A(&h->dw_part, rt::kDwPartFloats);
+    A(&h->mask_part, rt::kMaskParts);
+    A(&h->loss, 1);
     A(&h->wfrag, (size_t)rt::v2_weights_halves());
     {
         int cu = 0;
@@ -250,7 +194,7 @@ rt_status rt_mlp_create(rt_ctx* c, const rt_mlp_config* cfg, rt_mlp** out) {
     rt::MlpFourier fs{cfg->ff_scale, cfg->ff_scale_cell > 0 ? cfg->ff_scale_cell : cfg->ff_scale, cfg->ff_scale_rel,
                       cfg->ff_rows_tx, cfg->ff_rows_rel};
     if (e == hipSuccess) e = rt::launch_mlp_init(h->params, h->ff, cfg->seed, fs, h->lay, s);
-    if (e == hipSuccess) e = rt::launch_refresh_bf16(h->params, h->lay, h->wbf, h->wtbf, s);
+    if (e == hipSuccess) e = rt::launch_refresh_bf16(h->params, h->lay, h->wf, h->wb, s);
     if (e != hipSuccess) {
         rt_mlp_destroy(h);
         return rt_internal_fail(e == hipErrorOutOfMemory ? RT_ERR_OOM : RT_ERR_DEVICE, hipGetErrorString(e));
@@ -286,7 +230,7 @@ rt_status rt_mlp_set_params(rt_mlp* h, const float* params, const float* ff) {
     MLP_HIP(hipMemsetAsync(h->m1, 0, h->lay.total * sizeof(float), s));
     MLP_HIP(hipMemsetAsync(h->m2, 0, h->lay.total * sizeof(float), s));
     h->step = 0;
-    MLP_HIP(rt::launch_refresh_bf16(h->params, h->lay, h->wbf, h->wtbf, s));
+    MLP_HIP(rt::launch_refresh_bf16(h->params, h->lay, h->wf, h->wb, s));
     return RT_OK;
 }
 
@@ -296,10 +240,9 @@ rt_status rt_mlp_forward(rt_mlp* h, const float* v, int64_t n, float* y) {
     if (st != RT_OK) return st;
     hipStream_t s = rt_internal_stream(h->ctx);
     MLP_HIP(hipSetDevice(rt_internal_device(h->ctx)));
-    if ((st = forward(h, v, n, s)) != RT_OK) return st;
-    const rt::MlpLayout& L = h->lay;
-    MLP_HIP(rt::launch_head(h->H[3], h->Z[3], h->params + L.w_off[4], h->params + L.b_off[4], v, h->norm, nullptr,
-                            nullptr, n, nullptr, y, nullptr, nullptr, nullptr, nullptr, s));
+    rt::MlpRowsArgs a = rows_args(h, v, n);
+    a.pred = y;
+    MLP_HIP(rt::launch_mlp_predict_rows(a, s));
     return RT_OK;
 }
 
@@ -310,10 +253,7 @@ rt_status rt_mlp_grad(rt_mlp* h, const float* v, const float* t, const float* m,
     if (st != RT_OK) return st;
     hipStream_t s = rt_internal_stream(h->ctx);
     MLP_HIP(hipSetDevice(rt_internal_device(h->ctx)));
-    if ((st = gradient(h, v, t, m, n, s)) != RT_OK) return st;
-    MLP_HIP(hipMemcpyAsync(grad, h->grad, h->lay.total * sizeof(float), hipMemcpyDeviceToDevice, s));
-    if (loss) MLP_HIP(hipMemcpyAsync(loss, h->scal + 1, sizeof(float), hipMemcpyDeviceToDevice, s));
-    return RT_OK;
+    return gradient(h, v, t, m, n, grad, loss ? loss : h->loss, s);
 }
 
 rt_status rt_mlp_train_step(rt_mlp* h, const float* v, const float* t, const float* m, int64_t n, float lr,
@@ -324,14 +264,13 @@ rt_status rt_mlp_train_step(rt_mlp* h, const float* v, const float* t, const flo
     if (st != RT_OK) return st;
     hipStream_t s = rt_internal_stream(h->ctx);
     MLP_HIP(hipSetDevice(rt_internal_device(h->ctx)));
-    if ((st = gradient(h, v, t, m, n, s)) != RT_OK) return st;
+    if ((st = gradient(h, v, t, m, n, h->grad, loss ? loss : h->loss, s)) != RT_OK) return st;
     h->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = (float)(1.0 / (1.0 - std::pow((double)b1, (double)h->step)));
     const float c2 = (float)(1.0 / (1.0 - std::pow((double)b2, (double)h->step)));
     MLP_HIP(rt::launch_adam(h->params, h->grad, h->m1, h->m2, h->lay.total, lr, b1, b2, 1e-8f, c1, c2, s));
-    MLP_HIP(rt::launch_refresh_bf16(h->params, h->lay, h->wbf, h->wtbf, s));
-    if (loss) MLP_HIP(hipMemcpyAsync(loss, h->scal + 1, sizeof(float), hipMemcpyDeviceToDevice, s));
+    MLP_HIP(rt::launch_refresh_bf16(h->params, h->lay, h->wf, h->wb, s));
     return RT_OK;
 }
 

@@ -8,21 +8,6 @@
 namespace rt {
 
 constexpr int kFreq = 64;
-enum : int { kEpiStoreF32 = 0, kEpiBiasGelu = 1, kEpiGeluGrad = 2 };
-
-struct GemmArgs {  // C[m][n] = sum_k A[m * lda + k] B[n * ldb + k], bf16 in, fp32 accumulate
-    const __bf16* A;
-    const __bf16* B;
-    int lda, ldb;
-    int M, N, K, ksplit;
-    int epi;
-    const float* bias;     // kEpiBiasGelu
-    __bf16* outZ;          // kEpiBiasGelu: z; kEpiGeluGrad: dz (may be null for z)
-    __bf16* outH;          // kEpiBiasGelu: gelu(z)
-    const __bf16* Zprev;   // kEpiGeluGrad
-    float* outF;           // kEpiStoreF32: [split][M][N]
-};
-
 struct MlpNorm {
     float center[5];
     float inv_half[5];
@@ -40,19 +25,35 @@ struct MlpLayout {
     int64_t total;
 };
 
-hipError_t launch_gemm_nt(const GemmArgs& g, int splits, hipStream_t s);
-hipError_t launch_features(const float* v, int64_t n, const float* ff, const MlpNorm& norm, __bf16* out, hipStream_t s);
-hipError_t launch_head(const __bf16* H4, const __bf16* Z4, const float* w5, const float* b5, const float* v,
-                       const MlpNorm& norm, const float* t, const float* m, int64_t n, const float* msum, float* pred,
-                       float* loss, __bf16* dZ4, float* gw5, float* gb5, hipStream_t s);
-hipError_t launch_mask_sum(const float* m, int64_t n, float* out, hipStream_t s);
+// Training and row-wise prediction.  n: a multiple of 128 rows.
+constexpr int kMaskParts = 64;
+constexpr int kRowParts = 5 * 256 + 8;  // head weights, biases 1..4, head bias, loss (padded)
+constexpr int kDwMaxSplits = 32;
+constexpr int64_t kDwPartFloats = (int64_t)kDwMaxSplits * 7 * 256 * 128;
+struct MlpRowsArgs {
+    const float* v;          // [n][5]
+    const float* t;          // [n] targets (gradient only)
+    const float* m;          // [n] row weights (gradient only)
+    int64_t n;
+    const float* ff;
+    MlpNorm norm;
+    MlpLayout lay;
+    const float* params;
+    const __bf16* wf;        // operand fragments of W1..W4 (launch_refresh_bf16)
+    const __bf16* wb;        // the same of the transposed W2..W4
+    const float* mask_part;  // [kMaskParts] scratch: partial sums of m
+    __bf16* hf[4];           // [n][128], [n][256] x 3: features, H1..H3 as dW operand fragments
+    __bf16* df[4];           // [n][256]: dZ1..dZ4 likewise
+    float* part;             // [n / 64][kRowParts]
+    float* pred;             // [n] (prediction only)
+};
+hipError_t launch_mlp_predict_rows(const MlpRowsArgs& a, hipStream_t s);
+// Whole gradient vector (lay.total) and loss; dw_part: kDwPartFloats scratch.
+hipError_t launch_mlp_gradient(const MlpRowsArgs& a, float* dw_part, float* grad, float* loss, hipStream_t s);
 // *count += number of nonzero bytes of m[0 .. n) (count cleared by the caller).
 hipError_t launch_count_u8(const uint8_t* m, int64_t n, unsigned long long* count, hipStream_t s);
 // out[c] = 10 log10(gain[c]) (or -inf) for the cells with fallback[c] != 0.
 hipError_t launch_fallback_merge(const uint8_t* fallback, const float* gain, int64_t n, float* out, hipStream_t s);
-hipError_t launch_transpose(const __bf16* in, int64_t R, int64_t C, __bf16* out, hipStream_t s);
-hipError_t launch_rowsum(const __bf16* dZt, int64_t rows, int64_t cols, float* db, hipStream_t s);
-hipError_t launch_reduce_splits(const float* part, int S, int64_t n, float* grad, hipStream_t s);
 // Fourier-matrix initialisation (see init_kernel).
 struct MlpFourier {
     float s_tx, s_cell, s_rel;
@@ -60,7 +61,7 @@ struct MlpFourier {
 };
 hipError_t launch_mlp_init(float* params, float* ff, uint64_t seed, const MlpFourier& fs, const MlpLayout& lay,
                            hipStream_t s);
-hipError_t launch_refresh_bf16(const float* params, const MlpLayout& lay, __bf16* wbf, __bf16* wtbf, hipStream_t s);
+hipError_t launch_refresh_bf16(const float* params, const MlpLayout& lay, __bf16* wf, __bf16* wb, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m1, float* m2, int64_t n, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s);
 hipError_t launch_sample(const float* maps, const uint32_t* index, int64_t count, const float* tx, int32_t T,
