@@ -110,6 +110,7 @@ struct rt_ctx {
     DevBuf rx_ant;     // Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
+    DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
     DevBuf scat;       // scattered paths: points, masks, prefixes, counts of one chunk
     void* scratch = nullptr;  // this device's copy of the fixed scratch array
     int64_t last_candidates = 0;
@@ -395,7 +396,7 @@ rt_status rt_destroy(rt_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->rx_ant, &c->paths,
-                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat})
+                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->diff})
         if (b->p) (void)hipFree(b->p);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     delete c;
@@ -925,6 +926,7 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
     const size_t rec_bytes = per * (2 + 8 + 1 + 2 + 2) * sizeof(float) + per * 3 * sizeof(int32_t) +
                              (size_t)nrx * sizeof(uint32_t);
     RT_HIP(ensure(c->paths, rec_bytes));
+    RT_HIP(ensure(c->diff, rt::diffraction_scratch(nrx, s->dev.num_wedges)));
     RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
     RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
     std::vector<double> rxp(3 * (size_t)nrx);
@@ -963,7 +965,7 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
         for (int i = 0; i < 3; ++i) pa.tx[i] = tx[t].pos[i];
         pa.tx_ant = make_antenna(tx + t);
         RT_HIP(hipMemsetAsync(pa.counts, 0, (size_t)nrx * sizeof(uint32_t), c->stream));
-        RT_HIP(rt::launch_diffraction_paths(pa, mats, c->stream));
+        RT_HIP(rt::launch_diffraction_paths(pa, mats, c->diff.p, c->stream));
         const size_t off = (size_t)t * per;
         RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
                                      depth_sorted, wedge + off, num_paths + (size_t)t * nrx, c->stream));

@@ -86,9 +86,41 @@ __device__ __forceinline__ void face_fresnel(const MatTable& mats, int m, double
     fresnel(mats.m[m], cos_i, rs, rh);
 }
 
-// One diffracted path over wedge wi from S (antenna txa) to P (antenna rxa):
-// false when there is none.  FULL also fills the transfer matrix and the
-// directions; otherwise only the coefficient a.
+// The path over a wedge from S to P: diffraction point and the two angles
+// about the edge.
+struct EdgePoint {
+    d3 Q;
+    double phip, phi;
+};
+
+// False when the pair has no diffraction point inside the edge or either end
+// lies outside the wedge's exterior.
+__device__ __forceinline__ bool edge_point(const Wedge& w, d3 S, d3 P, EdgePoint& ep) {
+    const d3 A = ldw(w.a), e = ldw(w.e);
+    // Keller point: axial coordinates and distances from the edge line
+    const double zs = dot(sub(S, A), e), zp = dot(sub(P, A), e);
+    const double rs = norm(sub(sub(S, A), scale(e, zs))), rp = norm(sub(sub(P, A), scale(e, zp)));
+    if (rs < 1e-9 || rp < 1e-9) return false;
+    const double z = zs + (zp - zs) * rs / (rs + rp);
+    if (!(z > 0.0 && z < w.len)) return false;
+    ep.Q = add(A, scale(e, z));
+    ep.phip = angle_about(w, S, ep.Q);
+    ep.phi = angle_about(w, P, ep.Q);
+    const double lim = w.n * kPi;
+    return ep.phip > 0.0 && ep.phip < lim && ep.phi > 0.0 && ep.phi < lim;
+}
+
+// A leg of the path (open segment, the two wedge faces skipped) is blocked.
+template <int BS, bool OVF>
+__device__ __forceinline__ bool leg_blocked(const DevScene& sc, const Node* lds_nodes, int n_lds,
+                                            int32_t (*stack)[BS], d3 from, d3 to, const Wedge& w) {
+    double tb = 1.0;
+    return traverse<true, false, BS, OVF>(sc, lds_nodes, n_lds, from, sub(to, from), w.face0, w.facen, kOccEpsD, tb,
+                                          stack) >= 0;
+}
+
+// FULL also fills the transfer matrix and the directions; otherwise only the
+// coefficient a.
 struct DiffPath {
     cd a;
     cd T[4];
@@ -97,26 +129,10 @@ struct DiffPath {
 };
 
 template <bool FULL>
-__device__ bool diffracted(const DevScene& sc, const Node* lds_nodes, int n_lds, int32_t (*stack)[kBlock],
-                           const MatTable& mats, double lambda, d3 S, const Antenna& txa, d3 P, const Antenna& rxa,
-                           int wi, DiffPath& out) {
-    const Wedge w = sc.wedges[wi];
-    const d3 A = ldw(w.a), e = ldw(w.e);
-    // Keller point: axial coordinates and distances from the edge line
-    const double zs = dot(sub(S, A), e), zp = dot(sub(P, A), e);
-    const double rs = norm(sub(sub(S, A), scale(e, zs))), rp = norm(sub(sub(P, A), scale(e, zp)));
-    if (rs < 1e-9 || rp < 1e-9) return false;
-    const double z = zs + (zp - zs) * rs / (rs + rp);
-    if (!(z > 0.0 && z < w.len)) return false;
-    const d3 Q = add(A, scale(e, z));
-    const double phip = angle_about(w, S, Q), phi = angle_about(w, P, Q);
-    const double lim = w.n * kPi;
-    if (!(phip > 0.0 && phip < lim && phi > 0.0 && phi < lim)) return false;
-    // both legs unoccluded (open segments, the two wedge faces skipped)
-    double tb = 1.0;
-    if (traverse<true>(sc, lds_nodes, n_lds, S, sub(Q, S), w.face0, w.facen, kOccEpsD, tb, stack) >= 0) return false;
-    tb = 1.0;
-    if (traverse<true>(sc, lds_nodes, n_lds, Q, sub(P, Q), w.face0, w.facen, kOccEpsD, tb, stack) >= 0) return false;
+__device__ void diffracted_path(const MatTable& mats, double lambda, d3 S, const Antenna& txa, d3 P,
+                                const Antenna& rxa, const Wedge& w, const EdgePoint& pt, DiffPath& out) {
+    const d3 e = ldw(w.e), Q = pt.Q;
+    const double phip = pt.phip, phi = pt.phi, lim = w.n * kPi;
     // coefficients
     const double k = 2.0 * kPi / lambda;
     const d3 vin = sub(Q, S), vout = sub(P, Q);
@@ -177,26 +193,161 @@ __device__ bool diffracted(const DevScene& sc, const Node* lds_nodes, int n_lds,
         out.s_in = sin_;
         out.s_out = sout;
     }
-    return true;
 }
 
-__global__ __launch_bounds__(kBlock) void diffraction_kernel(PathArgs a, MatTable mats) {
+// Diffracted paths of a range of receivers in three passes, because a pair that
+// has a path is rare (1 in 8,000 of a city's 133 million) and every step before
+// it drops most pairs: one thread per pair through all steps kept a few lanes of
+// each wave busy (30.4 ms for 1024 receivers and 129,768 wedges).
+
+// Pass 1: 256 wedges per block against 64 receivers.  Keeps a pair unless it
+// surely has no diffraction point inside the edge or its receiver surely lies
+// inside the solid: axial and radial distances in fp32 of differences taken in
+// fp64, against bounds 4e-6 (8 times the worst rounding) of their products.
+// The transmitter's side is tested once per wedge.  Each thread gathers its
+// wedge's receivers in a 64-bit mask, so the queue takes one atomic per block.
+constexpr int kDiffRx = 64;
+__global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, int32_t r0, int32_t r1,
+                                                                    int32_t wedge_tiles, uint2* __restrict__ queue,
+                                                                    uint32_t* __restrict__ count) {
+    __shared__ double rx[kDiffRx][3];
+    __shared__ uint32_t wave_n[kBlock / 64];
+    __shared__ uint32_t start;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int rb = r0 + (int)(blockIdx.x / wedge_tiles) * kDiffRx, nr = min(kDiffRx, r1 - rb);
+    for (int i = tid; i < 3 * nr; i += kBlock) rx[i / 3][i % 3] = a.rx[3 * (int64_t)rb + i];
+    __syncthreads();
+    const int wi = (int)(blockIdx.x % wedge_tiles) * kBlock + tid;
+    uint64_t keep = 0;
+    if (wi < a.sc.num_wedges) {
+        const Wedge w = a.sc.wedges[wi];
+        const double lim = w.n * kPi;
+        const float sl = (float)sin(lim), cl = (float)cos(lim), len = (float)w.len;
+        const f3 e{(float)w.e[0], (float)w.e[1], (float)w.e[2]};
+        const f3 t0{(float)w.t0[0], (float)w.t0[1], (float)w.t0[2]}, n0{(float)w.n0[0], (float)w.n0[1], (float)w.n0[2]};
+        auto split = [&](double x, double y, double z, float& ax, float& rad, bool& outside) {
+            const f3 d{(float)(x - w.a[0]), (float)(y - w.a[1]), (float)(z - w.a[2])};
+            ax = dot(d, e);
+            const f3 q{d.x - ax * e.x, d.y - ax * e.y, d.z - ax * e.z};
+            rad = sqrtf(dot(q, q));
+            // exterior: in front of the 0-face's plane or of the n-face's
+            const float u0 = dot(d, t0), u1 = dot(d, n0), tol = -4e-6f * (fabsf(ax) + rad);
+            outside = !(u1 < tol && u0 * sl - u1 * cl < tol);
+        };
+        float zs, rs;
+        bool out_s;
+        split(a.tx[0], a.tx[1], a.tx[2], zs, rs, out_s);
+        if (out_s) {
+            const float s0 = 4e-6f * (fabsf(zs) + rs + len);
+            for (int r = 0; r < nr; ++r) {
+                float zp, rp;
+                bool out_p;
+                split(rx[r][0], rx[r][1], rx[r][2], zp, rp, out_p);
+                // 0 < z < len for z = (zs rp + zp rs) / (rs + rp)
+                const float tol = s0 * (fabsf(zp) + rp + len);
+                const bool no_point = zs * rp + zp * rs < -tol || (zs - len) * rp + (zp - len) * rs > tol;
+                if (out_p && !no_point) keep |= 1ull << r;
+            }
+        }
+    }
+    const uint32_t n = (uint32_t)__popcll(keep);
+    uint32_t incl = n;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    if (lane == 63) wave_n[wv] = incl;
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t sum = 0;
+        for (int i = 0; i < kBlock / 64; ++i) {
+            const uint32_t c = wave_n[i];
+            wave_n[i] = sum;
+            sum += c;
+        }
+        start = sum ? atomicAdd(count, sum) : 0u;
+    }
+    __syncthreads();
+    uint32_t at = start + wave_n[wv] + incl - n;
+    while (keep) {
+        const int r = __ffsll((long long)keep) - 1;
+        keep &= keep - 1;
+        queue[at++] = uint2{(uint32_t)(rb + r), (uint32_t)wi};
+    }
+}
+
+// Pass 2: the exact tests in fp64, then the leg from the transmitter, then, for
+// the survivors, the leg to the receiver.  A wave collects survivors of the
+// first leg in LDS until it has 64, so that the second leg runs with full waves
+// too.  Bound by the any-hit traversals.
+template <bool OVF>
+__global__ __launch_bounds__(kBlock) void diffraction_legs_kernel(PathArgs a, const uint2* __restrict__ queue,
+                                                                  const uint32_t* __restrict__ count,
+                                                                  uint2* __restrict__ out,
+                                                                  uint32_t* __restrict__ out_count) {
     __shared__ int32_t stack[kStack][kBlock];
     __shared__ Node lds_nodes[kLdsNodes];
+    __shared__ uint2 held[kBlock / 64][128];
     const int n_lds = stage_nodes(a.sc, lds_nodes);
-    const int64_t nw = a.sc.num_wedges;
-    const int64_t total = (int64_t)a.nrx * nw;
+    const int lane = threadIdx.x & 63;
+    uint2* mine = held[threadIdx.x >> 6];
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
-    for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < total;
-         item += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(item / nw);
-        const int wi = (int)(item - (int64_t)r * nw);
-        const d3 P{a.rx[3 * r], a.rx[3 * r + 1], a.rx[3 * r + 2]};
-        DiffPath p;
-        if (!diffracted<true>(a.sc, lds_nodes, n_lds, stack, mats, a.lambda, S, a.tx_ant, P, a.rx_ant[r], wi, p))
-            continue;
+    const int64_t n = (int64_t)*count;
+    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / 64);
+    int have = 0;  // survivors of the first leg in `mine` (the same in every lane)
+    auto second_leg = [&](int take) {
+        bool ok = false;
+        uint2 it{0u, 0u};
+        if (lane < take) {
+            it = mine[have - take + lane];
+            const Wedge w = a.sc.wedges[it.y];
+            const d3 P{a.rx[3 * (int64_t)it.x], a.rx[3 * (int64_t)it.x + 1], a.rx[3 * (int64_t)it.x + 2]};
+            EdgePoint pt;
+            ok = edge_point(w, S, P, pt) && !leg_blocked<kBlock, OVF>(a.sc, lds_nodes, n_lds, stack, pt.Q, P, w);
+        }
+        have -= take;
+        const uint64_t m = __ballot(ok);
+        if (m) {
+            uint32_t b = 0;
+            if (lane == 0) b = atomicAdd(out_count, (uint32_t)__popcll(m));
+            b = __shfl(b, 0);
+            if (ok) out[b + __popcll(m & ((1ull << lane) - 1ull))] = it;
+        }
+    };
+    for (int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * 64; base < n; base += nwaves * 64) {
+        bool ok = false;
+        uint2 it{0u, 0u};
+        if (base + lane < n) {
+            it = queue[base + lane];
+            const Wedge w = a.sc.wedges[it.y];
+            const d3 P{a.rx[3 * (int64_t)it.x], a.rx[3 * (int64_t)it.x + 1], a.rx[3 * (int64_t)it.x + 2]};
+            EdgePoint pt;
+            ok = edge_point(w, S, P, pt) && !leg_blocked<kBlock, OVF>(a.sc, lds_nodes, n_lds, stack, S, pt.Q, w);
+        }
+        const uint64_t m = __ballot(ok);
+        if (ok) mine[have + __popcll(m & ((1ull << lane) - 1ull))] = it;
+        have += __popcll(m);
+        if (have >= 64) second_leg(64);
+    }
+    if (have) second_leg(have);
+}
+
+// Pass 3: coefficients of the pairs that have a path.
+__global__ __launch_bounds__(kBlock) void diffraction_paths_kernel(PathArgs a, MatTable mats,
+                                                                   const uint2* __restrict__ queue,
+                                                                   const uint32_t* __restrict__ count) {
+    const d3 S{a.tx[0], a.tx[1], a.tx[2]};
+    const uint32_t n = *count;
+    for (uint32_t item = blockIdx.x * kBlock + threadIdx.x; item < n; item += gridDim.x * kBlock) {
+        const int r = (int)queue[item].x, wi = (int)queue[item].y;
+        const d3 P{a.rx[3 * (int64_t)r], a.rx[3 * (int64_t)r + 1], a.rx[3 * (int64_t)r + 2]};
+        const Wedge w = a.sc.wedges[wi];
+        EdgePoint pt;
+        if (!edge_point(w, S, P, pt)) continue;
         const uint32_t slot = atomicAdd(a.counts + r, 1u);
         if (slot >= (uint32_t)a.P) continue;
+        DiffPath p;
+        diffracted_path<true>(mats, a.lambda, S, a.tx_ant, P, a.rx_ant[r], w, pt, p);
         const int64_t at = (int64_t)r * a.P + slot;
         a.a[2 * at] = (float)p.a.re;
         a.a[2 * at + 1] = (float)p.a.im;
@@ -232,9 +383,14 @@ __global__ __launch_bounds__(kBlock) void coverage_diffraction_kernel(DevScene s
         const d3 P{gx0 + ((double)ix + 0.5) * gcell, gy0 + ((double)iy + 0.5) * gcell, gz};
         double acc = 0.0;
         for (int wi = 0; wi < sc.num_wedges; ++wi) {
+            const Wedge w = sc.wedges[wi];
+            EdgePoint pt;
+            if (!edge_point(w, S, P, pt) || leg_blocked<kBlock, true>(sc, lds_nodes, n_lds, stack, S, pt.Q, w) ||
+                leg_blocked<kBlock, true>(sc, lds_nodes, n_lds, stack, pt.Q, P, w))
+                continue;
             DiffPath p;
-            if (diffracted<false>(sc, lds_nodes, n_lds, stack, mats, lambda, S, txa, P, rxa, wi, p))
-                acc += p.a.re * p.a.re + p.a.im * p.a.im;
+            diffracted_path<false>(mats, lambda, S, txa, P, rxa, w, pt, p);
+            acc += p.a.re * p.a.re + p.a.im * p.a.im;
         }
         gain[c] += (float)acc;
     }
@@ -253,12 +409,45 @@ hipError_t launch_coverage_diffraction(const DevScene& sc, const MatTable& mats,
     return hipGetLastError();
 }
 
-hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, hipStream_t s) {
-    const int64_t total = (int64_t)a.nrx * a.sc.num_wedges;
-    if (total <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>((total + kBlock - 1) / kBlock, 8192);
-    hipLaunchKernelGGL(diffraction_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, a, mats);
-    return hipGetLastError();
+namespace {
+// Receivers handled together: their pairs must fit the queue even if all survive.
+int64_t diffraction_rx_chunk(int64_t nrx, int64_t nw) {
+    const int64_t most = std::max<int64_t>(1, kDiffQueuePairs / nw);
+    return std::min<int64_t>(nrx, most > kDiffRx ? most / kDiffRx * kDiffRx : most);
+}
+}  // namespace
+
+size_t diffraction_scratch(int64_t nrx, int64_t num_wedges) {
+    if (nrx <= 0 || num_wedges <= 0) return 0;
+    const size_t pairs = (size_t)(diffraction_rx_chunk(nrx, num_wedges) * num_wedges);
+    return 256 + 2 * pairs * sizeof(uint2);
+}
+
+hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s) {
+    const int64_t nw = a.sc.num_wedges;
+    if (a.nrx <= 0 || nw <= 0) return hipSuccess;
+    const int64_t chunk = diffraction_rx_chunk(a.nrx, nw);
+    uint32_t* count = (uint32_t*)scratch;
+    uint2* q0 = (uint2*)((char*)scratch + 256);
+    uint2* q1 = q0 + chunk * nw;
+    for (int64_t r0 = 0; r0 < a.nrx; r0 += chunk) {
+        const int64_t r1 = std::min<int64_t>(a.nrx, r0 + chunk), pairs = (r1 - r0) * nw;
+        hipError_t e = launch_fill_u32(count, 0u, 2, s);
+        if (e != hipSuccess) return e;
+        const int64_t wt = (nw + kBlock - 1) / kBlock, rt = (r1 - r0 + kDiffRx - 1) / kDiffRx;
+        hipLaunchKernelGGL(diffraction_filter_kernel, dim3((unsigned)(wt * rt)), dim3(kBlock), 0, s, a, (int32_t)r0,
+                           (int32_t)r1, (int32_t)wt, q0, count);
+        // three blocks of 52 KB per CU for the traversals
+        const dim3 grid((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 256 * 3));
+        if (a.sc.stack_need > kStack)
+            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kBlock), 0, s, a, q0, count, q1, count + 1);
+        else
+            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kBlock), 0, s, a, q0, count, q1, count + 1);
+        hipLaunchKernelGGL(diffraction_paths_kernel, dim3((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 512)),
+                           dim3(kBlock), 0, s, a, mats, q1, count + 1);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace rt

@@ -151,9 +151,13 @@ hipError_t launch_extract_pairs(const uint64_t* pairs, uint64_t pairs_cap, const
 hipError_t launch_extract_candidates(const uint64_t* table, uint64_t cap, int32_t max_depth, Cand* out,
                                      uint32_t* count, uint32_t max_out, hipStream_t s);
 hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t max_items, hipStream_t s);
-// First-order diffraction: one thread per (receiver, wedge) writes the valid
-// paths into the unsorted records of a (depth = 1, faces[0] = wedge id, fd = 1).
-hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, hipStream_t s);
+// First-order diffraction: the valid (receiver, wedge) paths into the unsorted
+// records of a (depth = 1, faces[0] = wedge id, fd = 1).  scratch:
+// diffraction_scratch(nrx, num_wedges) bytes, at most two queues of
+// kDiffQueuePairs pairs (or of one receiver's).
+constexpr int64_t kDiffQueuePairs = int64_t(1) << 25;
+size_t diffraction_scratch(int64_t nrx, int64_t num_wedges);
+hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s);
 // Diffraction part of a coverage map: gain[c] += sum over wedges of |a|^2 of the
 // diffracted path from tx to the centre of cell c (one thread per cell).
 hipError_t launch_coverage_diffraction(const DevScene& sc, const MatTable& mats, double lambda, const double* tx,

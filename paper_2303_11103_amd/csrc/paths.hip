@@ -10,6 +10,8 @@
 // validity (segment parameter, front side, point inside the face), occlusion
 // of every segment by an any-hit BVH traversal, then the field transfer
 // through the Fresnel reflections and the receive pattern.
+#include <algorithm>
+
 #include "traverse.h"
 
 namespace rt {
@@ -252,57 +254,61 @@ __global__ __launch_bounds__(kBlock) void image_paths_kernel(PathArgs a, MatTabl
 
 // Order the paths of one receiver by (depth, faces) and write them to the
 // caller's arrays; unused slots get a = 0, tau = -1, depth = -1, faces = -1.
-__global__ void sort_paths_kernel(PathArgs a, int32_t nrx, float* a_out, float* T_out, float* tau_out, float* aod_out,
-                                  float* aoa_out, int32_t* depth_out, int32_t* faces_out, int32_t* num_out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrx) return;
-    const uint32_t cnt = a.counts[r];
-    num_out[r] = (int32_t)cnt;
-    const int n = (int)(cnt < (uint32_t)a.P ? cnt : (uint32_t)a.P);
-    int order[256];
-    for (int i = 0; i < n; ++i) order[i] = i;
-    const int64_t base = (int64_t)r * a.P;
-    auto less = [&](int x, int y) {
-        const int dx = a.depth[base + x], dy = a.depth[base + y];
-        if (dx != dy) return dx < dy;
-        for (int i = 0; i < a.fd; ++i) {
-            const int fx = a.faces[(base + x) * a.fd + i], fy = a.faces[(base + y) * a.fd + i];
-            if (fx != fy) return fx < fy;
+// One block per receiver: thread i counts the paths that come before path i
+// (at most 256, keys in LDS), then all threads copy.  Bound by the writes (84
+// bytes and more per slot); one thread per receiver, sorting by insertion and
+// copying alone, took 806 us for 1024 receivers of 256 slots and 17,000 paths.
+constexpr int kSortSlots = 256, kSortFaces = 8;
+__global__ __launch_bounds__(kSortSlots) void sort_paths_kernel(PathArgs a, float* a_out, float* T_out,
+                                                                float* tau_out, float* aod_out, float* aoa_out,
+                                                                int32_t* depth_out, int32_t* faces_out,
+                                                                int32_t nrx, int32_t* num_out) {
+    __shared__ int32_t key[1 + kSortFaces][kSortSlots];
+    __shared__ int32_t from[kSortSlots];
+    const int tid = threadIdx.x;
+    for (int r = blockIdx.x; r < nrx; r += gridDim.x) {
+        const uint32_t cnt = a.counts[r];
+        const int n = (int)(cnt < (uint32_t)a.P ? cnt : (uint32_t)a.P);
+        const int64_t base = (int64_t)r * a.P;
+        if (tid == 0) num_out[r] = (int32_t)cnt;
+        if (tid < n) {
+            key[0][tid] = a.depth[base + tid];
+            for (int k = 0; k < a.fd; ++k) key[1 + k][tid] = a.faces[(base + tid) * a.fd + k];
         }
-        return false;
-    };
-    for (int i = 1; i < n; ++i) {
-        int v = order[i], j = i - 1;
-        while (j >= 0 && less(v, order[j])) {
-            order[j + 1] = order[j];
-            --j;
+        __syncthreads();
+        if (tid < n) {
+            int rank = 0;
+            for (int j = 0; j < n; ++j) {
+                int before = j < tid;  // equal keys keep their order
+                for (int k = 0; k <= a.fd; ++k) {
+                    const int x = key[k][j], y = key[k][tid];
+                    if (x != y) {
+                        before = x < y;
+                        break;
+                    }
+                }
+                rank += before;
+            }
+            from[rank] = tid;
         }
-        order[j + 1] = v;
-    }
-    for (int i = 0; i < a.P; ++i) {
-        const int64_t o = base + i;
-        if (i < n) {
-            const int64_t s = base + order[i];
-            a_out[2 * o] = a.a[2 * s];
-            a_out[2 * o + 1] = a.a[2 * s + 1];
-            for (int k = 0; k < 8; ++k) T_out[8 * o + k] = a.T[8 * s + k];
-            tau_out[o] = a.tau[s];
-            aod_out[2 * o] = a.aod[2 * s];
-            aod_out[2 * o + 1] = a.aod[2 * s + 1];
-            aoa_out[2 * o] = a.aoa[2 * s];
-            aoa_out[2 * o + 1] = a.aoa[2 * s + 1];
-            depth_out[o] = a.depth[s];
-            for (int k = 0; k < a.fd; ++k) faces_out[o * a.fd + k] = a.faces[s * a.fd + k];
-        } else {
-            a_out[2 * o] = 0.0f;
-            a_out[2 * o + 1] = 0.0f;
-            for (int k = 0; k < 8; ++k) T_out[8 * o + k] = 0.0f;
-            tau_out[o] = -1.0f;
-            aod_out[2 * o] = aod_out[2 * o + 1] = 0.0f;
-            aoa_out[2 * o] = aoa_out[2 * o + 1] = 0.0f;
-            depth_out[o] = -1;
-            for (int k = 0; k < a.fd; ++k) faces_out[o * a.fd + k] = -1;
+        __syncthreads();
+        auto copy = [&](float* dst, const float* src, int width, float none) {
+            for (int e = tid; e < a.P * width; e += kSortSlots) {
+                const int i = e / width;
+                dst[base * width + e] = i < n ? src[(base + from[i]) * width + (e - i * width)] : none;
+            }
+        };
+        copy(a_out, a.a, 2, 0.0f);
+        copy(T_out, a.T, 8, 0.0f);
+        copy(tau_out, a.tau, 1, -1.0f);
+        copy(aod_out, a.aod, 2, 0.0f);
+        copy(aoa_out, a.aoa, 2, 0.0f);
+        for (int i = tid; i < a.P; i += kSortSlots) depth_out[base + i] = i < n ? key[0][from[i]] : -1;
+        for (int e = tid; e < a.P * a.fd; e += kSortSlots) {
+            const int i = e / a.fd;
+            faces_out[base * a.fd + e] = i < n ? key[1 + e - i * a.fd][from[i]] : -1;
         }
+        __syncthreads();
     }
 }
 
@@ -356,9 +362,9 @@ hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t m
 hipError_t launch_sort_paths(const PathArgs& a, int32_t nrx, float* a_out, float* T_out, float* tau_out,
                              float* aod_out, float* aoa_out, int32_t* depth_out, int32_t* faces_out,
                              int32_t* num_paths_out, hipStream_t s) {
-    const int blocks = (nrx + 63) / 64;
-    hipLaunchKernelGGL(sort_paths_kernel, dim3(blocks), dim3(64), 0, s, a, nrx, a_out, T_out, tau_out, aod_out,
-                       aoa_out, depth_out, faces_out, num_paths_out);
+    if (a.P > kSortSlots || a.fd > kSortFaces) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sort_paths_kernel, dim3(std::min(nrx, 1 << 20)), dim3(kSortSlots), 0, s, a, a_out, T_out,
+                       tau_out, aod_out, aoa_out, depth_out, faces_out, nrx, num_paths_out);
     return hipGetLastError();
 }
 
