@@ -208,7 +208,7 @@ __device__ void diffracted_path(const MatTable& mats, double lambda, d3 S, const
 // wedge's receivers in a 64-bit mask, so the queue takes one atomic per block.
 constexpr int kDiffRx = 64;
 __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, int32_t r0, int32_t r1,
-                                                                    int32_t wedge_tiles, uint2* __restrict__ queue,
+                                                                    int32_t wedge_tiles, uint32_t* __restrict__ queue,
                                                                     uint32_t* __restrict__ count) {
     __shared__ double rx[kDiffRx][3];
     __shared__ uint32_t wave_n[kBlock / 64];
@@ -272,38 +272,50 @@ __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, 
     while (keep) {
         const int r = __ffsll((long long)keep) - 1;
         keep &= keep - 1;
-        queue[at++] = uint2{(uint32_t)(rb + r), (uint32_t)wi};
+        queue[at++] = (uint32_t)(rb - r0 + r) * (uint32_t)a.sc.num_wedges + (uint32_t)wi;
     }
 }
 
-// Pass 2: the exact tests in fp64, then the leg from the transmitter, then, for
-// the survivors, the leg to the receiver.  A wave collects survivors of the
+// Wedge and receiver position of queue entry `it` = (receiver - r0) * wedges + wedge.
+__device__ __forceinline__ Wedge load_pair(const PathArgs& a, int32_t r0, uint32_t it, d3& P) {
+    const double* rx = a.rx + 3 * ((int64_t)r0 + it / (uint32_t)a.sc.num_wedges);
+    P = d3{rx[0], rx[1], rx[2]};
+    return a.sc.wedges[it % (uint32_t)a.sc.num_wedges];
+}
+
+// Pass 2: the exact tests in fp64, then the leg to the receiver, then, for the
+// survivors, the leg from the transmitter.  A wave collects survivors of the
 // first leg in LDS until it has 64, so that the second leg runs with full waves
-// too.  Bound by the any-hit traversals.
+// too.  Bound by the any-hit traversals: 0.76 ms for the pairs of 1024 street
+// receivers and 129,768 wedges of a city (0.94 ms with the transmitter's leg
+// first, 1.40 ms that way with 12 instead of 16 waves per CU; blocks of 512
+// with 64 staged nodes leave room for two per CU).
+constexpr int kLegBlock = 512, kLegNodes = 64;
 template <bool OVF>
-__global__ __launch_bounds__(kBlock) void diffraction_legs_kernel(PathArgs a, const uint2* __restrict__ queue,
-                                                                  const uint32_t* __restrict__ count,
-                                                                  uint2* __restrict__ out,
-                                                                  uint32_t* __restrict__ out_count) {
-    __shared__ int32_t stack[kStack][kBlock];
-    __shared__ Node lds_nodes[kLdsNodes];
-    __shared__ uint2 held[kBlock / 64][128];
-    const int n_lds = stage_nodes(a.sc, lds_nodes);
+__global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a, int32_t r0,
+                                                                     const uint32_t* __restrict__ queue,
+                                                                     const uint32_t* __restrict__ count,
+                                                                     uint32_t* __restrict__ out,
+                                                                     uint32_t* __restrict__ out_count) {
+    __shared__ int32_t stack[kStack][kLegBlock];
+    __shared__ Node lds_nodes[kLegNodes];
+    __shared__ uint32_t held[kLegBlock / 64][128];
+    const int n_lds = stage_nodes<kLegNodes>(a.sc, lds_nodes);
     const int lane = threadIdx.x & 63;
-    uint2* mine = held[threadIdx.x >> 6];
+    uint32_t* mine = held[threadIdx.x >> 6];
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
     const int64_t n = (int64_t)*count;
-    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / 64);
+    const int64_t nwaves = (int64_t)gridDim.x * (kLegBlock / 64);
     int have = 0;  // survivors of the first leg in `mine` (the same in every lane)
     auto second_leg = [&](int take) {
         bool ok = false;
-        uint2 it{0u, 0u};
+        uint32_t it = 0u;
         if (lane < take) {
             it = mine[have - take + lane];
-            const Wedge w = a.sc.wedges[it.y];
-            const d3 P{a.rx[3 * (int64_t)it.x], a.rx[3 * (int64_t)it.x + 1], a.rx[3 * (int64_t)it.x + 2]};
+            d3 P;
+            const Wedge w = load_pair(a, r0, it, P);
             EdgePoint pt;
-            ok = edge_point(w, S, P, pt) && !leg_blocked<kBlock, OVF>(a.sc, lds_nodes, n_lds, stack, pt.Q, P, w);
+            ok = edge_point(w, S, P, pt) && !leg_blocked<kLegBlock, OVF>(a.sc, lds_nodes, n_lds, stack, S, pt.Q, w);
         }
         have -= take;
         const uint64_t m = __ballot(ok);
@@ -314,15 +326,15 @@ __global__ __launch_bounds__(kBlock) void diffraction_legs_kernel(PathArgs a, co
             if (ok) out[b + __popcll(m & ((1ull << lane) - 1ull))] = it;
         }
     };
-    for (int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * 64; base < n; base += nwaves * 64) {
+    for (int64_t base = ((int64_t)blockIdx.x * (kLegBlock / 64) + (threadIdx.x >> 6)) * 64; base < n; base += nwaves * 64) {
         bool ok = false;
-        uint2 it{0u, 0u};
+        uint32_t it = 0u;
         if (base + lane < n) {
             it = queue[base + lane];
-            const Wedge w = a.sc.wedges[it.y];
-            const d3 P{a.rx[3 * (int64_t)it.x], a.rx[3 * (int64_t)it.x + 1], a.rx[3 * (int64_t)it.x + 2]};
+            d3 P;
+            const Wedge w = load_pair(a, r0, it, P);
             EdgePoint pt;
-            ok = edge_point(w, S, P, pt) && !leg_blocked<kBlock, OVF>(a.sc, lds_nodes, n_lds, stack, S, pt.Q, w);
+            ok = edge_point(w, S, P, pt) && !leg_blocked<kLegBlock, OVF>(a.sc, lds_nodes, n_lds, stack, pt.Q, P, w);
         }
         const uint64_t m = __ballot(ok);
         if (ok) mine[have + __popcll(m & ((1ull << lane) - 1ull))] = it;
@@ -333,15 +345,16 @@ __global__ __launch_bounds__(kBlock) void diffraction_legs_kernel(PathArgs a, co
 }
 
 // Pass 3: coefficients of the pairs that have a path.
-__global__ __launch_bounds__(kBlock) void diffraction_paths_kernel(PathArgs a, MatTable mats,
-                                                                   const uint2* __restrict__ queue,
+__global__ __launch_bounds__(kBlock) void diffraction_paths_kernel(PathArgs a, MatTable mats, int32_t r0,
+                                                                   const uint32_t* __restrict__ queue,
                                                                    const uint32_t* __restrict__ count) {
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
     const uint32_t n = *count;
     for (uint32_t item = blockIdx.x * kBlock + threadIdx.x; item < n; item += gridDim.x * kBlock) {
-        const int r = (int)queue[item].x, wi = (int)queue[item].y;
-        const d3 P{a.rx[3 * (int64_t)r], a.rx[3 * (int64_t)r + 1], a.rx[3 * (int64_t)r + 2]};
-        const Wedge w = a.sc.wedges[wi];
+        const int r = r0 + (int)(queue[item] / (uint32_t)a.sc.num_wedges);
+        const int wi = (int)(queue[item] % (uint32_t)a.sc.num_wedges);
+        d3 P;
+        const Wedge w = load_pair(a, r0, queue[item], P);
         EdgePoint pt;
         if (!edge_point(w, S, P, pt)) continue;
         const uint32_t slot = atomicAdd(a.counts + r, 1u);
@@ -420,7 +433,7 @@ int64_t diffraction_rx_chunk(int64_t nrx, int64_t nw) {
 size_t diffraction_scratch(int64_t nrx, int64_t num_wedges) {
     if (nrx <= 0 || num_wedges <= 0) return 0;
     const size_t pairs = (size_t)(diffraction_rx_chunk(nrx, num_wedges) * num_wedges);
-    return 256 + 2 * pairs * sizeof(uint2);
+    return 256 + 2 * pairs * sizeof(uint32_t);
 }
 
 hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s) {
@@ -428,8 +441,8 @@ hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, voi
     if (a.nrx <= 0 || nw <= 0) return hipSuccess;
     const int64_t chunk = diffraction_rx_chunk(a.nrx, nw);
     uint32_t* count = (uint32_t*)scratch;
-    uint2* q0 = (uint2*)((char*)scratch + 256);
-    uint2* q1 = q0 + chunk * nw;
+    uint32_t* q0 = (uint32_t*)((char*)scratch + 256);
+    uint32_t* q1 = q0 + chunk * nw;
     for (int64_t r0 = 0; r0 < a.nrx; r0 += chunk) {
         const int64_t r1 = std::min<int64_t>(a.nrx, r0 + chunk), pairs = (r1 - r0) * nw;
         hipError_t e = launch_fill_u32(count, 0u, 2, s);
@@ -437,14 +450,16 @@ hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, voi
         const int64_t wt = (nw + kBlock - 1) / kBlock, rt = (r1 - r0 + kDiffRx - 1) / kDiffRx;
         hipLaunchKernelGGL(diffraction_filter_kernel, dim3((unsigned)(wt * rt)), dim3(kBlock), 0, s, a, (int32_t)r0,
                            (int32_t)r1, (int32_t)wt, q0, count);
-        // three blocks of 52 KB per CU for the traversals
-        const dim3 grid((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 256 * 3));
+        // two blocks of 76 KB per CU for the traversals
+        const dim3 grid((unsigned)std::min<int64_t>((pairs + kLegBlock - 1) / kLegBlock, 256 * 2));
         if (a.sc.stack_need > kStack)
-            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kBlock), 0, s, a, q0, count, q1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, count,
+                               q1, count + 1);
         else
-            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kBlock), 0, s, a, q0, count, q1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, count,
+                               q1, count + 1);
         hipLaunchKernelGGL(diffraction_paths_kernel, dim3((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 512)),
-                           dim3(kBlock), 0, s, a, mats, q1, count + 1);
+                           dim3(kBlock), 0, s, a, mats, (int32_t)r0, q1, count + 1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -155,7 +155,7 @@ hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t m
 // records of a (depth = 1, faces[0] = wedge id, fd = 1).  scratch:
 // diffraction_scratch(nrx, num_wedges) bytes, at most two queues of
 // kDiffQueuePairs pairs (or of one receiver's).
-constexpr int64_t kDiffQueuePairs = int64_t(1) << 25;
+constexpr int64_t kDiffQueuePairs = int64_t(1) << 27;
 size_t diffraction_scratch(int64_t nrx, int64_t num_wedges);
 hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s);
 // Diffraction part of a coverage map: gain[c] += sum over wedges of |a|^2 of the

@@ -82,10 +82,11 @@ __device__ __forceinline__ uint32_t live_children(int4 ch) {
            (uint32_t)(ch.w != kEmptyChild);
 }
 
-// Copies the first min(num_nodes, kLdsNodes) nodes into LDS (whole block),
-// in the global layout.
+// Copies the first min(num_nodes, N) nodes into LDS (whole block), in the
+// global layout.
+template <int N = kLdsNodes>
 __device__ __forceinline__ int stage_nodes(const DevScene& sc, Node* lds) {
-    const int n = sc.num_nodes < kLdsNodes ? sc.num_nodes : kLdsNodes;
+    const int n = sc.num_nodes < N ? sc.num_nodes : N;
     const float4* src = reinterpret_cast<const float4*>(sc.nodes);
     float4* dst = reinterpret_cast<float4*>(lds);
     for (int i = threadIdx.x; i < 8 * n; i += blockDim.x) dst[i] = src[i];
