@@ -999,7 +999,8 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     const int fd = std::max(D, 1);
     const int64_t count = traced_count(p);
     // chunk of rays: records, masks and prefixes within about 1 GiB
-    const int64_t per_ray = (int64_t)std::max(D, 1) * (int64_t)(sizeof(rt::ScatPoint) + (nrx * 12 + 63) / 64);
+    const int64_t per_ray = (int64_t)std::max(D, 1) * (int64_t)(sizeof(rt::ScatPoint) + sizeof(rt::ScatHit) +
+                                                                     sizeof(int32_t) + (nrx * 12 + 63) / 64);
     int64_t chunk = std::min<int64_t>(int64_t(1) << 20, std::max<int64_t>(64, (int64_t(1) << 30) / per_ray));
     chunk = std::min<int64_t>(chunk, count);
     const int64_t nrec_pad = (chunk * std::max(D, 1) + 63) / 64 * 64;
@@ -1007,8 +1008,9 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     const size_t pts_bytes = (size_t)chunk * std::max(D, 1) * sizeof(rt::ScatPoint);
     const size_t mask_bytes = (size_t)nrx * nwords * sizeof(uint64_t);
     const size_t pre_bytes = ((size_t)nrx * nwords * sizeof(uint32_t) + 255) / 256 * 256;
-    const size_t cnt_bytes = (size_t)nrx * 2 * sizeof(int64_t);
-    RT_HIP(ensure(c->scat, pts_bytes + mask_bytes + pre_bytes + cnt_bytes));
+    const size_t hits_bytes = (size_t)nrec_pad * sizeof(rt::ScatHit), hit_bytes = (size_t)nrec_pad * sizeof(int32_t);
+    const size_t cnt_bytes = (size_t)nrx * sizeof(int64_t) + sizeof(int64_t);
+    RT_HIP(ensure(c->scat, pts_bytes + hits_bytes + hit_bytes + mask_bytes + pre_bytes + cnt_bytes));
     RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
     RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
     std::vector<double> rxp(3 * (size_t)nrx);
@@ -1034,10 +1036,13 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     sa.rx = (const double*)c->rx.p;
     sa.rx_ant = (const rt::Antenna*)c->rx_ant.p;
     sa.points = (rt::ScatPoint*)buf; buf += pts_bytes;
+    sa.hits = (rt::ScatHit*)buf; buf += hits_bytes;
+    sa.hit = (int32_t*)buf; buf += hit_bytes;
     sa.nrec_pad = nrec_pad;
     sa.masks = (uint64_t*)buf; buf += mask_bytes;
     sa.prefix = (uint32_t*)buf; buf += pre_bytes;
-    sa.chunk_total = (int64_t*)buf;
+    sa.first = (int64_t*)buf; buf += (size_t)nrx * sizeof(int64_t);
+    sa.num_hits = (uint32_t*)buf;
     sa.P = P;
     sa.fd = fd;
     rt::MatTable mats = make_mats(s, p->freq_hz);

@@ -174,10 +174,18 @@ struct alignas(16) ScatPoint {
     double n[3];    // unit normal facing the incident ray
     double g[8];    // 2x2 complex G: (perp, par) from departure (theta, phi), times S w r_{perp,par}
     double s;       // ray length from the transmitter
-    int32_t face;   // face of the hit (-1: no hit at this depth)
-    int32_t scat;   // 1 when the hit scatters (S > 0)
+    double pad;
 };
 static_assert(sizeof(ScatPoint) == 128, "scattering point size");
+
+// What the visibility test needs of a scattering hit (64 bytes).
+struct alignas(16) ScatHit {
+    double p[3], n[3];
+    int32_t face;
+    int32_t rec;    // its record, ray * max_depth + depth
+    int32_t pad[2];
+};
+static_assert(sizeof(ScatHit) == 64, "scattering hit size");
 
 struct ScatArgs {
     DevScene sc;
@@ -189,12 +197,15 @@ struct ScatArgs {
     Antenna tx_ant;
     const double* rx;         // [nrx][3]
     const Antenna* rx_ant;    // [nrx]
-    ScatPoint* points;        // [n][max_depth]
+    ScatPoint* points;        // [n][max_depth], written where the hit scatters
+    int32_t* hit;             // [n][max_depth] 2 face + (1 where S > 0), -1: no hit
+    ScatHit* hits;            // [n * max_depth] dense list of the scattering hits
+    uint32_t* num_hits;       // its length
     int64_t nrec_pad;         // n * max_depth rounded up to a multiple of 64
     uint64_t* masks;          // [nrx][nrec_pad / 64] visibility bits
     uint32_t* prefix;         // [nrx][nrec_pad / 64] visible records before each word (this chunk)
-    int64_t* chunk_total;     // [nrx]
-    int64_t* base;            // [nrx] paths of the earlier chunks (after the last chunk: the counts)
+    int64_t* first;           // [nrx] paths of the earlier chunks
+    int64_t* base;            // [nrx] paths so far (after the last chunk: the counts)
     int64_t P;                // slots per receiver
     float* a;                 // [nrx][P][2]
     float* T;                 // [nrx][P][8]
@@ -206,8 +217,8 @@ struct ScatArgs {
     int32_t* faces;           // [nrx][P][fd]
     int32_t fd;               // max_depth
 };
-// Points, visibility, scan and write passes of one chunk; base must hold the
-// counts of the earlier chunks (zero before the first).
+// All passes of one chunk; base must hold the counts of the earlier chunks (zero
+// before the first).
 hipError_t launch_scatter_chunk(const ScatArgs& a, const MatTable& mats, hipStream_t s);
 // Empty-slot values for the slots at or after every receiver's final count.
 hipError_t launch_scatter_tail(const ScatArgs& a, hipStream_t s);

@@ -10,21 +10,25 @@
 // on the transverse basis of the scattered direction k, and w the product of
 // sqrt(1 - S^2) over the earlier (specular) reflections.
 //
-// Per chunk of lattice rays, four passes:
+// Per chunk of lattice rays, six passes:
 //   1. points: one thread per ray traces max_depth segments (closest hit,
-//      fp64) and writes one record per hit, [ray][depth], holding the point,
-//      the normal facing the ray, the ray length, the face and the 2x2
-//      complex map G from the departure components (theta, phi) of the field
-//      to the scattered components (perp, par), S w and the Fresnel
-//      coefficients included;
-//   2. visibility: one thread per (receiver, record): front side of the face
-//      and an any-hit traversal of the open segment point -> receiver; a wave
-//      ballot stores 64 bits of the receiver's visibility mask;
-//   3. scan: per receiver, the exclusive prefix of the mask popcounts;
-//   4. write: one thread per visible (receiver, record) writes its path at
-//      slot base + prefix + rank in the word, when below the capacity.
+//      fp64) and writes one record per scattering hit, [ray][depth], holding the
+//      point, the normal facing the ray, the ray length and the 2x2 complex map G
+//      from the departure components (theta, phi) of the field to the scattered
+//      components (perp, par), S w and the Fresnel coefficients included;
+//   2. gather: the scattering hits, about four in ten (ray, depth) slots, into a
+//      dense list of what visibility needs (64 bytes each);
+//   3. visibility: for every (receiver, listed hit), front side of the face and
+//      an any-hit traversal of the open segment point -> receiver; a bit of the
+//      receiver's visibility mask per visible (ray, depth);
+//   4. scan: per receiver, the exclusive prefix of the mask popcounts;
+//   5. expand: every visible (ray, depth) writes its record's index at its slot
+//      (base + prefix + rank in the word, when below the capacity);
+//   6. write: one thread per path.
 // Slots therefore follow (lattice ray, depth) for every receiver, with no
-// sort and no atomics; the receiver's running base carries over the chunks.
+// sort; the receiver's running base carries over the chunks.
+#include <algorithm>
+
 #include "traverse.h"
 
 namespace rt {
@@ -64,12 +68,18 @@ __device__ __forceinline__ int64_t ray_index(const ScatArgs& a, int64_t j) {
     return a.begin + (a.pos0 + j) * a.stride;
 }
 
-__global__ __launch_bounds__(kBlock) void scatter_points_kernel(ScatArgs a, MatTable mats) {
+// Three waves per SIMD, as many as the LDS allows (two by the compiler's choice
+// of registers): 87 -> 74 us for 400,000 rays of depth 3.
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void scatter_points_kernel(ScatArgs a, MatTable mats) {
     __shared__ int32_t stack[kStack][kBlock];
     __shared__ Node lds_nodes[kLdsNodes];
     const int n_lds = stage_nodes(a.sc, lds_nodes);
     const int D = a.max_depth;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < a.n; j += (int64_t)gridDim.x * blockDim.x) {
+    // clears what the later passes of this chunk count and mark
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nthreads = (int64_t)gridDim.x * blockDim.x;
+    if (t0 == 0) *a.num_hits = 0u;
+    for (int64_t i = t0; i < a.nrx * (a.nrec_pad / 64); i += nthreads) a.masks[i] = 0ull;
+    for (int64_t j = t0; j < a.n; j += nthreads) {
         d3 d = fib_dir(ray_index(a, j), a.num_rays);
         d3 o{a.tx[0], a.tx[1], a.tx[2]};
         d3 th, ph;
@@ -79,14 +89,12 @@ __global__ __launch_bounds__(kBlock) void scatter_points_kernel(ScatArgs a, MatT
         int excl = -1;
         bool alive = true;
         for (int k = 0; k < D; ++k) {
-            ScatPoint* rec = a.points + j * D + k;
             int best = -1;
             double tbest = __builtin_inf();
             if (alive) best = traverse<false>(a.sc, lds_nodes, n_lds, o, d, excl, excl, a.tmin, tbest, stack);
             if (best < 0) {
                 alive = false;
-                rec->face = -1;
-                rec->scat = 0;
+                a.hit[j * D + k] = -1;
                 continue;
             }
             const Shade sh = a.sc.shades[best];
@@ -102,16 +110,16 @@ __global__ __launch_bounds__(kBlock) void scatter_points_kernel(ScatArgs a, MatT
             const d3 dr = add(d, scale(n, 2.0 * cos_i));
             const d3 elr = cross(ep, dr);
             const double S = (double)mats.m[sh.mat].scat;
-            rec->p[0] = p.x;
-            rec->p[1] = p.y;
-            rec->p[2] = p.z;
-            rec->n[0] = n.x;
-            rec->n[1] = n.y;
-            rec->n[2] = n.z;
-            rec->s = s;
-            rec->face = sh.face;
-            rec->scat = S > 0.0 ? 1 : 0;
+            a.hit[j * D + k] = 2 * sh.face + (S > 0.0 ? 1 : 0);
             if (S > 0.0) {
+                ScatPoint* rec = a.points + j * D + k;
+                rec->p[0] = p.x;
+                rec->p[1] = p.y;
+                rec->p[2] = p.z;
+                rec->n[0] = n.x;
+                rec->n[1] = n.y;
+                rec->n[2] = n.z;
+                rec->s = s;
                 const double sw = S * w;
                 const cd g00 = cmulr(cmul(rp, dotc(U0, ep)), sw), g01 = cmulr(cmul(rp, dotc(U1, ep)), sw);
                 const cd g10 = cmulr(cmul(rl, dotc(U0, eli)), sw), g11 = cmulr(cmul(rl, dotc(U1, eli)), sw);
@@ -134,84 +142,179 @@ __global__ __launch_bounds__(kBlock) void scatter_points_kernel(ScatArgs a, MatT
     }
 }
 
-// One thread per (receiver, record); nrec_pad is a multiple of 64, so a wave
-// covers 64 consecutive records of one receiver and its ballot is one mask word.
-__global__ __launch_bounds__(kBlock) void scatter_visibility_kernel(ScatArgs a) {
-    __shared__ int32_t stack[kStack][kBlock];
-    __shared__ Node lds_nodes[kLdsNodes];
-    const int n_lds = stage_nodes(a.sc, lds_nodes);
+// The scattering hits of the chunk into the dense list, in (ray, depth) order
+// within a block of kGather records.  One atomic on the list's length per
+// block: 4,700 of them, one per 256 records, took 49 us by themselves.
+constexpr int kGatherTiles = 8, kGather = kGatherTiles * kBlock;
+__global__ __launch_bounds__(kBlock) void scatter_gather_kernel(ScatArgs a) {
+    __shared__ uint32_t before[kGatherTiles * (kBlock / 64)];
+    __shared__ uint32_t start;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t nrec = a.n * a.max_depth;
-    const int64_t total = (int64_t)a.nrx * a.nrec_pad;
-    for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < total;
-         item += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = item / a.nrec_pad;
-        const int64_t q = item - r * a.nrec_pad;
-        bool vis = false;
-        if (q < nrec) {
-            const ScatPoint* rec = a.points + q;
-            if (rec->scat) {
-                const d3 p = ldp(rec->p), n = ldp(rec->n);
-                const d3 R{a.rx[3 * r], a.rx[3 * r + 1], a.rx[3 * r + 2]};
-                const d3 v = sub(R, p);
-                if (dot(v, n) > 0.0) {
-                    double tb = 1.0;
-                    vis = traverse<true>(a.sc, lds_nodes, n_lds, p, v, rec->face, -1, kOccEpsS, tb, stack) < 0;
-                }
-            }
+    for (int64_t b0 = (int64_t)blockIdx.x * kGather; b0 < nrec; b0 += (int64_t)gridDim.x * kGather) {
+        uint64_t m[kGatherTiles];
+#pragma unroll
+        for (int t = 0; t < kGatherTiles; ++t) {
+            const int64_t q = b0 + t * kBlock + threadIdx.x;
+            const int32_t h = q < nrec ? a.hit[q] : -1;
+            m[t] = __ballot(h >= 0 && (h & 1));
+            if (lane == 0) before[t * (kBlock / 64) + wv] = (uint32_t)__popcll(m[t]);
         }
-        const uint64_t m = __ballot(vis);
-        if ((threadIdx.x & 63) == 0) a.masks[item >> 6] = m;
+        __syncthreads();
+        if (threadIdx.x < 64) {  // exclusive prefix of the counts
+            constexpr int kCounts = kGatherTiles * (kBlock / 64);
+            static_assert(kCounts <= 64, "at most one lane per wave and tile");
+            const uint32_t c = lane < kCounts ? before[lane] : 0u;
+            uint32_t incl = c;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t v = __shfl_up(incl, off);
+                if (lane >= off) incl += v;
+            }
+            if (lane < kCounts) before[lane] = incl - c;
+            if (lane == 63) start = incl ? atomicAdd(a.num_hits, incl) : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kGatherTiles; ++t) {
+            if (!((m[t] >> lane) & 1ull)) continue;
+            const int64_t q = b0 + t * kBlock + threadIdx.x;
+            const ScatPoint* rec = a.points + q;
+            ScatHit* o = a.hits + start + before[t * (kBlock / 64) + wv] + __popcll(m[t] & ((1ull << lane) - 1ull));
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                o->p[i] = rec->p[i];
+                o->n[i] = rec->n[i];
+            }
+            o->face = a.hit[q] >> 1;
+            o->rec = (int32_t)q;
+        }
+        __syncthreads();
+    }
+}
+
+// One wave per 512 listed hits of one receiver: hits whose face's front side
+// sees the receiver collect in LDS until 64 are there, so that the traversals
+// run with full waves of neighbouring segments towards one point.  A thread per
+// (receiver, ray, depth) slot spent 806 us on 16 receivers and 400,000 rays of
+// depth 3, most lanes idle in each traversal; this takes 220 us.
+constexpr int kVisBlock = 512, kVisNodes = 64, kVisHits = 512;
+template <bool OVF>
+__global__ __launch_bounds__(kVisBlock) void scatter_visibility_kernel(ScatArgs a) {
+    __shared__ int32_t stack[kStack][kVisBlock];
+    __shared__ Node lds_nodes[kVisNodes];
+    __shared__ uint32_t held[kVisBlock / 64][128];
+    const int n_lds = stage_nodes<kVisNodes>(a.sc, lds_nodes);
+    const int lane = threadIdx.x & 63;
+    uint32_t* mine = held[threadIdx.x >> 6];
+    const int64_t n = (int64_t)*a.num_hits, per = (n + kVisHits - 1) / kVisHits;
+    const int64_t nwaves = (int64_t)gridDim.x * (kVisBlock / 64);
+    for (int64_t item = ((int64_t)blockIdx.x * kVisBlock + threadIdx.x) >> 6; item < a.nrx * per; item += nwaves) {
+        const int64_t r = item / per, h0 = (item - r * per) * kVisHits, h1 = min(n, h0 + kVisHits);
+        const d3 R{a.rx[3 * r], a.rx[3 * r + 1], a.rx[3 * r + 2]};
+        int have = 0;
+        auto trace = [&](int take) {
+            if (lane < take) {
+                const ScatHit* h = a.hits + mine[have - take + lane];
+                const d3 p = ldp(h->p);
+                double tb = 1.0;
+                if (traverse<true, false, kVisBlock, OVF>(a.sc, lds_nodes, n_lds, p, sub(R, p), h->face, -1, kOccEpsS,
+                                                          tb, stack) < 0)
+                    atomicOr((unsigned long long*)a.masks + r * (a.nrec_pad / 64) + (h->rec >> 6),
+                             1ull << (h->rec & 63));
+            }
+            have -= take;
+        };
+        for (int64_t b = h0; b < h1; b += 64) {
+            bool on = false;
+            if (b + lane < h1) {
+                const ScatHit* h = a.hits + b + lane;
+                on = dot(sub(R, ldp(h->p)), ldp(h->n)) > 0.0;
+            }
+            const uint64_t m = __ballot(on);
+            if (on) mine[have + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)(b + lane);
+            have += __popcll(m);
+            if (have >= 64) trace(64);
+        }
+        if (have) trace(have);
     }
 }
 
 // Per receiver (one block each, grid-stride over receivers): prefix[r][w] =
 // number of visible records of the receiver in mask words 0..w-1 of this
-// chunk; chunk_total[r] = all of them.
-constexpr int kScanBlock = 256;
+// chunk; the receiver's paths of this chunk take slots [first[r], base[r]).
+constexpr int kScanBlock = 1024, kScanWords = 4;
 __global__ __launch_bounds__(kScanBlock) void scatter_scan_kernel(const uint64_t* __restrict__ masks,
                                                                   uint32_t* __restrict__ prefix, int64_t nwords,
-                                                                  int32_t nrx, int64_t* __restrict__ chunk_total) {
+                                                                  int32_t nrx, int64_t* __restrict__ first,
+                                                                  int64_t* __restrict__ total) {
     __shared__ uint32_t wave_sum[kScanBlock / 64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int r = blockIdx.x; r < nrx; r += gridDim.x) {
         const uint64_t* mr = masks + (int64_t)r * nwords;
         uint32_t* pr = prefix + (int64_t)r * nwords;
         uint32_t carry = 0;
-        for (int64_t base = 0; base < nwords; base += kScanBlock) {
-            const int64_t w = base + threadIdx.x;
-            const uint32_t c = w < nwords ? (uint32_t)__popcll(mr[w]) : 0u;
-            uint32_t incl = c;
+        for (int64_t base = 0; base < nwords; base += kScanBlock * kScanWords) {
+            const int64_t w = base + (int64_t)threadIdx.x * kScanWords;
+            uint32_t c[kScanWords], mine = 0;
+#pragma unroll
+            for (int i = 0; i < kScanWords; ++i) {
+                c[i] = w + i < nwords ? (uint32_t)__popcll(mr[w + i]) : 0u;
+                mine += c[i];
+            }
+            uint32_t incl = mine;
             for (int off = 1; off < 64; off <<= 1) {
                 const uint32_t v = __shfl_up(incl, off);
                 if (lane >= off) incl += v;
             }
             if (lane == 63) wave_sum[wv] = incl;
             __syncthreads();
-            uint32_t before = carry;
-            for (int i = 0; i < wv; ++i) before += wave_sum[i];
-            if (w < nwords) pr[w] = before + incl - c;
-            uint32_t tile = 0;
-            for (int i = 0; i < kScanBlock / 64; ++i) tile += wave_sum[i];
+            uint32_t before = carry + incl - mine, tile = 0;
+            for (int i = 0; i < kScanBlock / 64; ++i) {
+                if (i < wv) before += wave_sum[i];
+                tile += wave_sum[i];
+            }
+#pragma unroll
+            for (int i = 0; i < kScanWords; ++i) {
+                if (w + i < nwords) pr[w + i] = before;
+                before += c[i];
+            }
             carry += tile;
             __syncthreads();
         }
-        if (threadIdx.x == 0) chunk_total[r] = carry;
+        if (threadIdx.x == 0) {
+            first[r] = total[r];
+            total[r] += carry;
+        }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void scatter_write_kernel(ScatArgs a) {
-    const int64_t total = (int64_t)a.nrx * a.nrec_pad;
+// Record index of every visible (ray, depth) into its slot of `ray`, where the
+// next pass finds it; one thread per mask word.
+__global__ __launch_bounds__(kBlock) void scatter_expand_kernel(ScatArgs a) {
+    const int64_t nwords = a.nrec_pad / 64;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < a.nrx * nwords; i += (int64_t)gridDim.x * kBlock) {
+        uint64_t m = a.masks[i];
+        if (!m) continue;
+        const int64_t r = i / nwords;
+        int64_t slot = a.first[r] + (int64_t)a.prefix[i];
+        for (; m && slot < a.P; ++slot) {
+            const int bit = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            a.ray[r * a.P + slot] = (i - r * nwords) * 64 + bit;
+        }
+    }
+}
+
+// One thread per path of the chunk: 30 us for 340,000 paths of 16 receivers.
+// One thread per (receiver, ray, depth) slot, 2% of them visible, took 666 us.
+__global__ __launch_bounds__(kBlock) void scatter_write_kernel(ScatArgs a, int32_t blocks_per) {
     const int D = a.max_depth;
     const double dom = 4.0 * kPi / (double)a.num_rays;
-    for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < total;
-         item += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t m = a.masks[item >> 6];
-        const int lane = (int)(item & 63);
-        if (!((m >> lane) & 1ull)) continue;
-        const int64_t r = item / a.nrec_pad;
-        const int64_t q = item - r * a.nrec_pad;
-        const int64_t slot = a.base[r] + (int64_t)a.prefix[item >> 6] + __popcll(m & ((1ull << lane) - 1ull));
-        if (slot >= a.P) continue;
+    const int64_t r = blockIdx.x / blocks_per;
+    const int64_t end = min(a.base[r], a.P);
+    for (int64_t slot = a.first[r] + (int64_t)(blockIdx.x % blocks_per) * kBlock + threadIdx.x; slot < end;
+         slot += (int64_t)blocks_per * kBlock) {
+        const int64_t q = a.ray[r * a.P + slot];
         const ScatPoint rec = a.points[q];
         const int64_t j = q / D;
         const int k = (int)(q - j * D);
@@ -259,15 +362,8 @@ __global__ __launch_bounds__(kBlock) void scatter_write_kernel(ScatArgs a) {
         a.depth[at] = k + 1;
         a.ray[at] = ray;
         int32_t* fc = a.faces + at * a.fd;
-        for (int i = 0; i < a.fd; ++i) fc[i] = i <= k ? a.points[j * D + i].face : -1;
+        for (int i = 0; i < a.fd; ++i) fc[i] = i <= k ? a.hit[j * D + i] >> 1 : -1;
     }
-}
-
-// base[r] += chunk_total[r]
-__global__ void scatter_advance_kernel(int64_t* __restrict__ base, const int64_t* __restrict__ chunk_total,
-                                       int32_t nrx) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nrx) base[r] += chunk_total[r];
 }
 
 // Slots at or after min(count, P) of every receiver: a = T = 0, tau = -1,
@@ -300,14 +396,23 @@ int64_t blocks_for(int64_t items, int64_t cap) {
 hipError_t launch_scatter_chunk(const ScatArgs& a, const MatTable& mats, hipStream_t s) {
     if (a.n <= 0 || a.max_depth <= 0) return hipSuccess;
     hipLaunchKernelGGL(scatter_points_kernel, dim3((unsigned)blocks_for(a.n, 16384)), dim3(kBlock), 0, s, a, mats);
-    const int64_t total = (int64_t)a.nrx * a.nrec_pad;
-    hipLaunchKernelGGL(scatter_visibility_kernel, dim3((unsigned)blocks_for(total, 65536)), dim3(kBlock), 0, s, a);
-    const int64_t nwords = a.nrec_pad / 64;
+    const int64_t nrec = a.n * a.max_depth, nwords = a.nrec_pad / 64;
+    hipLaunchKernelGGL(scatter_gather_kernel, dim3((unsigned)std::min<int64_t>((nrec + kGather - 1) / kGather, 65536)),
+                       dim3(kBlock), 0, s, a);
+    // two blocks per CU for the traversals
+    const int64_t waves = a.nrx * ((nrec + kVisHits - 1) / kVisHits);
+    const dim3 vgrid((unsigned)std::min<int64_t>((waves + kVisBlock / 64 - 1) / (kVisBlock / 64), 512));
+    if (a.sc.stack_need > kStack)
+        hipLaunchKernelGGL(scatter_visibility_kernel<true>, vgrid, dim3(kVisBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(scatter_visibility_kernel<false>, vgrid, dim3(kVisBlock), 0, s, a);
     hipLaunchKernelGGL(scatter_scan_kernel, dim3((unsigned)std::min<int64_t>(a.nrx, 65535)), dim3(kScanBlock), 0, s,
-                       a.masks, a.prefix, nwords, a.nrx, a.chunk_total);
-    hipLaunchKernelGGL(scatter_write_kernel, dim3((unsigned)blocks_for(total, 65536)), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(scatter_advance_kernel, dim3((unsigned)((a.nrx + 255) / 256)), dim3(256), 0, s, a.base,
-                       a.chunk_total, a.nrx);
+                       a.masks, a.prefix, nwords, a.nrx, a.first, a.base);
+    hipLaunchKernelGGL(scatter_expand_kernel, dim3((unsigned)blocks_for(a.nrx * nwords, 65536)), dim3(kBlock), 0, s, a);
+    // blocks per receiver: enough to fill the chip, none beyond the hits there can be
+    const int64_t per = std::max<int64_t>(1, std::min<int64_t>((std::min(nrec, a.P) + kBlock - 1) / kBlock,
+                                                               (4096 + a.nrx - 1) / a.nrx));
+    hipLaunchKernelGGL(scatter_write_kernel, dim3((unsigned)(a.nrx * per)), dim3(kBlock), 0, s, a, (int32_t)per);
     return hipGetLastError();
 }
 
