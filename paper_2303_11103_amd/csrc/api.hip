@@ -56,6 +56,31 @@ hipError_t ensure(DevBuf& b, size_t bytes) {
     return e;
 }
 
+// Pinned host buffer of one transfer; `done` was recorded behind the last copy
+// from it.
+struct Staging {
+    void* p = nullptr;
+    size_t bytes = 0;
+    hipEvent_t done = nullptr;
+};
+constexpr int kStagings = 8;
+constexpr size_t kStagingMax = size_t(4) << 20;  // larger uploads go from pageable memory and are waited for
+
+hipError_t ensure_pinned(Staging& b, size_t bytes) {
+    if (b.bytes >= bytes) return hipSuccess;
+    if (b.p) {
+        hipError_t e = hipHostFree(b.p);
+        if (e != hipSuccess) return e;
+    }
+    b.p = nullptr;
+    b.bytes = 0;
+    size_t want = 4096;
+    while (want < bytes) want <<= 1;
+    hipError_t e = hipHostMalloc(&b.p, want, hipHostMallocDefault);
+    if (e == hipSuccess) b.bytes = want;
+    return e;
+}
+
 // Scratch of rt_coverage_map_noalloc: the two ray queues and the queue-region
 // counters of the shoot-and-bounce launches, in a file-scope device array (one
 // copy per GPU, alive until the process ends).  Host code uses only the
@@ -106,13 +131,16 @@ struct rt_ctx {
     DevBuf pair_rx;    // receiver of each extracted pair
     DevBuf rgrid;      // receiver grid: cell starts then receiver lists
     DevBuf cands;
-    DevBuf rx;         // double [nrx][3]
-    DevBuf rx_ant;     // Antenna [nrx]
+    DevBuf rx;         // double [nrx][3], then Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
     DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
     DevBuf scat;       // scattered paths: points, masks, prefixes, counts of one chunk
     void* scratch = nullptr;  // this device's copy of the fixed scratch array
+    Staging stage[kStagings]; // uploads of small host arrays, used in turn
+    int stage_next = 0;
+    Staging result;           // counts read back
+    std::vector<char> rx_host;  // receiver positions and antennas of the current call
     int64_t last_candidates = 0;
     // launch timing of the shoot-and-bounce kernels
     bool profiling = false;
@@ -133,9 +161,45 @@ struct rt_scene {
     uint64_t scat_seed = 0;
     DevBuf nodes, tris, shades, faces, face_tris, leaf_of_input, wedges;
     rt::DevScene dev{};
+    double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};  // box of the triangles' corners
 };
 
 namespace {
+
+// Copies a host array to the device on the context's stream.  Small arrays go
+// through the context's pinned buffers and nothing waits; a buffer is used
+// again only after the copy behind its event.  Calls that upload were never
+// capturable (they waited for the stream); a captured copy would read a
+// pinned buffer at replay, so it is still refused.
+rt_status upload(rt_ctx* c, void* dst, const void* src, size_t bytes) {
+    if (!bytes) return RT_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    RT_HIP(hipStreamIsCapturing(c->stream, &cap));
+    if (cap != hipStreamCaptureStatusNone) return fail(RT_ERR_DEVICE, "this call cannot be captured into a graph");
+    if (bytes > kStagingMax) {
+        RT_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream));
+        RT_HIP(hipStreamSynchronize(c->stream));
+        return RT_OK;
+    }
+    Staging& b = c->stage[c->stage_next];
+    c->stage_next = (c->stage_next + 1) % kStagings;
+    if (b.done) RT_HIP(hipEventSynchronize(b.done));
+    else RT_HIP(hipEventCreateWithFlags(&b.done, hipEventDisableTiming));
+    RT_HIP(ensure_pinned(b, bytes));
+    std::memcpy(b.p, src, bytes);
+    RT_HIP(hipMemcpyAsync(dst, b.p, bytes, hipMemcpyHostToDevice, c->stream));
+    RT_HIP(hipEventRecord(b.done, c->stream));
+    return RT_OK;
+}
+
+// Reads device memory back through the context's pinned buffer and waits.
+rt_status read_back(rt_ctx* c, const void* src, size_t bytes, const void** out) {
+    RT_HIP(ensure_pinned(c->result, bytes));
+    RT_HIP(hipMemcpyAsync(c->result.p, src, bytes, hipMemcpyDeviceToHost, c->stream));
+    RT_HIP(hipStreamSynchronize(c->stream));
+    *out = c->result.p;
+    return RT_OK;
+}
 
 bool finite3(const float* p) { return std::isfinite(p[0]) && std::isfinite(p[1]) && std::isfinite(p[2]); }
 
@@ -191,6 +255,28 @@ rt::Antenna make_antenna(const rt_device* d) {
     a.pattern = d->pattern;
     a.pol = d->pol;
     return a;
+}
+
+// Puts positions (double [nrx][3]) and antennas of the receivers on the device
+// with one copy; kernels still queued on the stream (a gradient of the
+// previous call) read the same buffer before it.  Returns the host positions.
+rt_status stage_receivers(rt_ctx* c, const rt_device* rx, int32_t nrx, const double** rx_host = nullptr) {
+    const size_t pos = (size_t)nrx * 3 * sizeof(double), ant = (size_t)nrx * sizeof(rt::Antenna);
+    RT_HIP(ensure(c->rx, pos + ant));
+    if (c->rx_host.size() < pos + ant) c->rx_host.resize(pos + ant);
+    double* p = (double*)c->rx_host.data();
+    rt::Antenna* an = (rt::Antenna*)(c->rx_host.data() + pos);
+    for (int i = 0; i < nrx; ++i) {
+        for (int k = 0; k < 3; ++k) p[3 * i + k] = rx[i].pos[k];
+        // receivers mostly share one orientation: its sines are those of the one before
+        const bool same = i > 0 && !std::memcmp(&rx[i].yaw, &rx[i - 1].yaw, 3 * sizeof(float));
+        if (same) an[i] = an[i - 1];
+        else an[i] = make_antenna(rx + i);
+        an[i].pattern = rx[i].pattern;
+        an[i].pol = rx[i].pol;
+    }
+    if (rx_host) *rx_host = p;
+    return upload(c, c->rx.p, p, pos + ant);
 }
 
 rt::MatTable make_mats(const rt_scene* s, double freq) {
@@ -395,9 +481,15 @@ rt_status rt_destroy(rt_ctx* c) {
     if (!c) return RT_OK;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->rx_ant, &c->paths,
+    for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->paths,
                       &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->diff})
         if (b->p) (void)hipFree(b->p);
+    for (Staging& b : c->stage) {
+        if (b.done) (void)hipEventSynchronize(b.done);  // its copy may be on another stream than the last
+        if (b.done) (void)hipEventDestroy(b.done);
+        if (b.p) (void)hipHostFree(b.p);
+    }
+    if (c->result.p) (void)hipHostFree(c->result.p);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     delete c;
     return RT_OK;
@@ -437,6 +529,12 @@ rt_status rt_scene_create(rt_ctx* c, const float* V, int64_t nv, const int32_t* 
         if (e == hipSuccess && bytes) e = hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice);
     };
     const rt::HostScene& h = s->host;
+    for (const rt::Tri& tr : h.tris)
+        for (int k = 0; k < 3; ++k) {
+            const double v[3] = {tr.v0[k], tr.v0[k] + tr.e1[k], tr.v0[k] + tr.e2[k]};
+            s->lo[k] = std::min({s->lo[k], v[0], v[1], v[2]});
+            s->hi[k] = std::max({s->hi[k], v[0], v[1], v[2]});
+        }
     up(s->nodes, h.nodes.data(), h.nodes.size() * sizeof(rt::Node));
     up(s->tris, h.tris.data(), h.tris.size() * sizeof(rt::Tri));
     up(s->shades, h.shades.data(), h.shades.size() * sizeof(rt::Shade));
@@ -683,30 +781,20 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
         while (pcap < 16ull * (uint64_t)nrx * (uint64_t)P && pcap < (1ull << 26)) pcap <<= 1;
     const uint32_t max_cand = (uint32_t)std::min<uint64_t>(sphere ? pcap : cap, 1ull << 24);
     RT_HIP(ensure(c->cands, (size_t)max_cand * sizeof(rt::Cand)));
-    RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
-    RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
     const size_t per = (size_t)nrx * P;
     const size_t rec_bytes = per * (2 + 8 + 1 + 2 + 2) * sizeof(float) + per * (1 + fd) * sizeof(int32_t) +
                              (size_t)nrx * sizeof(uint32_t) + 3 * sizeof(uint32_t);
     RT_HIP(ensure(c->paths, rec_bytes));
-    std::vector<double> rxp(3 * (size_t)nrx);
-    std::vector<rt::Antenna> rxa(nrx);
-    for (int i = 0; i < nrx; ++i) {
-        for (int k = 0; k < 3; ++k) rxp[3 * i + k] = rx[i].pos[k];
-        rxa[i] = make_antenna(rx + i);
-    }
-    // staged on the context's stream: kernels still queued there (a gradient of
-    // the previous call) read these buffers
-    RT_HIP(hipMemcpyAsync(c->rx.p, rxp.data(), rxp.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    RT_HIP(hipMemcpyAsync(c->rx_ant.p, rxa.data(), rxa.size() * sizeof(rt::Antenna), hipMemcpyHostToDevice,
-                          c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));  // host staging vectors go out of scope
+    const double* rxp = nullptr;
+    if ((st = stage_receivers(c, rx, nrx, &rxp)) != RT_OK) return st;
     rt::SbrArgs sph{};
     if (sphere) {
         // every accepted pair has a path length below (max_depth + 1) times the
         // diagonal of the box holding the scene, the transmitters and the
         // receivers, so no sphere is wider than r_ins
-        double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
+        double lo[3], hi[3];
+        std::memcpy(lo, s->lo, sizeof lo);
+        std::memcpy(hi, s->hi, sizeof hi);
         auto grow = [&](double x, double y, double z) {
             const double v[3] = {x, y, z};
             for (int k = 0; k < 3; ++k) {
@@ -714,11 +802,6 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
                 hi[k] = std::max(hi[k], v[k]);
             }
         };
-        for (const rt::Tri& tr : s->host.tris) {
-            grow(tr.v0[0], tr.v0[1], tr.v0[2]);
-            grow(tr.v0[0] + tr.e1[0], tr.v0[1] + tr.e1[1], tr.v0[2] + tr.e1[2]);
-            grow(tr.v0[0] + tr.e2[0], tr.v0[1] + tr.e2[1], tr.v0[2] + tr.e2[2]);
-        }
         for (int i = 0; i < ntx; ++i) grow(tx[i].pos[0], tx[i].pos[1], tx[i].pos[2]);
         double rlo[3] = {1e300, 1e300, 1e300}, rhi[3] = {-1e300, -1e300, -1e300};
         for (int i = 0; i < nrx; ++i) {
@@ -766,16 +849,13 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
                 items.assign(start[ncell], 0);
             }
         }
-        RT_HIP(ensure(c->rgrid, (start.size() + items.size()) * sizeof(int32_t)));
-        RT_HIP(hipMemcpyAsync(c->rgrid.p, start.data(), start.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                              c->stream));
-        if (!items.empty())
-            RT_HIP(hipMemcpyAsync((int32_t*)c->rgrid.p + start.size(), items.data(), items.size() * sizeof(int32_t),
-                                  hipMemcpyHostToDevice, c->stream));
-        RT_HIP(hipStreamSynchronize(c->stream));
+        const size_t ncells = start.size();
+        start.insert(start.end(), items.begin(), items.end());
+        RT_HIP(ensure(c->rgrid, start.size() * sizeof(int32_t)));
+        if ((st = upload(c, c->rgrid.p, start.data(), start.size() * sizeof(int32_t))) != RT_OK) return st;
         sph.rx = (const double*)c->rx.p;
         sph.cell_start = (const int32_t*)c->rgrid.p;
-        sph.cell_rx = (const int32_t*)c->rgrid.p + start.size();
+        sph.cell_rx = (const int32_t*)c->rgrid.p + ncells;
         RT_HIP(ensure(c->pairs, pcap * sizeof(uint64_t)));
         RT_HIP(ensure(c->pair_rx, (size_t)max_cand * sizeof(int32_t)));
         sph.pairs = (uint64_t*)c->pairs.p;
@@ -787,7 +867,7 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     pa.freq = p->freq_hz;
     pa.lambda = kC0 / p->freq_hz;
     pa.rx = (const double*)c->rx.p;
-    pa.rx_ant = (const rt::Antenna*)c->rx_ant.p;
+    pa.rx_ant = (const rt::Antenna*)((const double*)c->rx.p + 3 * (size_t)nrx);
     pa.nrx = nrx;
     pa.cands = (const rt::Cand*)c->cands.p;
     pa.pair_rx = sphere ? (const int32_t*)c->pair_rx.p : nullptr;
@@ -807,7 +887,6 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     sph.pairs_overflow = ncand + 2;
     rt::MatTable mats = make_mats(s, p->freq_hz);
     int worst = 0;
-    std::vector<int32_t> counts_h(nrx);
     for (int t = 0; t < ntx; ++t) {
         RT_HIP(hipMemsetAsync(c->table.p, 0xff, cap * sizeof(uint64_t), c->stream));
         if (sphere) RT_HIP(hipMemsetAsync(c->pairs.p, 0xff, pcap * sizeof(uint64_t), c->stream));
@@ -827,9 +906,10 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
             RT_HIP(rt::launch_extract_candidates((const uint64_t*)c->table.p, cap, p->max_depth,
                                                  (rt::Cand*)c->cands.p, ncand, max_cand, c->stream));
         }
-        uint32_t hc[3] = {0, 0, 0};
-        RT_HIP(hipMemcpyAsync(hc, ncand, sizeof(hc), hipMemcpyDeviceToHost, c->stream));
-        RT_HIP(hipStreamSynchronize(c->stream));
+        const void* back = nullptr;
+        uint32_t hc[3];
+        if ((st = read_back(c, ncand, sizeof(hc), &back)) != RT_OK) return st;
+        std::memcpy(hc, back, sizeof(hc));
         if (hc[1]) return fail(RT_ERR_CAPACITY, "candidate table overflow: too many distinct face sequences");
         if (hc[2]) return fail(RT_ERR_CAPACITY, "reception-sphere pair set overflow");
         if (hc[0] > max_cand) return fail(RT_ERR_CAPACITY, "more than 2^24 candidates");
@@ -841,10 +921,8 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
         const size_t off = (size_t)t * per;
         RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
                                      depth + off, faces + (size_t)fd * off, num_paths + (size_t)t * nrx, c->stream));
-        RT_HIP(hipMemcpyAsync(counts_h.data(), num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t),
-                              hipMemcpyDeviceToHost, c->stream));
-        RT_HIP(hipStreamSynchronize(c->stream));
-        for (int i = 0; i < nrx; ++i) worst = std::max(worst, counts_h[i]);
+        if ((st = read_back(c, num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t), &back)) != RT_OK) return st;
+        for (int i = 0; i < nrx; ++i) worst = std::max(worst, ((const int32_t*)back)[i]);
     }
     if (worst > P)
         return fail(RT_ERR_CAPACITY, "a receiver has " + std::to_string(worst) +
@@ -927,25 +1005,14 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
                              (size_t)nrx * sizeof(uint32_t);
     RT_HIP(ensure(c->paths, rec_bytes));
     RT_HIP(ensure(c->diff, rt::diffraction_scratch(nrx, s->dev.num_wedges)));
-    RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
-    RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
-    std::vector<double> rxp(3 * (size_t)nrx);
-    std::vector<rt::Antenna> rxa(nrx);
-    for (int i = 0; i < nrx; ++i) {
-        for (int k = 0; k < 3; ++k) rxp[3 * i + k] = rx[i].pos[k];
-        rxa[i] = make_antenna(rx + i);
-    }
-    RT_HIP(hipMemcpyAsync(c->rx.p, rxp.data(), rxp.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    RT_HIP(hipMemcpyAsync(c->rx_ant.p, rxa.data(), rxa.size() * sizeof(rt::Antenna), hipMemcpyHostToDevice,
-                          c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));  // host staging vectors go out of scope
+    if ((st = stage_receivers(c, rx, nrx)) != RT_OK) return st;
     char* base = (char*)c->paths.p;
     rt::PathArgs pa{};
     pa.sc = s->dev;
     pa.freq = freq_hz;
     pa.lambda = kC0 / freq_hz;
     pa.rx = (const double*)c->rx.p;
-    pa.rx_ant = (const rt::Antenna*)c->rx_ant.p;
+    pa.rx_ant = (const rt::Antenna*)((const double*)c->rx.p + 3 * (size_t)nrx);
     pa.nrx = nrx;
     pa.P = P;
     pa.fd = 1;
@@ -960,19 +1027,17 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
     pa.counts = (uint32_t*)base;
     rt::MatTable mats = make_mats(s, freq_hz);
     int worst = 0;
-    std::vector<int32_t> counts_h(nrx);
     for (int t = 0; t < ntx; ++t) {
         for (int i = 0; i < 3; ++i) pa.tx[i] = tx[t].pos[i];
         pa.tx_ant = make_antenna(tx + t);
+        const void* back = nullptr;
         RT_HIP(hipMemsetAsync(pa.counts, 0, (size_t)nrx * sizeof(uint32_t), c->stream));
         RT_HIP(rt::launch_diffraction_paths(pa, mats, c->diff.p, c->stream));
         const size_t off = (size_t)t * per;
         RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
                                      depth_sorted, wedge + off, num_paths + (size_t)t * nrx, c->stream));
-        RT_HIP(hipMemcpyAsync(counts_h.data(), num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t),
-                              hipMemcpyDeviceToHost, c->stream));
-        RT_HIP(hipStreamSynchronize(c->stream));
-        for (int i = 0; i < nrx; ++i) worst = std::max(worst, counts_h[i]);
+        if ((st = read_back(c, num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t), &back)) != RT_OK) return st;
+        for (int i = 0; i < nrx; ++i) worst = std::max(worst, ((const int32_t*)back)[i]);
     }
     if (worst > P)
         return fail(RT_ERR_CAPACITY, "a receiver has " + std::to_string(worst) +
@@ -1011,18 +1076,7 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     const size_t hits_bytes = (size_t)nrec_pad * sizeof(rt::ScatHit), hit_bytes = (size_t)nrec_pad * sizeof(int32_t);
     const size_t cnt_bytes = (size_t)nrx * sizeof(int64_t) + sizeof(int64_t);
     RT_HIP(ensure(c->scat, pts_bytes + hits_bytes + hit_bytes + mask_bytes + pre_bytes + cnt_bytes));
-    RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
-    RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
-    std::vector<double> rxp(3 * (size_t)nrx);
-    std::vector<rt::Antenna> rxa(nrx);
-    for (int i = 0; i < nrx; ++i) {
-        for (int k = 0; k < 3; ++k) rxp[3 * i + k] = rx[i].pos[k];
-        rxa[i] = make_antenna(rx + i);
-    }
-    RT_HIP(hipMemcpyAsync(c->rx.p, rxp.data(), rxp.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    RT_HIP(hipMemcpyAsync(c->rx_ant.p, rxa.data(), rxa.size() * sizeof(rt::Antenna), hipMemcpyHostToDevice,
-                          c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));  // host staging vectors go out of scope
+    if ((st = stage_receivers(c, rx, nrx)) != RT_OK) return st;
     char* buf = (char*)c->scat.p;
     rt::ScatArgs sa{};
     sa.sc = s->dev;
@@ -1034,7 +1088,7 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     sa.tmin = p->t_min;
     sa.lambda = kC0 / p->freq_hz;
     sa.rx = (const double*)c->rx.p;
-    sa.rx_ant = (const rt::Antenna*)c->rx_ant.p;
+    sa.rx_ant = (const rt::Antenna*)((const double*)c->rx.p + 3 * (size_t)nrx);
     sa.points = (rt::ScatPoint*)buf; buf += pts_bytes;
     sa.hits = (rt::ScatHit*)buf; buf += hits_bytes;
     sa.hit = (int32_t*)buf; buf += hit_bytes;
@@ -1047,7 +1101,6 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
     sa.fd = fd;
     rt::MatTable mats = make_mats(s, p->freq_hz);
     int64_t worst = 0;
-    std::vector<int64_t> counts_h(nrx);
     for (int t = 0; t < ntx; ++t) {
         for (int i = 0; i < 3; ++i) sa.tx[i] = tx[t].pos[i];
         sa.tx_ant = make_antenna(tx + t);
@@ -1068,10 +1121,9 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
             RT_HIP(rt::launch_scatter_chunk(sa, mats, c->stream));
         }
         RT_HIP(rt::launch_scatter_tail(sa, c->stream));
-        RT_HIP(hipMemcpyAsync(counts_h.data(), sa.base, (size_t)nrx * sizeof(int64_t), hipMemcpyDeviceToHost,
-                              c->stream));
-        RT_HIP(hipStreamSynchronize(c->stream));
-        for (int i = 0; i < nrx; ++i) worst = std::max(worst, counts_h[i]);
+        const void* back = nullptr;
+        if ((st = read_back(c, sa.base, (size_t)nrx * sizeof(int64_t), &back)) != RT_OK) return st;
+        for (int i = 0; i < nrx; ++i) worst = std::max(worst, ((const int64_t*)back)[i]);
     }
     if (worst > P)
         return fail(RT_ERR_CAPACITY, "a receiver has " + std::to_string(worst) +
@@ -1092,18 +1144,7 @@ static rt_status paths_grad_impl(rt_ctx* c, rt_scene* s, const rt_trace_params* 
     for (int i = 0; i < nrx; ++i)
         if ((st = check_device(rx + i, "rx", s->host.max_abs)) != RT_OK) return st;
     RT_HIP(hipSetDevice(c->device));
-    RT_HIP(ensure(c->rx, (size_t)nrx * 3 * sizeof(double)));
-    RT_HIP(ensure(c->rx_ant, (size_t)nrx * sizeof(rt::Antenna)));
-    std::vector<double> rxp(3 * (size_t)nrx);
-    std::vector<rt::Antenna> rxa(nrx);
-    for (int i = 0; i < nrx; ++i) {
-        for (int k = 0; k < 3; ++k) rxp[3 * i + k] = rx[i].pos[k];
-        rxa[i] = make_antenna(rx + i);
-    }
-    RT_HIP(hipMemcpyAsync(c->rx.p, rxp.data(), rxp.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    RT_HIP(hipMemcpyAsync(c->rx_ant.p, rxa.data(), rxa.size() * sizeof(rt::Antenna), hipMemcpyHostToDevice,
-                          c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));  // host staging vectors go out of scope
+    if ((st = stage_receivers(c, rx, nrx)) != RT_OK) return st;
     const int nm = (int)s->mats.size();
     RT_HIP(hipMemsetAsync(grad, 0, (size_t)(2 * nm + 5) * sizeof(double), c->stream));
     rt::GradArgs g{};
@@ -1117,7 +1158,7 @@ static rt_status paths_grad_impl(rt_ctx* c, rt_scene* s, const rt_trace_params* 
     g.tx_pattern = tx->pattern;
     g.tx_pol = tx->pol;
     g.rx = (const double*)c->rx.p;
-    g.rx_ant = (const rt::Antenna*)c->rx_ant.p;
+    g.rx_ant = (const rt::Antenna*)((const double*)c->rx.p + 3 * (size_t)nrx);
     g.nrx = nrx;
     g.P = P;
     g.fd = std::max(p->max_depth, 1);
@@ -1233,8 +1274,8 @@ rt_status cfr_setup(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, const float*
     const size_t head = (h.size() * sizeof(double) + 15) / 16 * 16;
     RT_HIP(ensure(c->chan, head + (scratch ? rt::cfr_adjoint_scratch(cf) : 0)));
     if (scratch) *scratch = (char*)c->chan.p + head;
-    RT_HIP(hipMemcpyAsync(c->chan.p, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    RT_HIP(hipStreamSynchronize(c->stream));  // the staging vector goes out of scope
+    const rt_status st = upload(c, c->chan.p, h.data(), h.size() * sizeof(double));
+    if (st != RT_OK) return st;
     const double* d = (const double*)c->chan.p;
     cf.nrx = nrx;
     cf.a = a;
