@@ -626,9 +626,12 @@ rt_status rt_trace_record(rt_ctx* c, rt_scene* s, const rt_trace_params* p, cons
     if (st != RT_OK) return st;
     if ((st = check_device(tx, "tx", s->host.max_abs)) != RT_OK) return st;
     RT_HIP(hipSetDevice(c->device));
-    const int64_t n = traced_count(p) * (p->max_depth + 1);
-    RT_HIP(hipMemsetD32Async((hipDeviceptr_t)hit_tri, (int)-2, (size_t)n, c->stream));
-    RT_HIP(hipMemsetAsync(hit_t, 0xff, (size_t)n * sizeof(double), c->stream));  // NaN until written
+    // every ray writes its first segment; later ones are -2 and NaN until written
+    const int64_t first = traced_count(p), n = first * p->max_depth;
+    if (n > 0) {
+        RT_HIP(hipMemsetD32Async((hipDeviceptr_t)(hit_tri + first), (int)-2, (size_t)n, c->stream));
+        RT_HIP(hipMemsetAsync(hit_t + first, 0xff, (size_t)n * sizeof(double), c->stream));
+    }
     return run_sbr(c, s, p, tx, nullptr, nullptr, rt::kModeRecord, nullptr, nullptr, nullptr, hit_tri, hit_t,
                    nullptr, 0, nullptr);
 }
@@ -1195,7 +1198,7 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     const int nm = (int)s->mats.size();
     if (nm > rt::kCovMaxMat) return fail(RT_ERR_ARG, "coverage gradient supports at most 4 materials");
     RT_HIP(hipSetDevice(c->device));
-    RT_HIP(hipMemsetAsync(out, 0, (size_t)(2 * nm + 3) * sizeof(double), c->stream));
+    RT_HIP(rt::launch_fill_u32(out, 0u, (size_t)(2 * nm + 3) * 2, c->stream));
     rt::CovGradArgs a{};
     a.sc = s->dev;
     a.num_rays = p->num_rays;
@@ -1205,9 +1208,16 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.max_depth = p->max_depth;
     a.nm = nm;
     for (int k = 0; k < 3; ++k) a.tx[k] = tx->pos[k];
-    a.yaw = tx->yaw;
-    a.pitch = tx->pitch;
-    a.roll = tx->roll;
+    rot(tx->yaw, tx->pitch, tx->roll, a.R);
+    const double yaw = tx->yaw, pitch = tx->pitch, roll = tx->roll;  // fp64 sines of the fp32 angles
+    const double cy = std::cos(yaw), sy = std::sin(yaw), cp = std::cos(pitch), sp = std::sin(pitch);
+    const double cr = std::cos(roll), sr = std::sin(roll);
+    const double dy[9] = {-sy * cp, -sy * sp * sr - cy * cr, -sy * sp * cr + cy * sr,
+                          cy * cp,  cy * sp * sr - sy * cr,  cy * sp * cr + sy * sr, 0.0, 0.0, 0.0};
+    const double dp[9] = {-cy * sp, cy * cp * sr, cy * cp * cr, -sy * sp, sy * cp * sr, sy * cp * cr,
+                          -cp, -sp * sr, -sp * cr};
+    std::memcpy(a.Ryaw, dy, sizeof dy);
+    std::memcpy(a.Rpitch, dp, sizeof dp);
     a.tx_pattern = tx->pattern;
     a.tx_pol = tx->pol;
     a.gnx = g->nx;
@@ -1225,7 +1235,7 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.hit_tri = hit_tri;
     a.hit_t = hit_t;
     a.out = out;
-    RT_HIP(rt::launch_coverage_grad(a, make_mats(s, p->freq_hz), grid_for(c), c->stream));
+    RT_HIP(rt::launch_coverage_grad(a, make_mats(s, p->freq_hz), c->num_cu, c->stream));
     return RT_OK;
 }
 

@@ -220,8 +220,11 @@ __device__ __forceinline__ d3 lambert_dir(d3 n, double u1, double u2) {
 
 // Direction of Fibonacci-lattice ray i of N (Sec. II-B): z = 1 - (2i+1)/N,
 // azimuth 2 pi frac(i g) with frac(i g) = (i * 0x9E3779B97F4A7C15 mod 2^64) / 2^64.
+__device__ __forceinline__ double fib_height(int64_t i, int64_t N) {
+    return 1.0 - (2.0 * (double)i + 1.0) / (double)N;
+}
 __device__ __forceinline__ d3 fib_dir(int64_t i, int64_t N) {
-    const double z = 1.0 - (2.0 * (double)i + 1.0) / (double)N;
+    const double z = fib_height(i, N);
     const double rho = sqrt((1.0 - z) * (1.0 + z));
     const uint64_t h = (uint64_t)i * 0x9E3779B97F4A7C15ull;
     double s, c;

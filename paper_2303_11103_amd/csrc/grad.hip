@@ -28,89 +28,108 @@ constexpr int NT = 5;
 constexpr int kMaxK = 8;
 constexpr double kEps0 = 8.8541878128e-12;
 
-struct D {
+// Dual number with N tangents.
+template <int N>
+struct Dual {
     double v;
-    double d[NT];
+    double d[N];
 };
-__device__ __forceinline__ D dc(double v) {
-    D r;
+using D = Dual<NT>;
+template <int N>
+__device__ __forceinline__ Dual<N> dconst(double v) {
+    Dual<N> r;
     r.v = v;
-    for (int i = 0; i < NT; ++i) r.d[i] = 0.0;
+    for (int i = 0; i < N; ++i) r.d[i] = 0.0;
     return r;
 }
-__device__ __forceinline__ D operator+(D a, D b) {
-    D r;
+__device__ __forceinline__ D dc(double v) { return dconst<NT>(v); }
+template <int N>
+__device__ __forceinline__ Dual<N> operator+(Dual<N> a, Dual<N> b) {
+    Dual<N> r;
     r.v = a.v + b.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] + b.d[i];
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] + b.d[i];
     return r;
 }
-__device__ __forceinline__ D operator-(D a, D b) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> operator-(Dual<N> a, Dual<N> b) {
+    Dual<N> r;
     r.v = a.v - b.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] - b.d[i];
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] - b.d[i];
     return r;
 }
-__device__ __forceinline__ D operator-(D a) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> operator-(Dual<N> a) {
+    Dual<N> r;
     r.v = -a.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = -a.d[i];
+    for (int i = 0; i < N; ++i) r.d[i] = -a.d[i];
     return r;
 }
-__device__ __forceinline__ D operator*(D a, D b) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> operator*(Dual<N> a, Dual<N> b) {
+    Dual<N> r;
     r.v = a.v * b.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] * b.v + a.v * b.d[i];
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] * b.v + a.v * b.d[i];
     return r;
 }
-__device__ __forceinline__ D operator*(D a, double s) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> operator*(Dual<N> a, double s) {
+    Dual<N> r;
     r.v = a.v * s;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] * s;
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] * s;
     return r;
 }
-__device__ __forceinline__ D operator/(D a, D b) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> operator/(Dual<N> a, Dual<N> b) {
+    Dual<N> r;
     r.v = a.v / b.v;
     const double ib = 1.0 / b.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = (a.d[i] - r.v * b.d[i]) * ib;
+    for (int i = 0; i < N; ++i) r.d[i] = (a.d[i] - r.v * b.d[i]) * ib;
     return r;
 }
-__device__ __forceinline__ D dsqrt(D a) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> dsqrt(Dual<N> a) {
+    Dual<N> r;
     r.v = sqrt(a.v);
     const double k = r.v > 0.0 ? 0.5 / r.v : 0.0;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] * k;
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] * k;
     return r;
 }
-__device__ __forceinline__ D dfun(D a, double v, double dv) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> dfun(Dual<N> a, double v, double dv) {
+    Dual<N> r;
     r.v = v;
-    for (int i = 0; i < NT; ++i) r.d[i] = a.d[i] * dv;
+    for (int i = 0; i < N; ++i) r.d[i] = a.d[i] * dv;
     return r;
 }
 __device__ __forceinline__ D dcos(D a) { return dfun(a, cos(a.v), -sin(a.v)); }
 __device__ __forceinline__ D dsin(D a) { return dfun(a, sin(a.v), cos(a.v)); }
-__device__ __forceinline__ D dacos(D a) {
+template <int N>
+__device__ __forceinline__ Dual<N> dacos(Dual<N> a) {
     const double x = fmin(fmax(a.v, -1.0), 1.0);
     const double den = sqrt(fmax(1.0 - x * x, 1e-300));
     return dfun(a, acos(x), -1.0 / den);
 }
-__device__ __forceinline__ D datan2(D y, D x) {
-    D r;
+template <int N>
+__device__ __forceinline__ Dual<N> datan2(Dual<N> y, Dual<N> x) {
+    Dual<N> r;
     r.v = atan2(y.v, x.v);
     const double den = x.v * x.v + y.v * y.v;
-    for (int i = 0; i < NT; ++i) r.d[i] = den > 0.0 ? (x.v * y.d[i] - y.v * x.d[i]) / den : 0.0;
+    for (int i = 0; i < N; ++i) r.d[i] = den > 0.0 ? (x.v * y.d[i] - y.v * x.d[i]) / den : 0.0;
     return r;
 }
-__device__ __forceinline__ D dexp10(D a) {
+template <int N>
+__device__ __forceinline__ Dual<N> dexp10(Dual<N> a) {
     const double v = exp10(a.v);
     return dfun(a, v, v * 2.302585092994045684);
 }
-__device__ __forceinline__ D dmin(D a, D b) { return a.v <= b.v ? a : b; }
+template <int N>
+__device__ __forceinline__ Dual<N> dmin(Dual<N> a, Dual<N> b) { return a.v <= b.v ? a : b; }
 
-struct D3 {
-    D x, y, z;
+template <int N>
+struct Dual3 {
+    Dual<N> x, y, z;
 };
+using D3 = Dual3<NT>;
 __device__ __forceinline__ D3 operator+(D3 a, D3 b) { return D3{a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ __forceinline__ D3 operator-(D3 a, D3 b) { return D3{a.x - b.x, a.y - b.y, a.z - b.z}; }
 __device__ __forceinline__ D3 operator*(D3 a, D s) { return D3{a.x * s, a.y * s, a.z * s}; }
@@ -170,36 +189,42 @@ __device__ DRot drot(D yaw, D pitch, D roll) {
     return o;
 }
 
-__device__ D3 dantenna(const DRot& Rr, int pattern, D3 d, int pol = 0) {
-    const D* R = Rr.R;
-    D lx = R[0] * d.x + R[3] * d.y + R[6] * d.z;
-    D ly = R[1] * d.x + R[4] * d.y + R[7] * d.z;
-    D lz = R[2] * d.x + R[5] * d.y + R[8] * d.z;
-    D rho = dsqrt(lx * lx + ly * ly);
-    D cph = dc(1.0), sph = dc(0.0);
+// Field of an antenna with orientation R towards the local direction (lx, ly, lz).
+template <int N>
+__device__ Dual3<N> dantenna_local(const Dual<N>* R, int pattern, Dual<N> lx, Dual<N> ly, Dual<N> lz, int pol) {
+    using T = Dual<N>;
+    T rho = dsqrt(lx * lx + ly * ly);
+    T cph = dconst<N>(1.0), sph = dconst<N>(0.0);
     if (rho.v > 0.0) {
         cph = lx / rho;
         sph = ly / rho;
     }
-    D c = dc(1.0);
+    T c = dconst<N>(1.0);
     if (pattern == kPatTR38901) {
         const double kDeg = 180.0 / kPi;
-        D th = dacos(lz) * kDeg;
-        D ph = datan2(ly, lx) * kDeg;
-        D u = (th - dc(90.0)) * (1.0 / 65.0);
-        D w = ph * (1.0 / 65.0);
-        D av = -dmin(u * u * 12.0, dc(30.0));
-        D ah = -dmin(w * w * 12.0, dc(30.0));
-        D a = -dmin(-(av + ah), dc(30.0));
-        c = dexp10((a + dc(8.0)) * (1.0 / 20.0));
+        T th = dacos(lz) * kDeg;
+        T ph = datan2(ly, lx) * kDeg;
+        T u = (th - dconst<N>(90.0)) * (1.0 / 65.0);
+        T w = ph * (1.0 / 65.0);
+        T av = -dmin(u * u * 12.0, dconst<N>(30.0));
+        T ah = -dmin(w * w * 12.0, dconst<N>(30.0));
+        T a = -dmin(-(av + ah), dconst<N>(30.0));
+        c = dexp10((a + dconst<N>(8.0)) * (1.0 / 20.0));
     } else if (pattern == kPatDipole) {
         c = rho * 1.2247448713915890;  // sqrt(1.5) sin(theta)
     }
     double zc, zs;
     pol_angle(pol, zc, zs);
-    const D ct = c * zc, cp = c * zs;
-    D tx = ct * lz * cph - cp * sph, ty = ct * lz * sph + cp * cph, tz = -(ct * rho);
-    return D3{R[0] * tx + R[1] * ty + R[2] * tz, R[3] * tx + R[4] * ty + R[5] * tz, R[6] * tx + R[7] * ty + R[8] * tz};
+    const T ct = c * zc, cp = c * zs;
+    T tx = ct * lz * cph - cp * sph, ty = ct * lz * sph + cp * cph, tz = -(ct * rho);
+    return Dual3<N>{R[0] * tx + R[1] * ty + R[2] * tz, R[3] * tx + R[4] * ty + R[5] * tz,
+                    R[6] * tx + R[7] * ty + R[8] * tz};
+}
+
+__device__ D3 dantenna(const DRot& Rr, int pattern, D3 d, int pol = 0) {
+    const D* R = Rr.R;
+    return dantenna_local(R, pattern, R[0] * d.x + R[3] * d.y + R[6] * d.z, R[1] * d.x + R[4] * d.y + R[7] * d.z,
+                          R[2] * d.x + R[5] * d.y + R[8] * d.z, pol);
 }
 
 __device__ D3 dperp(D3 d, d3 n) {
@@ -370,158 +395,288 @@ __global__ void power_grad_kernel(GradArgs g, MatTable mats) {
 // coverage analogue of the received-power gradient; Sec. III-B optimises a
 // transmitter orientation by gradient steps).  Ray geometry does not depend
 // on these parameters, so the recorded hits (triangle and distance per
-// segment) fix every ray; one thread per ray replays it in fp64 with the
-// same formulas as the shoot-and-bounce kernel and carries, beside the field
-// E, its tangents dE/dtheta:
-//   * at launch, d F_tx / d(yaw, pitch) from the dual-number transmit pattern;
-//   * at a reflection off material m, E' = R E gives
-//     dE'/dtheta = R dE/dtheta + [theta of m] (dR/d eta) E (d eta/d theta),
-//     with dR/d eta from d r_perp / d eta and d r_par / d eta as above;
-//   * every crossing of the grid plane inside the region adds
+// segment) fix every ray, replayed in fp64 with the formulas of the
+// shoot-and-bounce kernel in two passes:
+//   * a walk of the geometry alone, which marks the segments that cross the
+//     grid plane inside the region;
+//   * for the rays with a mark, the field E and its tangents dE/dtheta up to
+//     the last marked segment.  At launch dE/d(yaw, pitch) comes from the
+//     dual-number transmit pattern; at a reflection off material m, E' = R E
+//     gives dE'/dtheta = R dE/dtheta + [theta of m] (dR/d eta) E (d eta/d theta),
+//     with dR/d eta from d r_perp / d eta and d r_par / d eta as above.  As
+//     d eta/d sigma = -j/(eps0 w) is a constant, so is the ratio of a
+//     material's two tangents: only dE/d eps_r is carried.  Every mark adds
 //     w = wscale |F_rx . E|^2 / |d_z| and dw = wscale 2 Re(conj(a) F_rx . dE) / |d_z|.
+// Most rays never cross the region, and the second pass is fp64 arithmetic
+// with antenna functions, so a wave collects marked rays in LDS and replays
+// 64 at a time, those without a reflection apart from the others.  After a
+// reflection a field is its two components on the segment's transverse basis.
+// Tangents are a template parameter: with ten for every scene the kernel took
+// 220 registers.  Bound by fp64 arithmetic; 10^7 rays of depth 3 over the
+// street canyon's 770 triangles: 1380 -> 411 us, of which the walk is 232.
 __device__ __forceinline__ cd dot3(const cd* v, d3 u) {
     return cd{v[0].re * u.x + v[1].re * u.y + v[2].re * u.z, v[0].im * u.x + v[1].im * u.y + v[2].im * u.z};
 }
 
-__global__ __launch_bounds__(256) void coverage_grad_kernel(CovGradArgs g, MatTable mats) {
-    __shared__ double red[4][1 + kCovT];
-    double acc[1 + kCovT];
-#pragma unroll
-    for (int i = 0; i <= kCovT; ++i) acc[i] = 0.0;
-    const int yaw_t = 2 * kCovMaxMat, pitch_t = 2 * kCovMaxMat + 1;
-    // transmit pattern tangents are those of dantenna's slots 3 (yaw) and 4 (pitch)
-    D yaw = dc(g.yaw), pitch = dc(g.pitch);
-    yaw.d[3] = 1.0;
-    pitch.d[4] = 1.0;
-    const DRot Rt = drot(yaw, pitch, dc(g.roll));
-    const double dsig = 1.0 / (kEps0 * g.omega);
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < g.count;
-         j += (int64_t)gridDim.x * blockDim.x) {
-        d3 d = fib_dir(g.begin + j * g.stride, g.num_rays);
-        d3 o{g.tx[0], g.tx[1], g.tx[2]};
-        const D3 F0 = dantenna(Rt, g.tx_pattern, dconst(d), g.tx_pol);
-        cd E[3] = {cd{F0.x.v, 0.0}, cd{F0.y.v, 0.0}, cd{F0.z.v, 0.0}};
-        cd dE[kCovT][3];
-#pragma unroll
-        for (int i = 0; i < kCovT; ++i) dE[i][0] = dE[i][1] = dE[i][2] = cd{0.0, 0.0};
-        dE[yaw_t][0] = cd{F0.x.d[3], 0.0};
-        dE[yaw_t][1] = cd{F0.y.d[3], 0.0};
-        dE[yaw_t][2] = cd{F0.z.d[3], 0.0};
-        dE[pitch_t][0] = cd{F0.x.d[4], 0.0};
-        dE[pitch_t][1] = cd{F0.y.d[4], 0.0};
-        dE[pitch_t][2] = cd{F0.z.d[4], 0.0};
-        for (int k = 0; k <= g.max_depth; ++k) {
-            const int32_t tri = g.hit_tri[(int64_t)k * g.count + j];
-            if (tri == -2) break;
-            const double t = g.hit_t[(int64_t)k * g.count + j];
-            const double dz = d.z;
-            if (fabs(dz) >= 1e-12) {
-                const double tc = (g.gz - o.z) / dz;
-                if (tc > 0.0 && tc < t) {
-                    const double x = o.x + tc * d.x, y = o.y + tc * d.y;
-                    const double fx = floor((x - g.gx0) / g.gcell), fy = floor((y - g.gy0) / g.gcell);
-                    if (fx >= 0.0 && fx < (double)g.gnx && fy >= 0.0 && fy < (double)g.gny) {
-                        const int64_t cell = (int64_t)fy * g.gnx + (int64_t)fx;
-                        if (!g.region || g.region[cell]) {
-                            const d3 fr = antenna_field(g.rx_ant, d3{-d.x, -d.y, -d.z});
-                            const cd a = dot3(E, fr);
-                            const double w0 = g.wscale / fabs(dz);
-                            acc[0] += w0 * (a.re * a.re + a.im * a.im);
-#pragma unroll
-                            for (int i = 0; i < kCovT; ++i) {
-                                const cd da = dot3(dE[i], fr);
-                                acc[1 + i] += 2.0 * w0 * (a.re * da.re + a.im * da.im);
-                            }
-                        }
-                    }
-                }
-            }
-            if (tri < 0 || k == g.max_depth || tri >= g.sc.nt) break;
-            const Shade sh = g.sc.shades[g.sc.leaf_of_input[tri]];
-            d3 n{sh.n[0], sh.n[1], sh.n[2]};
-            if (dot(d, n) > 0.0) n = scale(n, -1.0);
-            const double cos_i = -dot(d, n);
-            const d3 dr = add(d, scale(n, 2.0 * cos_i));
-            const d3 p = add(o, scale(d, t));
-            const d3 ep = perp_basis(d, n);
-            const d3 eli = cross(ep, d);
-            // the outgoing direction and transverse basis: specular, or diffuse
-            // with the forward kernel's draws (they depend on no parameter)
-            d3 dout = dr, epo = ep, elr = cross(ep, dr);
-            if (mats.m[sh.mat].scat > 0.0f) {
-                const uint64_t ri = (uint64_t)(g.begin + j * g.stride);
-                const uint64_t c0 = (ri * (uint64_t)(g.max_depth + 1) + (uint64_t)k) * 3ull;
-                const double S = (double)mats.m[sh.mat].scat;
-                if (uniform01(g.scat_seed, c0) < S * S) {
-                    dout = lambert_dir(n, uniform01(g.scat_seed, c0 + 1), uniform01(g.scat_seed, c0 + 2));
-                    epo = perp_basis(dout, n);
-                    elr = cross(epo, dout);
-                }
-            }
-            const Mat mt = mats.m[sh.mat];
-            cd rp, rl;
-            fresnel(mt, cos_i, rp, rl);
-            cd drp{0.0, 0.0}, drl{0.0, 0.0};
-            if (!mt.pec) {
-                const cd eta{mt.eta_re_d, mt.eta_im_d};
-                const double sin2 = 1.0 - cos_i * cos_i;
-                const cd s = csqrt(cd{eta.re - sin2, eta.im});
-                const cd cps = cadd(cd{cos_i, 0.0}, s), ecs = cadd(cmulr(eta, cos_i), s);
-                drp = cdiv(cd{-cos_i, 0.0}, cmul(s, cmul(cps, cps)));
-                drl = cdiv(cmulr(csub(eta, cd{2.0 * sin2, 0.0}), cos_i), cmul(s, cmul(ecs, ecs)));
-            }
-            const cd ap = dot3(E, ep), al = dot3(E, eli);
-            const cd sp = cmul(rp, ap), sl = cmul(rl, al);
-            const cd dsp = cmul(drp, ap), dsl = cmul(drl, al);  // d(r a)/d eta
-#pragma unroll
-            for (int i = 0; i < kCovT; ++i) {
-                const cd api = cmul(rp, dot3(dE[i], ep)), ali = cmul(rl, dot3(dE[i], eli));
-                dE[i][0] = cadd(cmulr(api, epo.x), cmulr(ali, elr.x));
-                dE[i][1] = cadd(cmulr(api, epo.y), cmulr(ali, elr.y));
-                dE[i][2] = cadd(cmulr(api, epo.z), cmulr(ali, elr.z));
-            }
-            if (sh.mat < kCovMaxMat && !mt.pec) {
-                const cd de[3] = {cadd(cmulr(dsp, epo.x), cmulr(dsl, elr.x)), cadd(cmulr(dsp, epo.y), cmulr(dsl, elr.y)),
-                                  cadd(cmulr(dsp, epo.z), cmulr(dsl, elr.z))};
-                const cd mj{0.0, -dsig};  // d eta / d sigma = -j / (eps0 w)
-#pragma unroll
-                for (int m = 0; m < kCovMaxMat; ++m)
-                    if (m == sh.mat) {
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            dE[2 * m][c] = cadd(dE[2 * m][c], de[c]);
-                            dE[2 * m + 1][c] = cadd(dE[2 * m + 1][c], cmul(de[c], mj));
-                        }
-                    }
-            }
-            E[0] = cadd(cmulr(sp, epo.x), cmulr(sl, elr.x));
-            E[1] = cadd(cmulr(sp, epo.y), cmulr(sl, elr.y));
-            E[2] = cadd(cmulr(sp, epo.z), cmulr(sl, elr.z));
-            o = p;
-            d = dout;
+constexpr int kCovWaves = 3;  // per SIMD: 168 registers; the grid is three blocks per CU
+
+struct CovHit {
+    d3 n;              // normal facing the ray
+    double cos_i;
+    d3 p, dout;        // reflection point, outgoing direction
+    int32_t mat;
+    bool diffuse;
+};
+
+// The reflection of recorded ray j at depth k: the specular direction, or the
+// forward kernel's diffuse draw (it depends on no parameter).
+__device__ __forceinline__ CovHit cov_reflect(const CovGradArgs& g, const MatTable& mats, int64_t j, int k, int tri,
+                                              double t, d3 o, d3 d) {
+    const Shade sh = g.sc.shades[g.sc.leaf_of_input[tri]];
+    CovHit h;
+    h.n = d3{sh.n[0], sh.n[1], sh.n[2]};
+    if (dot(d, h.n) > 0.0) h.n = scale(h.n, -1.0);
+    h.cos_i = -dot(d, h.n);
+    h.dout = add(d, scale(h.n, 2.0 * h.cos_i));
+    h.p = add(o, scale(d, t));
+    h.mat = sh.mat;
+    h.diffuse = false;
+    if (mats.m[sh.mat].scat > 0.0f) {
+        const uint64_t ri = (uint64_t)(g.begin + j * g.stride);
+        const uint64_t c0 = (ri * (uint64_t)(g.max_depth + 1) + (uint64_t)k) * 3ull;
+        const double S = (double)mats.m[sh.mat].scat;
+        if (uniform01(g.scat_seed, c0) < S * S) {
+            h.dout = lambert_dir(h.n, uniform01(g.scat_seed, c0 + 1), uniform01(g.scat_seed, c0 + 2));
+            h.diffuse = true;
         }
+    }
+    return h;
+}
+
+// Bit k: segment k of recorded ray j crosses the grid plane inside the region.
+__device__ __forceinline__ uint32_t cov_walk(const CovGradArgs& g, const MatTable& mats, int64_t j) {
+    uint32_t marks = 0;
+    int32_t tri = g.hit_tri[j];
+    double t = g.hit_t[j];
+    d3 o{g.tx[0], g.tx[1], g.tx[2]};
+    // A ray that neither hits nor crosses the plane (the sky: whole waves, as the
+    // lattice is ordered by height) ends before its azimuth is computed.
+    const double z = fib_height(g.begin + j * g.stride, g.num_rays);
+    if (tri < 0 || g.max_depth == 0) {
+        const double tc = (g.gz - o.z) / z;
+        if (!(fabs(z) >= 1e-12 && tc > 0.0 && tc < t)) return 0;
+    }
+    d3 d = fib_dir(g.begin + j * g.stride, g.num_rays);
+    for (int k = 0; k <= g.max_depth; ++k) {
+        if (tri == -2) break;
+        int32_t tri_next = -2;
+        double t_next = 0.0;
+        if (k < g.max_depth) {
+            tri_next = g.hit_tri[(int64_t)(k + 1) * g.count + j];
+            t_next = g.hit_t[(int64_t)(k + 1) * g.count + j];
+        }
+        if (fabs(d.z) >= 1e-12) {
+            const double tc = (g.gz - o.z) / d.z;
+            if (tc > 0.0 && tc < t) {
+                const double x = o.x + tc * d.x, y = o.y + tc * d.y;
+                const double fx = floor((x - g.gx0) / g.gcell), fy = floor((y - g.gy0) / g.gcell);
+                if (fx >= 0.0 && fx < (double)g.gnx && fy >= 0.0 && fy < (double)g.gny) {
+                    const int64_t cell = (int64_t)fy * g.gnx + (int64_t)fx;
+                    if (!g.region || g.region[cell]) marks |= 1u << k;
+                }
+            }
+        }
+        if (tri < 0 || k == g.max_depth || tri >= g.sc.nt) break;
+        const CovHit h = cov_reflect(g, mats, j, k, tri, t, o, d);
+        o = h.p;
+        d = h.dout;
+        tri = tri_next;
+        t = t_next;
+    }
+    return marks;
+}
+
+// Sums of one thread: the gain, and its derivatives with respect to eps_r and
+// eps0 w sigma per material, yaw and pitch.
+template <int NM>
+struct CovSums {
+    double w, eps[NM], sig[NM], yaw, pitch;
+};
+
+// Complex field of one tangent on the transverse basis (u, v) of its segment.
+struct Trans {
+    cd u, v;
+};
+
+// Adds a marked segment: the amplitude and its tangents received along fr.
+template <int NM>
+__device__ __forceinline__ void cov_deposit(double w0, cd a, cd y, cd p, const cd* e, CovSums<NM>& acc) {
+    acc.w += w0 * (a.re * a.re + a.im * a.im);
+    const double w2 = 2.0 * w0;
+    acc.yaw += w2 * (a.re * y.re + a.im * y.im);
+    acc.pitch += w2 * (a.re * p.re + a.im * p.im);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        acc.eps[m] += w2 * (a.re * e[m].re + a.im * e[m].im);
+        acc.sig[m] += w2 * (a.re * e[m].im - a.im * e[m].re);  // Re(conj(a) (-j) e)
+    }
+}
+
+template <int NM>
+__device__ __forceinline__ void cov_replay(const CovGradArgs& g, const MatTable& mats, int64_t j, uint32_t marks,
+                                           CovSums<NM>& acc) {
+    d3 d = fib_dir(g.begin + j * g.stride, g.num_rays);
+    d3 o{g.tx[0], g.tx[1], g.tx[2]};
+    // field and tangents of the segment: real vectors F from the transmitter,
+    // then (after a reflection) transverse components on (u, v)
+    d3 F, FY, FP, u, v;
+    Trans E, Y, P, M[NM];
+    {
+        Dual<2> R[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) R[i] = Dual<2>{g.R[i], {g.Ryaw[i], g.Rpitch[i]}};
+        const Dual3<2> f = dantenna_local(R, g.tx_pattern, R[0] * d.x + R[3] * d.y + R[6] * d.z,
+                                          R[1] * d.x + R[4] * d.y + R[7] * d.z, R[2] * d.x + R[5] * d.y + R[8] * d.z,
+                                          g.tx_pol);
+        F = d3{f.x.v, f.y.v, f.z.v};
+        FY = d3{f.x.d[0], f.y.d[0], f.z.d[0]};
+        FP = d3{f.x.d[1], f.y.d[1], f.z.d[1]};
+    }
+    for (int k = 0;; ++k) {
+        if ((marks >> k) & 1u) {
+            const d3 fr = antenna_field(g.rx_ant, d3{-d.x, -d.y, -d.z});
+            const double w0 = g.wscale / fabs(d.z);
+            if (k == 0) {
+                const double a = dot(F, fr);
+                acc.w += w0 * a * a;
+                acc.yaw += 2.0 * w0 * a * dot(FY, fr);
+                acc.pitch += 2.0 * w0 * a * dot(FP, fr);
+            } else {
+                const double fu = dot(u, fr), fv = dot(v, fr);
+                auto at = [&](const Trans& x) { return cadd(cmulr(x.u, fu), cmulr(x.v, fv)); };
+                cd e[NM];
+#pragma unroll
+                for (int m = 0; m < NM; ++m) e[m] = at(M[m]);
+                cov_deposit<NM>(w0, at(E), at(Y), at(P), e, acc);
+            }
+        }
+        if (!(marks >> (k + 1))) return;
+        const int64_t at = (int64_t)k * g.count + j;
+        const CovHit h = cov_reflect(g, mats, j, k, g.hit_tri[at], g.hit_t[at], o, d);
+        const d3 ep = perp_basis(d, h.n), eli = cross(ep, d);
+        const d3 epo = h.diffuse ? perp_basis(h.dout, h.n) : ep;
+        const Mat& mt = mats.m[h.mat];
+        const double cos_i = h.cos_i;
+        cd rp{-1.0, 0.0}, rl{1.0, 0.0}, drp{0.0, 0.0}, drl{0.0, 0.0};
+        if (!mt.pec) {
+            const cd eta{mt.eta_re_d, mt.eta_im_d}, c{cos_i, 0.0};
+            const double sin2 = 1.0 - cos_i * cos_i;
+            const cd s = csqrt(cd{eta.re - sin2, eta.im});
+            const cd ec = cmulr(eta, cos_i);
+            const cd ip = cdiv(cd{1.0, 0.0}, cadd(c, s)), il = cdiv(cd{1.0, 0.0}, cadd(ec, s));
+            const cd is = cdiv(cd{cos_i, 0.0}, s);
+            rp = cmul(csub(c, s), ip);
+            rl = cmul(csub(ec, s), il);
+            drp = cmul(cd{-is.re, -is.im}, cmul(ip, ip));
+            drl = cmul(cmul(csub(eta, cd{2.0 * sin2, 0.0}), is), cmul(il, il));
+        }
+        if (k == 0) {
+            const double fu = dot(F, ep), fv = dot(F, eli);
+            E = Trans{cmulr(rp, fu), cmulr(rl, fv)};
+            Y = Trans{cmulr(rp, dot(FY, ep)), cmulr(rl, dot(FY, eli))};
+            P = Trans{cmulr(rp, dot(FP, ep)), cmulr(rl, dot(FP, eli))};
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+                M[m] = m == h.mat ? Trans{cmulr(drp, fu), cmulr(drl, fv)} : Trans{cd{0.0, 0.0}, cd{0.0, 0.0}};
+        } else {
+            const double uu = dot(u, ep), vu = dot(v, ep), uv = dot(u, eli), vv = dot(v, eli);
+            auto turn = [&](const Trans& x) {  // components on (ep, eli)
+                return Trans{cadd(cmulr(x.u, uu), cmulr(x.v, vu)), cadd(cmulr(x.u, uv), cmulr(x.v, vv))};
+            };
+            auto through = [&](const Trans& x) { return Trans{cmul(rp, x.u), cmul(rl, x.v)}; };
+            const Trans e = turn(E);
+            E = through(e);
+            Y = through(turn(Y));
+            P = through(turn(P));
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                M[m] = through(turn(M[m]));
+                if (m == h.mat) M[m] = Trans{cadd(M[m].u, cmul(drp, e.u)), cadd(M[m].v, cmul(drl, e.v))};
+            }
+        }
+        u = epo;
+        v = cross(epo, h.dout);
+        o = h.p;
+        d = h.dout;
+    }
+}
+
+template <int NM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kCovWaves, kCovWaves)))
+void coverage_grad_kernel(CovGradArgs g, MatTable mats) {
+    constexpr int kOut = 2 * NM + 3;  // the region sum, (eps_r, sigma) per material, yaw, pitch
+    __shared__ uint2 queue[4][2][128];  // marked rays (index, marks) of each wave: last mark on segment 0, or later
+    __shared__ double red[4][kOut];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    CovSums<NM> acc{};
+    int n0 = 0, n1 = 0;
+    for (int64_t base = ((int64_t)blockIdx.x * 4 + wave) * 64;; base += (int64_t)gridDim.x * 256) {
+        const bool more = base < g.count;
+        if (more) {
+            const int64_t j = base + lane;
+            const uint32_t marks = j < g.count ? cov_walk(g, mats, j) : 0u;
+            const uint64_t below = (1ull << lane) - 1ull;
+            const uint64_t b0 = __ballot(marks == 1u), b1 = __ballot(marks > 1u);
+            if (marks == 1u) queue[wave][0][n0 + __popcll(b0 & below)] = uint2{(uint32_t)j, marks};
+            if (marks > 1u) queue[wave][1][n1 + __popcll(b1 & below)] = uint2{(uint32_t)j, marks};
+            n0 += __popcll(b0);
+            n1 += __popcll(b1);
+        }
+        // full batches of one kind while there are rays to walk, then what is left
+        while (n0 >= 64 || n1 >= 64 || (!more && n0 + n1 > 0)) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            uint2 e{0u, 0u};
+            if (n1 >= 64) {
+                n1 -= 64;
+                e = queue[wave][1][n1 + lane];
+            } else if (n0 >= 64) {
+                n0 -= 64;
+                e = queue[wave][0][n0 + lane];
+            } else {
+                const int from1 = n1, from0 = min(n0, 64 - n1);
+                if (lane < from1) e = queue[wave][1][lane];
+                else if (lane < from1 + from0) e = queue[wave][0][n0 - 1 - (lane - from1)];
+                n1 = 0;
+                n0 -= from0;
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (e.y) cov_replay<NM>(g, mats, (int64_t)e.x, e.y, acc);
+        }
+        if (!more) break;
     }
     // block reduction (wave shuffles, then the four waves through LDS), one
     // fp64 atomic per block and output
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[kOut];
+    const double dsig = 1.0 / (kEps0 * g.omega);
+    v[0] = acc.w;
 #pragma unroll
-    for (int i = 0; i <= kCovT; ++i) {
-        double v = acc[i];
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) red[wave][i] = v;
+    for (int m = 0; m < NM; ++m) {
+        v[1 + 2 * m] = acc.eps[m];
+        v[2 + 2 * m] = acc.sig[m] * dsig;
+    }
+    v[kOut - 2] = acc.yaw;
+    v[kOut - 1] = acc.pitch;
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+        for (int off = 32; off >= 1; off >>= 1) v[i] += __shfl_xor(v[i], off);
+        if (lane == 0) red[wave][i] = v[i];
     }
     __syncthreads();
-    if (threadIdx.x <= kCovT) {
-        // slot 0 the region sum, 1 + 2m + {0, 1} material m, then yaw, pitch;
-        // out has 2 nm + 3 entries in the same order
+    if (threadIdx.x < kOut) {
         const int i = threadIdx.x;
-        int o = -1;
-        if (i == 0) o = 0;
-        else if (i - 1 < 2 * g.nm) o = i;
-        else if (i - 1 == yaw_t) o = 1 + 2 * g.nm;
-        else if (i - 1 == pitch_t) o = 2 + 2 * g.nm;
-        const double v = red[0][i] + red[1][i] + red[2][i] + red[3][i];
-        if (o >= 0 && v != 0.0) atomicAdd(g.out + o, v);
+        const double s = red[0][i] + red[1][i] + red[2][i] + red[3][i];
+        if (s != 0.0) atomicAdd(g.out + i, s);
     }
 }
 
@@ -535,11 +690,18 @@ hipError_t launch_power_grad(const GradArgs& a, const MatTable& mats, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int grid, hipStream_t s) {
+hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, hipStream_t s) {
     if (a.count <= 0) return hipSuccess;
     const int64_t need = (a.count + 255) / 256;
-    const unsigned blocks = (unsigned)(need < grid ? need : grid);
-    hipLaunchKernelGGL(coverage_grad_kernel, dim3(blocks), dim3(256), 0, s, a, mats);
+    const int64_t grid = (int64_t)num_cu * kCovWaves;
+    const dim3 blocks((unsigned)(need < grid ? need : grid)), threads(256);
+    switch (a.nm) {
+        case 1: hipLaunchKernelGGL(coverage_grad_kernel<1>, blocks, threads, 0, s, a, mats); break;
+        case 2: hipLaunchKernelGGL(coverage_grad_kernel<2>, blocks, threads, 0, s, a, mats); break;
+        case 3: hipLaunchKernelGGL(coverage_grad_kernel<3>, blocks, threads, 0, s, a, mats); break;
+        case 4: hipLaunchKernelGGL(coverage_grad_kernel<4>, blocks, threads, 0, s, a, mats); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

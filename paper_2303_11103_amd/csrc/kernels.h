@@ -267,14 +267,13 @@ hipError_t launch_cfr_adjoint(const CfrArgs& c, const float* G, double* g, void*
 
 // Coverage-map gradient: replay of recorded rays with field tangents.
 constexpr int kCovMaxMat = 4;                 // materials with tangents
-constexpr int kCovT = 2 * kCovMaxMat + 2;     // (eps_r, sigma) per material, yaw, pitch
 struct CovGradArgs {
     DevScene sc;
     int64_t num_rays, begin, stride, count;
     int32_t max_depth;
     int32_t nm;
     double tx[3];
-    double yaw, pitch, roll;
+    double R[9], Ryaw[9], Rpitch[9];  // tx orientation and its derivatives
     int32_t tx_pattern, tx_pol;
     int32_t gnx, gny;
     Antenna rx_ant;
@@ -287,6 +286,6 @@ struct CovGradArgs {
     const double* hit_t;      // [max_depth+1][count]
     double* out;              // [2 nm + 3]: region sum, d/d(eps_r, sigma) per material, d/d yaw, d/d pitch
 };
-hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int grid, hipStream_t s);
+hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, hipStream_t s);
 
 }  // namespace rt
