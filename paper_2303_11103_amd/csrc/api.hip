@@ -324,27 +324,39 @@ void band_perm(int64_t count, int64_t stride, int64_t& F, int64_t& G) {
 }
 
 int grid_for(const rt_ctx* c) { return c->num_cu * 4; }
+// Blocks that give every lane of a shoot-and-bounce launch one ray of the chunk.
+int blocks_needed(int64_t chunk) {
+    return (int)std::min<int64_t>(1 << 30, (chunk + rt::kTraceBlock - 1) / rt::kTraceBlock);
+}
 // Blocks of the shoot-and-bounce launch of depth k when the queues are
 // allocated per call (measured on the large city: more, smaller blocks for the
-// coherent first bounce, fewer for the second), and the region capacity that
-// covers every such grid.  The fixed-scratch path keeps grid_for for all
-// depths: a larger grid's minimum region capacity would not fit its scratch.
-int grid_for_depth(const rt_ctx* c, int k) { return c->num_cu * (k == 0 ? 8 : k == 1 ? 2 : 4); }
+// coherent first bounce, fewer for the second; small calls no more than their
+// rays fill), and the region capacity that covers every such grid.  The
+// fixed-scratch path keeps grid_for for all depths: a larger grid's minimum
+// region capacity would not fit its scratch.
+int grid_for_depth(const rt_ctx* c, int k, int64_t chunk) {
+    return std::min(c->num_cu * (k == 0 ? 8 : k == 1 ? 2 : 4), blocks_needed(chunk));
+}
 int64_t region_capacity_by_depth(const rt_ctx* c, int64_t chunk) {
     int64_t cap = 0;
-    for (int k = 0; k < 3; ++k) cap = std::max(cap, rt::sbr_region_capacity(chunk, grid_for_depth(c, k)));
+    for (int k = 0; k < 3; ++k) cap = std::max(cap, rt::sbr_region_capacity(chunk, grid_for_depth(c, k, chunk)));
     return cap;
 }
 
-// Runs the shoot-and-bounce launches for all rays of one transmitter.
+// Runs the shoot-and-bounce launches for all rays of one transmitter.  `clear`
+// names up to three arrays to zero first (with the queue counters, in the same
+// launch).
 rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_device* tx, const rt_device* rx_ant,
                   const rt_grid* g, int mode, float* gain, uint32_t* hits, uint64_t* stats, int32_t* rec_tri,
                   double* rec_t, uint64_t* table, uint64_t table_mask, uint32_t* overflow,
-                  uint64_t* work = nullptr, const rt::SbrArgs* sphere = nullptr, const FixedQueues* fixed = nullptr) {
+                  uint64_t* work = nullptr, const rt::SbrArgs* sphere = nullptr, const FixedQueues* fixed = nullptr,
+                  const rt::ClearArgs* clear = nullptr) {
     const int64_t count = traced_count(p);
     const int64_t chunk = std::min(count, fixed ? fixed->max_chunk : kChunk);
     const int64_t region_cap =
         fixed ? rt::sbr_region_capacity(chunk, grid_for(c)) : region_capacity_by_depth(c, chunk);
+    // one iteration of fewer waves never needs a larger region
+    const int fixed_grid = std::min(grid_for(c), blocks_needed(chunk));
     rt::RayState* queue[2];
     uint32_t* cnt;
     if (fixed) {
@@ -417,8 +429,10 @@ rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_dev
         a.pos0 = pos0;
         a.chunk = std::min(chunk, count - pos0);
         const size_t nwords = (size_t)(p->max_depth + 1) * rt::kQueueRegions * rt::kCounterStride;
-        if (fixed) RT_HIP(rt::launch_fill_u32(cnt, 0u, nwords, c->stream));
-        else RT_HIP(hipMemsetAsync(cnt, 0, nwords * sizeof(uint32_t), c->stream));
+        rt::ClearArgs cl = clear && pos0 == 0 ? *clear : rt::ClearArgs{};
+        cl.p[3] = cnt;
+        cl.words[3] = (int64_t)nwords;
+        RT_HIP(rt::launch_clear(cl, c->stream));
         for (int k = 0; k <= p->max_depth; ++k) {
             a.depth = k;
             a.in = k ? queue[(k - 1) & 1] : nullptr;
@@ -437,7 +451,7 @@ rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_dev
                 e1 = c->ev_pool[c->ev_used++];
                 RT_HIP(hipEventRecord(e0, c->stream));
             }
-            RT_HIP(rt::launch_sbr_bounce(a, mats, mode, fixed ? grid_for(c) : grid_for_depth(c, k), c->stream));
+            RT_HIP(rt::launch_sbr_bounce(a, mats, mode, fixed ? fixed_grid : grid_for_depth(c, k, chunk), c->stream));
             if (profiling) {
                 RT_HIP(hipEventRecord(e1, c->stream));
                 c->recs.push_back({k, e0, e1});
@@ -652,19 +666,13 @@ rt_status coverage_impl(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const 
         return fail(RT_ERR_ARG, "grid origin, cell size and height must be finite, cell > 0");
     RT_HIP(hipSetDevice(c->device));
     const int64_t cells = (int64_t)g->nx * g->ny;
-    if (fixed) {  // fill kernels: callers of the fixed-memory path may capture it in a graph
-        RT_HIP(rt::launch_fill_u32(gain, 0u, (size_t)cells, c->stream));
-        RT_HIP(rt::launch_fill_u32(hits, 0u, (size_t)cells, c->stream));
-        if (ray_bounces) RT_HIP(rt::launch_fill_u32(ray_bounces, 0u, (size_t)(p->max_depth + 1) * 2, c->stream));
-    } else {
-        RT_HIP(hipMemsetAsync(gain, 0, (size_t)cells * sizeof(float), c->stream));
-        RT_HIP(hipMemsetAsync(hits, 0, (size_t)cells * sizeof(uint32_t), c->stream));
-        if (ray_bounces)
-            RT_HIP(hipMemsetAsync(ray_bounces, 0, (size_t)(p->max_depth + 1) * sizeof(uint64_t), c->stream));
-        if (work) RT_HIP(hipMemsetAsync(work, 0, (size_t)4 * (p->max_depth + 1) * sizeof(uint64_t), c->stream));
-    }
+    // one kernel clears the outputs together with the queue counters (a kernel
+    // also because callers of the fixed-memory path may capture it in a graph)
+    rt::ClearArgs clear{{gain, hits, ray_bounces, nullptr},
+                        {cells, cells, ray_bounces ? 2 * ((int64_t)p->max_depth + 1) : 0, 0}};
+    if (work) RT_HIP(rt::launch_fill_u32(work, 0u, (size_t)8 * (p->max_depth + 1), c->stream));
     st = run_sbr(c, s, p, tx, rx_ant, g, work ? (rt::kModeCoverage | rt::kModeStats) : rt::kModeCoverage, gain, hits,
-                 ray_bounces, nullptr, nullptr, nullptr, 0, nullptr, work, nullptr, fixed);
+                 ray_bounces, nullptr, nullptr, nullptr, 0, nullptr, work, nullptr, fixed, &clear);
     if (st != RT_OK) return st;
     if (gain_db) RT_HIP(rt::launch_finalize_db(gain, gain_db, cells, c->stream));
     return RT_OK;
@@ -893,8 +901,7 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     for (int t = 0; t < ntx; ++t) {
         RT_HIP(hipMemsetAsync(c->table.p, 0xff, cap * sizeof(uint64_t), c->stream));
         if (sphere) RT_HIP(hipMemsetAsync(c->pairs.p, 0xff, pcap * sizeof(uint64_t), c->stream));
-        RT_HIP(hipMemsetAsync(ncand, 0, 3 * sizeof(uint32_t), c->stream));
-        RT_HIP(hipMemsetAsync(pa.counts, 0, (size_t)nrx * sizeof(uint32_t), c->stream));
+        RT_HIP(rt::launch_fill_u32(pa.counts, 0u, (size_t)nrx + 3, c->stream));  // counts, then ncand
         if (sphere) {
             st = run_sbr(c, s, p, tx + t, nullptr, nullptr, rt::kModeSphere, nullptr, nullptr, nullptr, nullptr,
                          nullptr, (uint64_t*)c->table.p, cap - 1, ncand + 1, nullptr, &sph);

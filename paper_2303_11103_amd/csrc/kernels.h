@@ -21,6 +21,7 @@ struct alignas(16) RayState {
 };
 static_assert(sizeof(RayState) == 96, "ray state size");
 
+constexpr int kTraceBlock = 512;  // block size of the shoot-and-bounce kernels
 constexpr uint64_t kEmptyKey = ~0ull;
 constexpr int kQueueRegions = 64;
 // The region counters sit 64 bytes apart: every wave's append is a
@@ -111,6 +112,12 @@ int64_t sbr_region_capacity(int64_t chunk, int grid);
 hipError_t launch_sbr_bounce(const SbrArgs& a, const MatTable& mats, int mode, int grid, hipStream_t s);
 hipError_t launch_fib_dirs(int64_t N, int64_t begin, int64_t stride, int64_t count, double* out, hipStream_t s);
 hipError_t launch_finalize_db(const float* gain, float* db, int64_t n, hipStream_t s);
+// Zeroes p[k][0 .. words[k]) (32-bit words) of all arrays in one launch.
+struct ClearArgs {
+    void* p[4];
+    int64_t words[4];
+};
+hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 // p[0 .. n) = v (32-bit words), as a kernel (usable inside captured graphs).
 hipError_t launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);
 

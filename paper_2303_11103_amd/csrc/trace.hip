@@ -267,7 +267,6 @@ __global__ __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(RT_
 void sbr_bounce(SbrArgs a, MatTable mats) {
     __shared__ int32_t stack[kStack][kTraceBlock];
     __shared__ Node lds_nodes[kLdsNodes];
-    const int n_lds = stage_nodes(a.sc, lds_nodes);
     const int lane = threadIdx.x & 63;
     const int64_t wave = ((int64_t)blockIdx.x * kTraceBlock + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * kTraceBlock) >> 6;
@@ -288,6 +287,10 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
         for (int off = 32; off >= 1; off >>= 1) dropped += __shfl_xor(dropped, off);
         if (threadIdx.x == 0) atomicAdd((unsigned long long*)&a.stats[a.depth], (unsigned long long)(count + dropped));
     }
+    // blocks without a ray (the host sizes the grid for the first bounce's rays)
+    // end before they stage nodes
+    if ((int64_t)blockIdx.x * kTraceBlock >= count) return;
+    const int n_lds = stage_nodes(a.sc, lds_nodes);
     uint32_t wave_dropped = 0;  // rays of this wave dropped before the last bounce
     for (int64_t base = wave * 64; base < count; base += nwaves * 64) {
         const int64_t item = base + lane;
@@ -495,6 +498,19 @@ __global__ void fib_dirs_kernel(int64_t N, int64_t begin, int64_t stride, int64_
     out[3 * j + 2] = d.z;
 }
 
+// Zeroes up to four arrays of 32-bit words with 16-byte stores where an array
+// is aligned for them.
+__global__ __launch_bounds__(256) void clear_kernel(ClearArgs a) {
+    const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x, n = (int64_t)gridDim.x * 256;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t* p = (uint32_t*)a.p[k];
+        const int64_t words = a.words[k], vec = ((uintptr_t)p & 15) == 0 ? words / 4 : 0;
+        for (int64_t i = tid; i < vec; i += n) reinterpret_cast<uint4*>(p)[i] = uint4{0u, 0u, 0u, 0u};
+        for (int64_t i = 4 * vec + tid; i < words; i += n) p[i] = 0u;
+    }
+}
+
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t v, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -552,6 +568,15 @@ hipError_t launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t blocks = ((int64_t)n + 255) / 256;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)p, v, (int64_t)n);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(const ClearArgs& a, hipStream_t s) {
+    int64_t words = 0;
+    for (int k = 0; k < 4; ++k) words += a.words[k];
+    if (words == 0) return hipSuccess;
+    const int64_t blocks = (words + 1023) / 1024;
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

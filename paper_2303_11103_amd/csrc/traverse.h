@@ -8,7 +8,6 @@
 namespace rt {
 
 constexpr int kBlock = 256;       // block size of kernels that do not stage nodes
-constexpr int kTraceBlock = 512;  // block size of the shoot-and-bounce kernels
 constexpr int kStack = kStackEntries;
 constexpr int kLdsNodes = 128;    // top BVH nodes (breadth-first order) staged in LDS, 16 KB
 // Conservative slab interval: a box is entered when near <= far (1 + 3e-6).
