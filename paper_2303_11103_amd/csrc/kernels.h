@@ -63,6 +63,7 @@ struct SbrArgs {
     float wscale;       // (lambda/4pi)^2 (4pi/N) / cell^2
     float* gain;
     uint32_t* hits;
+    int32_t merge;      // the first two bounces merge a wave's deposits per cell
     // queues
     int32_t depth, max_depth;
     // The queues are split into kQueueRegions regions of region_cap rays; a
