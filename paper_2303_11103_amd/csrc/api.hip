@@ -113,7 +113,7 @@ rt_status scratch_address(int device, void** out) {
 
 // Fixed queue memory handed to run_sbr instead of the context's buffers.
 struct FixedQueues {
-    rt::RayState* q[2];
+    void* q[2];
     uint32_t* counters;
     int64_t max_chunk;
 };
@@ -374,19 +374,19 @@ rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_dev
         fixed ? rt::sbr_region_capacity(chunk, grid_for(c)) : region_capacity_by_depth(c, chunk);
     // one iteration of fewer waves never needs a larger region
     const int fixed_grid = std::min(grid_for(c), blocks_needed(chunk));
-    rt::RayState* queue[2];
+    void* queue[2];
     uint32_t* cnt;
     if (fixed) {
         queue[0] = fixed->q[0];
         queue[1] = fixed->q[1];
         cnt = fixed->counters;
     } else {
-        const size_t qbytes = (size_t)rt::kQueueRegions * region_cap * sizeof(rt::RayState);
+        const size_t qbytes = (size_t)rt::kQueueRegions * region_cap * rt::sbr_ray_bytes(mode, p->max_depth);
         RT_HIP(ensure(c->queue[0], qbytes));
         RT_HIP(ensure(c->queue[1], qbytes));
         RT_HIP(ensure(c->counters, (size_t)(p->max_depth + 1) * rt::kQueueRegions * rt::kCounterStride * sizeof(uint32_t)));
-        queue[0] = (rt::RayState*)c->queue[0].p;
-        queue[1] = (rt::RayState*)c->queue[1].p;
+        queue[0] = c->queue[0].p;
+        queue[1] = c->queue[1].p;
         cnt = (uint32_t*)c->counters.p;
     }
     rt::MatTable mats = make_mats(s, p->freq_hz);
@@ -713,16 +713,16 @@ rt_status rt_coverage_map_noalloc(rt_ctx* c, rt_scene* s, const rt_trace_params*
     int64_t chunk = kNoAllocMaxChunk;
     const size_t qmax = (kNoAllocScratchBytes - kNoAllocCounterBytes) / 2;
     while (chunk > 64 && (size_t)rt::kQueueRegions * rt::sbr_region_capacity(chunk, grid_for(c)) *
-                                 sizeof(rt::RayState) > qmax)
+                                 rt::sbr_ray_bytes(rt::kModeCoverage, 0) > qmax)
         chunk >>= 1;
     const size_t qbytes = (size_t)rt::kQueueRegions * rt::sbr_region_capacity(chunk, grid_for(c)) *
-                          sizeof(rt::RayState);
+                          rt::sbr_ray_bytes(rt::kModeCoverage, 0);
     if (qbytes > qmax) return fail(RT_ERR_CAPACITY, "the ray queues of this device do not fit the fixed scratch");
     unsigned char* base = (unsigned char*)c->scratch;
     FixedQueues fq;
     fq.counters = (uint32_t*)base;
-    fq.q[0] = (rt::RayState*)(base + kNoAllocCounterBytes);
-    fq.q[1] = (rt::RayState*)(base + kNoAllocCounterBytes + qmax);
+    fq.q[0] = base + kNoAllocCounterBytes;
+    fq.q[1] = base + kNoAllocCounterBytes + qmax;
     fq.max_chunk = chunk;
     return coverage_impl(c, s, p, tx, rx_ant, g, gain, hits, gain_db, ray_bounces, nullptr, &fq);
 }

@@ -73,9 +73,10 @@ __device__ int32_t cand_insert(uint64_t* table, uint64_t mask, int32_t parent, i
     return -2;
 }
 
-// Ray state in registers; loaded from / stored to the 96-byte queue record
-// with 16-byte vector accesses.  In reception-sphere mode (SPH) the prefix
-// word holds the path length so far and the last 16 bytes the face sequence.
+// Ray state in registers; loaded from / stored to its queue record with
+// 16-byte vector accesses.  Only maps carry a field (the image method computes
+// a path's own, a record has none), so only their records hold E; in
+// reception-sphere mode (SPH) a ray carries its path length and face sequence.
 struct Ray {
     d3 o, d;
     float E[6];
@@ -83,52 +84,6 @@ struct Ray {
     float s;          // SPH: path length before the current segment [m]
     uint32_t seq[4];  // SPH: faces of the reflections so far, 24 bits each
 };
-
-template <bool SPH>
-__device__ __forceinline__ void load_ray(const RayState* __restrict__ p, Ray& r) {
-    const double2* q = reinterpret_cast<const double2*>(p);
-    const double2 a0 = q[0], a1 = q[1], a2 = q[2];
-    const float4 f0 = reinterpret_cast<const float4*>(p)[3];
-    const int4 f1 = reinterpret_cast<const int4*>(p)[4];
-    const int4 f2 = reinterpret_cast<const int4*>(p)[5];
-    r.o = d3{a0.x, a0.y, a1.x};
-    r.d = d3{a1.y, a2.x, a2.y};
-    r.E[0] = f0.x;
-    r.E[1] = f0.y;
-    r.E[2] = f0.z;
-    r.E[3] = f0.w;
-    r.E[4] = __int_as_float(f1.x);
-    r.E[5] = __int_as_float(f1.y);
-    r.excl = f1.z;
-    if (SPH) {
-        r.prefix = -1;
-        r.s = __int_as_float(f1.w);
-        r.ray = -1;
-        r.seq[0] = (uint32_t)f2.x;
-        r.seq[1] = (uint32_t)f2.y;
-        r.seq[2] = (uint32_t)f2.z;
-        r.seq[3] = (uint32_t)f2.w;
-    } else {
-        r.prefix = f1.w;
-        r.ray = f2.x;
-    }
-}
-
-template <bool SPH>
-__device__ __forceinline__ void store_ray(RayState* __restrict__ p, const Ray& r) {
-    double2* q = reinterpret_cast<double2*>(p);
-    q[0] = double2{r.o.x, r.o.y};
-    q[1] = double2{r.o.z, r.d.x};
-    q[2] = double2{r.d.y, r.d.z};
-    reinterpret_cast<float4*>(p)[3] = float4{r.E[0], r.E[1], r.E[2], r.E[3]};
-    if (SPH) {
-        reinterpret_cast<int4*>(p)[4] = int4{__float_as_int(r.E[4]), __float_as_int(r.E[5]), r.excl, __float_as_int(r.s)};
-        reinterpret_cast<int4*>(p)[5] = int4{(int)r.seq[0], (int)r.seq[1], (int)r.seq[2], (int)r.seq[3]};
-    } else {
-        reinterpret_cast<int4*>(p)[4] = int4{__float_as_int(r.E[4]), __float_as_int(r.E[5]), r.excl, r.prefix};
-        reinterpret_cast<int4*>(p)[5] = int4{r.ray, 0, 0, 0};
-    }
-}
 
 // Face i (0..4) of a packed sequence: bits [24 i, 24 i + 24) of the 128-bit
 // little-endian word seq (constant word indices, so the array stays in registers).
@@ -149,6 +104,61 @@ __device__ __forceinline__ void put_face(uint32_t seq[4], int i, uint32_t f) {
         case 2: seq[1] |= f << 16; seq[2] |= f >> 16; break;
         case 3: seq[2] |= f << 8; break;
         default: seq[3] |= f; break;
+    }
+}
+
+// faces: reflections of the queue's rays (its launch's depth; uniform).
+template <int MODE>
+__device__ __forceinline__ void load_ray(const char* __restrict__ p, int faces, Ray& r) {
+    const double2* q = reinterpret_cast<const double2*>(p);
+    const double2 a0 = q[0], a1 = q[1], a2 = q[2];
+    const int4 f0 = reinterpret_cast<const int4*>(p)[3];
+    r.o = d3{a0.x, a0.y, a1.x};
+    r.d = d3{a1.y, a2.x, a2.y};
+    if (MODE & kModeCoverage) {
+        const int4 f1 = reinterpret_cast<const int4*>(p)[4];
+        const int4 f2 = reinterpret_cast<const int4*>(p)[5];
+        r.E[0] = __int_as_float(f0.x);
+        r.E[1] = __int_as_float(f0.y);
+        r.E[2] = __int_as_float(f0.z);
+        r.E[3] = __int_as_float(f0.w);
+        r.E[4] = __int_as_float(f1.x);
+        r.E[5] = __int_as_float(f1.y);
+        r.excl = f1.z;
+        r.prefix = f1.w;
+        r.ray = f2.x;
+    } else if (MODE & kModeSphere) {
+        r.prefix = -1;
+        r.ray = -1;
+        r.s = __int_as_float(f0.x);
+        r.seq[0] = (uint32_t)f0.y;
+        r.seq[1] = (uint32_t)f0.z;
+        r.seq[2] = (uint32_t)f0.w;
+        r.seq[3] = faces > 4 ? (uint32_t)reinterpret_cast<const int4*>(p)[4].x : 0u;
+        r.excl = (int32_t)get_face(r.seq, faces - 1);
+    } else {
+        r.excl = f0.x;
+        r.prefix = f0.y;
+        r.ray = f0.z;
+    }
+}
+
+template <int MODE>
+__device__ __forceinline__ void store_ray(char* __restrict__ p, int faces, const Ray& r) {
+    double2* q = reinterpret_cast<double2*>(p);
+    int4* f = reinterpret_cast<int4*>(p) + 3;
+    q[0] = double2{r.o.x, r.o.y};
+    q[1] = double2{r.o.z, r.d.x};
+    q[2] = double2{r.d.y, r.d.z};
+    if (MODE & kModeCoverage) {
+        reinterpret_cast<float4*>(f)[0] = float4{r.E[0], r.E[1], r.E[2], r.E[3]};
+        f[1] = int4{__float_as_int(r.E[4]), __float_as_int(r.E[5]), r.excl, r.prefix};
+        f[2] = int4{r.ray, 0, 0, 0};
+    } else if (MODE & kModeSphere) {
+        f[0] = int4{__float_as_int(r.s), (int)r.seq[0], (int)r.seq[1], (int)r.seq[2]};
+        if (faces > 4) f[1] = int4{(int)r.seq[3], 0, 0, 0};
+    } else {
+        f[0] = int4{r.excl, r.prefix, r.ray, 0};
     }
 }
 
@@ -352,20 +362,23 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
                 const int64_t pos = lattice_position(a, a.pos0 + item);
                 st.d = fib_dir(a.begin + pos * a.stride, a.num_rays);
                 st.o = d3{a.tx[0], a.tx[1], a.tx[2]};
-                const f3 F = antenna_field(a.tx_ant, f3{(float)st.d.x, (float)st.d.y, (float)st.d.z});
-                st.E[0] = F.x;
-                st.E[1] = 0.0f;
-                st.E[2] = F.y;
-                st.E[3] = 0.0f;
-                st.E[4] = F.z;
-                st.E[5] = 0.0f;
+                if (MODE & kModeCoverage) {
+                    const f3 F = antenna_field(a.tx_ant, f3{(float)st.d.x, (float)st.d.y, (float)st.d.z});
+                    st.E[0] = F.x;
+                    st.E[1] = 0.0f;
+                    st.E[2] = F.y;
+                    st.E[3] = 0.0f;
+                    st.E[4] = F.z;
+                    st.E[5] = 0.0f;
+                }
                 st.excl = -1;
                 st.prefix = -1;
                 st.ray = (int32_t)pos;
                 st.s = 0.0f;
                 st.seq[0] = st.seq[1] = st.seq[2] = st.seq[3] = 0u;
             } else {
-                load_ray<(MODE & kModeSphere) != 0>(a.in + region_in * a.region_cap + region_off, st);
+                load_ray<MODE>((const char*)a.in + (region_in * a.region_cap + region_off) * sbr_ray_bytes(MODE, a.depth),
+                               a.depth, st);
             }
             const d3 o = st.o;
             const d3 d = st.d;
@@ -439,52 +452,57 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
                 // the material's fields in one round trip to memory (used here, so
                 // that no load is sunk into the branches below)
                 Mat mt{};
-                mt.eta_re = mats.m[sh.mat].eta_re;
-                mt.eta_im = mats.m[sh.mat].eta_im;
-                mt.pec = mats.m[sh.mat].pec;
-                mt.scat = mats.m[sh.mat].scat;
-                asm volatile("" ::"v"(mt.eta_re), "v"(mt.eta_im), "v"(mt.pec), "v"(mt.scat));
+                if (MODE & kModeCoverage) {
+                    mt.eta_re = mats.m[sh.mat].eta_re;
+                    mt.eta_im = mats.m[sh.mat].eta_im;
+                    mt.pec = mats.m[sh.mat].pec;
+                    mt.scat = mats.m[sh.mat].scat;
+                    asm volatile("" ::"v"(mt.eta_re), "v"(mt.eta_im), "v"(mt.pec), "v"(mt.scat));
+                } else if (MODE & kModeRecord) {
+                    mt.scat = mats.m[sh.mat].scat;
+                }
                 d3 n{sh.n[0], sh.n[1], sh.n[2]};
                 if (dot(d, n) > 0.0) n = scale(n, -1.0);
                 const double cos_i = -dot(d, n);
                 const d3 dr = add(d, scale(n, 2.0 * cos_i));
                 const d3 p = add(o, scale(d, tbest));
-                const d3 ep = perp_basis(d, n);
-                const d3 eli = cross(ep, d);
-                const d3 elr = cross(ep, dr);
-                cf rp, rl;
-                fresnel(mt, (float)cos_i, rp, rl);
-                const f3 fep{(float)ep.x, (float)ep.y, (float)ep.z};
-                const f3 feli{(float)eli.x, (float)eli.y, (float)eli.z};
-                f3 felr{(float)elr.x, (float)elr.y, (float)elr.z};
                 // diffuse scattering (coverage and record modes): with probability
                 // S^2 the ray leaves in a Lambertian direction and the reflected
                 // components ride on that direction's transverse basis
                 d3 dout = dr;
-                f3 fepo = fep;
+                bool diffuse = false;
                 if ((MODE & (kModeCoverage | kModeRecord)) && mt.scat > 0.0f) {
                     const uint64_t ri = (uint64_t)(a.begin + (int64_t)st.ray * a.stride);
                     const uint64_t c0 = (ri * (uint64_t)(a.max_depth + 1) + (uint64_t)a.depth) * 3ull;
                     const double S = (double)mt.scat;
                     if (uniform01(a.scat_seed, c0) < S * S) {
                         dout = lambert_dir(n, uniform01(a.scat_seed, c0 + 1), uniform01(a.scat_seed, c0 + 2));
-                        const d3 eps = perp_basis(dout, n);
-                        const d3 els = cross(eps, dout);
-                        fepo = f3{(float)eps.x, (float)eps.y, (float)eps.z};
-                        felr = f3{(float)els.x, (float)els.y, (float)els.z};
+                        diffuse = true;
                     }
                 }
-                const cf Ex{st.E[0], st.E[1]}, Ey{st.E[2], st.E[3]}, Ez{st.E[4], st.E[5]};
-                const cf ap{fep.x * Ex.re + fep.y * Ey.re + fep.z * Ez.re, fep.x * Ex.im + fep.y * Ey.im + fep.z * Ez.im};
-                const cf al{feli.x * Ex.re + feli.y * Ey.re + feli.z * Ez.re,
-                            feli.x * Ex.im + feli.y * Ey.im + feli.z * Ez.im};
-                const cf sp = cmul(rp, ap), sl = cmul(rl, al);
-                st.E[0] = sp.re * fepo.x + sl.re * felr.x;
-                st.E[1] = sp.im * fepo.x + sl.im * felr.x;
-                st.E[2] = sp.re * fepo.y + sl.re * felr.y;
-                st.E[3] = sp.im * fepo.y + sl.im * felr.y;
-                st.E[4] = sp.re * fepo.z + sl.re * felr.z;
-                st.E[5] = sp.im * fepo.z + sl.im * felr.z;
+                if (MODE & kModeCoverage) {
+                    const d3 ep = perp_basis(d, n);
+                    const d3 eli = cross(ep, d);
+                    const d3 epo = diffuse ? perp_basis(dout, n) : ep;
+                    const d3 elr = cross(epo, dout);
+                    cf rp, rl;
+                    fresnel(mt, (float)cos_i, rp, rl);
+                    const f3 fep{(float)ep.x, (float)ep.y, (float)ep.z};
+                    const f3 feli{(float)eli.x, (float)eli.y, (float)eli.z};
+                    const f3 fepo{(float)epo.x, (float)epo.y, (float)epo.z};
+                    const f3 felr{(float)elr.x, (float)elr.y, (float)elr.z};
+                    const cf Ex{st.E[0], st.E[1]}, Ey{st.E[2], st.E[3]}, Ez{st.E[4], st.E[5]};
+                    const cf ap{fep.x * Ex.re + fep.y * Ey.re + fep.z * Ez.re, fep.x * Ex.im + fep.y * Ey.im + fep.z * Ez.im};
+                    const cf al{feli.x * Ex.re + feli.y * Ey.re + feli.z * Ez.re,
+                                feli.x * Ex.im + feli.y * Ey.im + feli.z * Ez.im};
+                    const cf sp = cmul(rp, ap), sl = cmul(rl, al);
+                    st.E[0] = sp.re * fepo.x + sl.re * felr.x;
+                    st.E[1] = sp.im * fepo.x + sl.im * felr.x;
+                    st.E[2] = sp.re * fepo.y + sl.re * felr.y;
+                    st.E[3] = sp.im * fepo.y + sl.im * felr.y;
+                    st.E[4] = sp.re * fepo.z + sl.re * felr.z;
+                    st.E[5] = sp.im * fepo.z + sl.im * felr.z;
+                }
                 st.o = p;
                 st.d = dout;
                 st.excl = sh.face;
@@ -523,8 +541,9 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
             if (lane == 0) b = atomicAdd(a.out_count + region * kCounterStride, (uint32_t)__popcll(m));
             b = __shfl(b, 0);
             if (alive)
-                store_ray<(MODE & kModeSphere) != 0>(
-                    a.out + region * a.region_cap + b + __popcll(m & ((1ull << lane) - 1ull)), st);
+                store_ray<MODE>((char*)a.out + (region * a.region_cap + b + __popcll(m & ((1ull << lane) - 1ull))) *
+                                                   sbr_ray_bytes(MODE, a.depth + 1),
+                                a.depth + 1, st);
         }
     }
     // the dropped rays go to word 1 of the region counter (the next launch adds
