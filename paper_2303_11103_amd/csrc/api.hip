@@ -437,6 +437,8 @@ rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_dev
         a.rgny = sphere->rgny;
         a.rz_lo = sphere->rz_lo;
         a.rz_hi = sphere->rz_hi;
+        a.rx_zmin = sphere->rx_zmin;
+        a.rx_zmax = sphere->rx_zmax;
         a.sphere_k = sphere->sphere_k;
         a.pairs = sphere->pairs;
         a.pairs_mask = sphere->pairs_mask;
@@ -853,6 +855,8 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
         sph.rgny = std::max(1, (int)std::ceil((rhi[1] - rlo[1] + 2.0 * r_ins) / cell));
         sph.rz_lo = rlo[2] - r_ins;
         sph.rz_hi = rhi[2] + r_ins;
+        sph.rx_zmin = rlo[2];
+        sph.rx_zmax = rhi[2];
         // CSR lists: receiver r in every cell that meets the square of half-side r_ins around it
         const int ncell = sph.rgnx * sph.rgny;
         std::vector<int32_t> start(ncell + 1, 0), items;

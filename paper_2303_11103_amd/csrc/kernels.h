@@ -79,7 +79,7 @@ struct SbrArgs {
     const int32_t* cell_rx;
     double rgx0, rgy0, rgcell;
     int32_t rgnx, rgny;
-    double rz_lo, rz_hi;
+    double rz_lo, rz_hi, rx_zmin, rx_zmax;  // the receivers' heights with and without r_ins
     double sphere_k;             // kappa sqrt(4 pi / N): sphere radius per metre of path
     uint64_t* pairs;
     uint64_t pairs_mask;

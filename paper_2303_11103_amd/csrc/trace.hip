@@ -179,13 +179,14 @@ __device__ void pair_insert(const SbrArgs& a, int32_t r, int32_t slot) {
     atomicOr(a.pairs_overflow, 1u);
 }
 
-// Receivers whose reception sphere the segment o + t d, 0 <= t <= tbest
-// (tbest = inf: no hit) passes: the closest approach t* = clamp((R - o) . d,
-// 0, tbest) lies within sphere_k (s + t*) of R.  The segment is clipped to
-// the receivers' height band and grid rectangle and walked cell by cell (2-D
-// DDA); the face sequence's prefix slot is inserted on the first pair.
-__device__ void sphere_pairs(const SbrArgs& a, const Ray& st, d3 o, d3 d, double tbest) {
-    double t0 = 0.0, t1 = tbest;
+// The part t0 <= t <= t1 of the segment o + t d, 0 <= t <= tbest, on which a
+// reception sphere can be met: inside the receivers' grid rectangle and height
+// band, which hold the largest sphere of any path, then inside the band of the
+// largest sphere of this segment, sphere_k (s + t1) (a path is mostly ten times
+// shorter than the longest, so that band is a metre high and not twenty).
+__device__ __forceinline__ bool rx_span(const SbrArgs& a, float s, d3 o, d3 d, double tbest, double& t0, double& t1) {
+    t0 = 0.0;
+    t1 = tbest;
     auto clip = [&](double oc, double dc, double lo, double hi) {
         if (dc != 0.0) {
             const double ta = (lo - oc) / dc, tb = (hi - oc) / dc;
@@ -198,7 +199,24 @@ __device__ void sphere_pairs(const SbrArgs& a, const Ray& st, d3 o, d3 d, double
     clip(o.z, d.z, a.rz_lo, a.rz_hi);
     clip(o.x, d.x, a.rgx0, a.rgx0 + a.rgnx * a.rgcell);
     clip(o.y, d.y, a.rgy0, a.rgy0 + a.rgny * a.rgcell);
-    if (!(t0 <= t1)) return;
+    if (!(t0 <= t1)) return false;
+    const double rad = a.sphere_k * ((double)s + t1) * (1.0 + 1e-9) + 1e-9;
+    clip(o.z, d.z, a.rx_zmin - rad, a.rx_zmax + rad);
+    return t0 <= t1;
+}
+
+// Receivers whose reception sphere the segment o + t d, 0 <= t <= tbest
+// (tbest = inf: no hit) passes: the closest approach t* = clamp((R - o) . d,
+// 0, tbest) lies within sphere_k (s + t*) of R.  The segment's span is walked
+// over the grid cell by cell (2-D DDA).  ANY: whether there is one; otherwise
+// the face sequence's prefix slot and the pairs are inserted.  10^8 rays of
+// depth 5 for 4096 street receivers of a city: 26.6 -> 22.1 ms with the spans
+// of a segment's own spheres and without the last segments that meet none
+// (their launch 2.7 ms -> 94 us).
+template <bool ANY>
+__device__ bool sphere_pairs(const SbrArgs& a, const Ray& st, d3 o, d3 d, double tbest) {
+    double t0, t1;
+    if (!rx_span(a, st.s, o, d, tbest, t0, t1)) return false;
     const double px = o.x + t0 * d.x - a.rgx0, py = o.y + t0 * d.y - a.rgy0;
     int ix = min(max((int)floor(px / a.rgcell), 0), a.rgnx - 1);
     int iy = min(max((int)floor(py / a.rgcell), 0), a.rgny - 1);
@@ -216,8 +234,9 @@ __device__ void sphere_pairs(const SbrArgs& a, const Ray& st, d3 o, d3 d, double
             double ts = dot(sub(R, o), d);
             ts = ts < 0.0 ? 0.0 : (ts > tbest ? tbest : ts);
             const d3 w = sub(add(o, scale(d, ts)), R);
-            const double rad = a.sphere_k * ((double)st.s + ts);
+            const double rad = a.sphere_k * ((double)st.s + ts) * (ANY ? 1.0 + 1e-9 : 1.0);
             if (dot(w, w) <= rad * rad) {
+                if (ANY) return true;
                 if (slot == -3) {
                     slot = -1;
                     for (int i = 0; i < a.depth && slot != -2; ++i)
@@ -237,6 +256,7 @@ __device__ void sphere_pairs(const SbrArgs& a, const Ray& st, d3 o, d3 d, double
             if (iy < 0 || iy >= a.rgny) break;
         }
     }
+    return false;
 }
 
 // Whether the ray o + t d, t > 0, crosses the coverage plane z = gz inside
@@ -248,25 +268,6 @@ __device__ __forceinline__ bool crosses_grid(const SbrArgs& a, d3 o, d3 d, doubl
     const double x = o.x + tc * d.x, y = o.y + tc * d.y;
     const double fx = floor((x - a.gx0) / a.gcell), fy = floor((y - a.gy0) / a.gcell);
     return fx >= 0.0 && fx < (double)a.gnx && fy >= 0.0 && fy < (double)a.gny;
-}
-
-// Whether the ray o + t d, t >= 0, enters the receivers' height band and grid
-// rectangle (the region where reception spheres are looked up).
-__device__ __forceinline__ bool reaches_rx_region(const SbrArgs& a, d3 o, d3 d) {
-    double t0 = 0.0, t1 = __builtin_inf();
-    auto clip = [&](double oc, double dc, double lo, double hi) {
-        if (dc != 0.0) {
-            const double ta = (lo - oc) / dc, tb = (hi - oc) / dc;
-            t0 = fmax(t0, fmin(ta, tb));
-            t1 = fmin(t1, fmax(ta, tb));
-        } else if (oc < lo || oc > hi) {
-            t1 = -1.0;
-        }
-    };
-    clip(o.z, d.z, a.rz_lo, a.rz_hi);
-    clip(o.x, d.x, a.rgx0, a.rgx0 + a.rgnx * a.rgcell);
-    clip(o.y, d.y, a.rgy0, a.rgy0 + a.rgny * a.rgcell);
-    return t0 <= t1;
 }
 
 // Adds the deposits of a wave to the map.  Rays of a wave leave the
@@ -395,9 +396,14 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
                 search = crosses_grid(a, o, d, tc);
                 if (search) tbest = __longlong_as_double(__double_as_longlong(tc) + 1);  // next double above tc
             }
-            // in reception-sphere mode the last segment only meets spheres: one
-            // that never enters the receivers' region needs no search
-            if ((MODE & kModeSphere) && !FIRST && a.depth == a.max_depth) search = reaches_rx_region(a, o, d);
+            // in reception-sphere mode the last segment only meets spheres: it is
+            // searched up to the end of its span (a hit behind meets none)
+            const bool last_span = (MODE & kModeSphere) && !FIRST && a.depth == a.max_depth;
+            if (last_span) {
+                double t0, t1;
+                search = rx_span(a, st.s, o, d, tbest, t0, t1);
+                if (search) tbest = __longlong_as_double(__double_as_longlong(t1) + 1);  // next double above t1
+            }
             if (last) {
                 if (search)
                     best = traverse<false, (MODE & kModeStats) != 0, kTraceBlock, OVF, true>(
@@ -413,7 +419,8 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
                 atomicAdd((unsigned long long*)&a.work[2 * nd + a.depth], (unsigned long long)ts.boxes);
                 atomicAdd((unsigned long long*)&a.work[3 * nd + a.depth], (unsigned long long)ts.tris);
             }
-            if ((MODE & kModeSphere) && a.depth >= 1) sphere_pairs(a, st, o, d, tbest);
+            if (last_span && best < 0) tbest = __builtin_inf();
+            if ((MODE & kModeSphere) && a.depth >= 1) sphere_pairs<false>(a, st, o, d, tbest);
             if (MODE & kModeRecord) {
                 const int64_t at = (int64_t)a.depth * a.count + st.ray;
                 a.rec_tri[at] = best >= 0 ? a.sc.tris[best].orig : -1;
@@ -516,18 +523,19 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
                         dropped = true;
                     }
                 }
-                // likewise in reception-sphere mode for a last segment that cannot
-                // enter the receivers' region
-                if (MODE == kModeSphere && a.depth + 1 == a.max_depth && !reaches_rx_region(a, p, dout)) {
-                    alive = false;
-                    dropped = true;
-                }
                 if (MODE & kModeCandidates) {
                     if (st.prefix != -2) st.prefix = cand_insert(a.table, a.table_mask, st.prefix, sh.face, a.overflow);
                 }
                 if (MODE & kModeSphere) {
                     st.s += (float)tbest;
                     put_face(st.seq, a.depth, (uint32_t)sh.face);
+                    // likewise a last segment that meets no sphere even unobstructed: a
+                    // hit only moves its closest approach away from a receiver and
+                    // shrinks the sphere there
+                    if (a.depth + 1 == a.max_depth && !sphere_pairs<true>(a, st, p, dout, __builtin_inf())) {
+                        alive = false;
+                        dropped = true;
+                    }
                 }
             }
         }

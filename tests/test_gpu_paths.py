@@ -217,3 +217,24 @@ def test_power_gradient_matches_finite_differences(pattern):
     assert rel.max() < 1e-3, (gr, fd)
     if pattern == "iso":
         assert abs(gr[-2]) < 1e-9 * scale.max()   # d/dyaw = 0 for an isotropic V-pol antenna
+
+
+@pytest.mark.parametrize("depth, rays, kappa", [(1, 20_000, 2.0), (2, 20_000, 8.0), (3, 60_000, 2.0), (5, 20_000, 4.0)])
+def test_reception_sphere_pairs_over_receiver_heights(depth, rays, kappa):
+    """The (receiver, sequence) pairs of segments clipped to the spheres' height
+    band, with last segments dropped that meet no sphere: receivers in the
+    street, above the roofs and at the transmitter's height, spheres from small
+    to wider than the streets."""
+    m = lib()
+    w = sg.diff_workload(num_rays=rays)
+    z = [1.5, 1.5, 20.0, 65.0, w.tx[0].pos[2], 0.5]
+    w.rx = [sg.Device((r.pos[0], r.pos[1], float(np.float32(z[i % 6])))) for i, r in enumerate(w.rx[:24])]
+    p = params(w, max_depth=depth, max_paths_per_rx=256, cand_mode=1, sphere_kappa=kappa)
+    m.compute_paths(ctx(), scene(w.scene), p, w.tx, w.rx)
+    got = m.last_candidate_count(ctx())
+    rxp = np.array([r.pos for r in w.rx], dtype=np.float32).astype(np.float64)
+    r = sbr.trace(w.scene, w.tx[0], oracle_params(p), candidates=True, sphere=(rxp, kappa),
+                  geo=geom.Geometry(w.scene))
+    sure, pairs = sum(len(s) for s in r.sphere_sure), sum(len(s) for s in r.sphere_pairs)
+    print("pairs gpu %d, oracle %d (%d sure)" % (got, pairs, sure), flush=True)
+    assert sure > 0 and sure <= got <= pairs + len(r.sphere_borderline)
