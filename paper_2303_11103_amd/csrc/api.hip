@@ -134,6 +134,7 @@ struct rt_ctx {
     DevBuf rx;         // double [nrx][3], then Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
+    DevBuf image;      // image method: queue of (receiver, candidate) pairs
     DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
     DevBuf scat;       // scattered paths: points, masks, prefixes, counts of one chunk
     void* scratch = nullptr;  // this device's copy of the fixed scratch array
@@ -516,7 +517,7 @@ rt_status rt_destroy(rt_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->paths,
-                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->diff})
+                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->diff})
         if (b->p) (void)hipFree(b->p);
     for (Staging& b : c->stage) {
         if (b.done) (void)hipEventSynchronize(b.done);  // its copy may be on another stream than the last
@@ -949,7 +950,8 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
         for (int k = 0; k < 3; ++k) pa.tx[k] = tx[t].pos[k];
         pa.tx_ant = make_antenna(tx + t);
         const int64_t items = sphere ? (int64_t)nrx + (int64_t)hc[0] : (int64_t)nrx * ((int64_t)hc[0] + 1);
-        RT_HIP(rt::launch_image_paths(pa, mats, items, c->stream));
+        RT_HIP(ensure(c->image, rt::image_scratch(items)));
+        RT_HIP(rt::launch_image_paths(pa, mats, items, c->image.p, c->stream));
         const size_t off = (size_t)t * per;
         RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
                                      depth + off, faces + (size_t)fd * off, num_paths + (size_t)t * nrx, c->stream));

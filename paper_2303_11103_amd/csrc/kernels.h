@@ -158,7 +158,9 @@ hipError_t launch_extract_pairs(const uint64_t* pairs, uint64_t pairs_cap, const
                                 int32_t* out_rx, uint32_t* count, uint32_t max_out, hipStream_t s);
 hipError_t launch_extract_candidates(const uint64_t* table, uint64_t cap, int32_t max_depth, Cand* out,
                                      uint32_t* count, uint32_t max_out, hipStream_t s);
-hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t max_items, hipStream_t s);
+// Device memory launch_image_paths needs for `items` (receiver, candidate) pairs.
+size_t image_scratch(int64_t items);
+hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, void* scratch, hipStream_t s);
 // First-order diffraction: the valid (receiver, wedge) paths into the unsorted
 // records of a (depth = 1, faces[0] = wedge id, fd = 1).  scratch:
 // diffraction_scratch(nrx, num_wedges) bytes, at most two queues of
