@@ -134,6 +134,7 @@ struct rt_ctx {
     DevBuf rx;         // double [nrx][3], then Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
+    DevBuf cov;        // coverage gradient: queue of marked rays (made with the context, see rt_coverage_grad)
     DevBuf image;      // image method: queue of (receiver, candidate) pairs
     DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
     DevBuf scat;       // scattered paths: points, masks, prefixes, counts of one chunk
@@ -508,6 +509,11 @@ rt_status rt_create(rt_ctx** out, int32_t device) {
     c->scratch = scr;
     int cu = 0;
     if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cu > 0) c->num_cu = cu;
+    const hipError_t e = ensure(c->cov, rt::coverage_grad_scratch(rt::kCovCapturedChunk, c->num_cu));
+    if (e != hipSuccess) {
+        delete c;
+        return fail(e == hipErrorOutOfMemory ? RT_ERR_OOM : RT_ERR_DEVICE, hipGetErrorString(e));
+    }
     *out = c;
     return RT_OK;
 }
@@ -517,7 +523,7 @@ rt_status rt_destroy(rt_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->paths,
-                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->diff})
+                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->cov, &c->diff})
         if (b->p) (void)hipFree(b->p);
     for (Staging& b : c->stage) {
         if (b.done) (void)hipEventSynchronize(b.done);  // its copy may be on another stream than the last
@@ -1238,6 +1244,7 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.count = traced_count(p);
     a.max_depth = p->max_depth;
     a.nm = nm;
+    for (float S : s->scat) a.scatters |= S > 0.0f;
     for (int k = 0; k < 3; ++k) a.tx[k] = tx->pos[k];
     rot(tx->yaw, tx->pitch, tx->roll, a.R);
     const double yaw = tx->yaw, pitch = tx->pitch, roll = tx->roll;  // fp64 sines of the fp32 angles
@@ -1266,7 +1273,14 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.hit_tri = hit_tri;
     a.hit_t = hit_t;
     a.out = out;
-    RT_HIP(rt::launch_coverage_grad(a, make_mats(s, p->freq_hz), c->num_cu, c->stream));
+    // under capture nothing can be allocated: if the queue is not there for the
+    // whole call, the rays go through what the context was made with
+    int64_t chunk = std::min(a.count, rt::kCovChunk);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    RT_HIP(hipStreamIsCapturing(c->stream, &cap));
+    if (cap == hipStreamCaptureStatusNone) RT_HIP(ensure(c->cov, rt::coverage_grad_scratch(chunk, c->num_cu)));
+    else if (c->cov.bytes < rt::coverage_grad_scratch(chunk, c->num_cu)) chunk = std::min(chunk, rt::kCovCapturedChunk);
+    RT_HIP(rt::launch_coverage_grad(a, make_mats(s, p->freq_hz), c->num_cu, chunk, c->cov.p, c->stream));
     return RT_OK;
 }
 

@@ -19,6 +19,8 @@
 //     deta/deps_r = 1, deta/dsigma = -j / (eps0 w).
 // Power derivatives dP/dtheta = 2 Re(conj(a) da/dtheta) are contracted with
 // the upstream adjoint dL/dP_r and accumulated with fp64 atomics.
+#include <algorithm>
+
 #include "traverse.h"
 
 namespace rt {
@@ -416,17 +418,28 @@ __global__ void power_grad_kernel(GradArgs g, MatTable mats) {
 //     material's two tangents: only dE/d eps_r is carried.  Every mark adds
 //     w = wscale |F_rx . E|^2 / |d_z| and dw = wscale 2 Re(conj(a) F_rx . dE) / |d_z|.
 // Most rays never cross the region, and the second pass is fp64 arithmetic
-// with antenna functions, so a wave collects marked rays in LDS and replays
-// 64 at a time, those without a reflection apart from the others.  After a
-// reflection a field is its two components on the segment's transverse basis.
-// Tangents are a template parameter: with ten for every scene the kernel took
-// 220 registers.  Bound by fp64 arithmetic; 10^7 rays of depth 3 over the
-// street canyon's 770 triangles: 1380 -> 411 us, of which the walk is 232.
+// with antenna functions, so it runs over a queue, in a launch of its own: the
+// walk needs a third of its registers and many waves to hide the records' and
+// the normals' latency.  Rays without a reflection are kept apart from the
+// others.  After a reflection a field is its two components on the segment's
+// transverse basis.  Tangents are a template parameter: with ten for every
+// scene one kernel for all took 220 registers.  Bound by fp64 arithmetic; 10^7
+// rays of depth 3 over the street canyon's 770 triangles: 1380 us as one
+// kernel of one thread per ray -> 170 (walk) + 151 us (replay).
 __device__ __forceinline__ cd dot3(const cd* v, d3 u) {
     return cd{v[0].re * u.x + v[1].re * u.y + v[2].re * u.z, v[0].im * u.x + v[1].im * u.y + v[2].im * u.z};
 }
 
-constexpr int kCovWaves = 3;  // per SIMD: 168 registers; the grid is three blocks per CU
+constexpr int kCovWaves = 3;  // of the replay per SIMD: 168 registers; both grids are three blocks per CU
+constexpr int kWalkTris = 1024;
+
+// Marked rays (index, marks) in parts, one per wave: count[w] = (those from the
+// back of part w, those from its front).
+struct CovQueue {
+    uint2* ray;
+    uint2* count;
+    int64_t part;
+};
 
 struct CovHit {
     d3 n;              // normal facing the ray
@@ -438,9 +451,8 @@ struct CovHit {
 
 // The reflection of recorded ray j at depth k: the specular direction, or the
 // forward kernel's diffuse draw (it depends on no parameter).
-__device__ __forceinline__ CovHit cov_reflect(const CovGradArgs& g, const MatTable& mats, int64_t j, int k, int tri,
-                                              double t, d3 o, d3 d) {
-    const Shade sh = g.sc.shades[g.sc.leaf_of_input[tri]];
+__device__ __forceinline__ CovHit cov_reflect(const CovGradArgs& g, const MatTable& mats, int64_t j, int k,
+                                              const Shade& sh, double t, d3 o, d3 d) {
     CovHit h;
     h.n = d3{sh.n[0], sh.n[1], sh.n[2]};
     if (dot(d, h.n) > 0.0) h.n = scale(h.n, -1.0);
@@ -449,7 +461,7 @@ __device__ __forceinline__ CovHit cov_reflect(const CovGradArgs& g, const MatTab
     h.p = add(o, scale(d, t));
     h.mat = sh.mat;
     h.diffuse = false;
-    if (mats.m[sh.mat].scat > 0.0f) {
+    if (g.scatters && mats.m[sh.mat].scat > 0.0f) {
         const uint64_t ri = (uint64_t)(g.begin + j * g.stride);
         const uint64_t c0 = (ri * (uint64_t)(g.max_depth + 1) + (uint64_t)k) * 3ull;
         const double S = (double)mats.m[sh.mat].scat;
@@ -462,7 +474,10 @@ __device__ __forceinline__ CovHit cov_reflect(const CovGradArgs& g, const MatTab
 }
 
 // Bit k: segment k of recorded ray j crosses the grid plane inside the region.
-__device__ __forceinline__ uint32_t cov_walk(const CovGradArgs& g, const MatTable& mats, int64_t j) {
+// staged: the triangles' shades in input order (LDS), or null.
+template <bool STAGED>
+__device__ __forceinline__ uint32_t cov_walk(const CovGradArgs& g, const MatTable& mats, const Shade* staged,
+                                             int64_t j) {
     uint32_t marks = 0;
     int32_t tri = g.hit_tri[j];
     double t = g.hit_t[j];
@@ -495,7 +510,8 @@ __device__ __forceinline__ uint32_t cov_walk(const CovGradArgs& g, const MatTabl
             }
         }
         if (tri < 0 || k == g.max_depth || tri >= g.sc.nt) break;
-        const CovHit h = cov_reflect(g, mats, j, k, tri, t, o, d);
+        const CovHit h = cov_reflect(g, mats, j, k, STAGED ? staged[tri] : g.sc.shades[g.sc.leaf_of_input[tri]], t, o,
+                                     d);
         o = h.p;
         d = h.dout;
         tri = tri_next;
@@ -570,7 +586,7 @@ __device__ __forceinline__ void cov_replay(const CovGradArgs& g, const MatTable&
         }
         if (!(marks >> (k + 1))) return;
         const int64_t at = (int64_t)k * g.count + j;
-        const CovHit h = cov_reflect(g, mats, j, k, g.hit_tri[at], g.hit_t[at], o, d);
+        const CovHit h = cov_reflect(g, mats, j, k, g.sc.shades[g.sc.leaf_of_input[g.hit_tri[at]]], g.hit_t[at], o, d);
         const d3 ep = perp_basis(d, h.n), eli = cross(ep, d);
         const d3 epo = h.diffuse ? perp_basis(h.dout, h.n) : ep;
         const Mat& mt = mats.m[h.mat];
@@ -619,49 +635,47 @@ __device__ __forceinline__ void cov_replay(const CovGradArgs& g, const MatTable&
     }
 }
 
+// Rays [first, first + n).  Every wave writes the rays it marks to its own part
+// of the queue, those marked on segment 0 alone from the back: appends to a
+// shared queue took 140 us, atomics on two counters.
+template <bool STAGED>
+__global__ __launch_bounds__(256) void coverage_walk_kernel(CovGradArgs g, MatTable mats, int64_t first, int64_t n,
+                                                            CovQueue q) {
+    __shared__ Shade staged[STAGED ? kWalkTris : 1];
+    if (STAGED) {
+        for (int i = threadIdx.x; i < g.sc.nt; i += 256) staged[i] = g.sc.shades[g.sc.leaf_of_input[i]];
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (int64_t)gridDim.x * 4;
+    uint2* out = q.ray + wave * q.part;
+    uint32_t n0 = 0, n1 = 0;
+    for (int64_t base = wave * 64; base < n; base += nwaves * 64) {
+        const int64_t j = first + base + lane;
+        const uint32_t marks = base + lane < n ? cov_walk<STAGED>(g, mats, staged, j) : 0u;
+        const uint64_t below = (1ull << lane) - 1ull;
+        const uint64_t b0 = __ballot(marks == 1u), b1 = __ballot(marks > 1u);
+        if (marks == 1u) out[q.part - 1 - n0 - __popcll(b0 & below)] = uint2{(uint32_t)j, marks};
+        if (marks > 1u) out[n1 + __popcll(b1 & below)] = uint2{(uint32_t)j, marks};
+        n0 += (uint32_t)__popcll(b0);
+        n1 += (uint32_t)__popcll(b1);
+    }
+    if (lane == 0) q.count[wave] = uint2{n0, n1};
+}
+
 template <int NM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kCovWaves, kCovWaves)))
-void coverage_grad_kernel(CovGradArgs g, MatTable mats) {
+void coverage_grad_kernel(CovGradArgs g, MatTable mats, CovQueue q) {
     constexpr int kOut = 2 * NM + 3;  // the region sum, (eps_r, sigma) per material, yaw, pitch
-    __shared__ uint2 queue[4][2][128];  // marked rays (index, marks) of each wave: last mark on segment 0, or later
     __shared__ double red[4][kOut];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     CovSums<NM> acc{};
-    int n0 = 0, n1 = 0;
-    for (int64_t base = ((int64_t)blockIdx.x * 4 + wave) * 64;; base += (int64_t)gridDim.x * 256) {
-        const bool more = base < g.count;
-        if (more) {
-            const int64_t j = base + lane;
-            const uint32_t marks = j < g.count ? cov_walk(g, mats, j) : 0u;
-            const uint64_t below = (1ull << lane) - 1ull;
-            const uint64_t b0 = __ballot(marks == 1u), b1 = __ballot(marks > 1u);
-            if (marks == 1u) queue[wave][0][n0 + __popcll(b0 & below)] = uint2{(uint32_t)j, marks};
-            if (marks > 1u) queue[wave][1][n1 + __popcll(b1 & below)] = uint2{(uint32_t)j, marks};
-            n0 += __popcll(b0);
-            n1 += __popcll(b1);
-        }
-        // full batches of one kind while there are rays to walk, then what is left
-        while (n0 >= 64 || n1 >= 64 || (!more && n0 + n1 > 0)) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            uint2 e{0u, 0u};
-            if (n1 >= 64) {
-                n1 -= 64;
-                e = queue[wave][1][n1 + lane];
-            } else if (n0 >= 64) {
-                n0 -= 64;
-                e = queue[wave][0][n0 + lane];
-            } else {
-                const int from1 = n1, from0 = min(n0, 64 - n1);
-                if (lane < from1) e = queue[wave][1][lane];
-                else if (lane < from1 + from0) e = queue[wave][0][n0 - 1 - (lane - from1)];
-                n1 = 0;
-                n0 -= from0;
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (e.y) cov_replay<NM>(g, mats, (int64_t)e.x, e.y, acc);
-        }
-        if (!more) break;
+    const int64_t part = (int64_t)blockIdx.x * 4 + wave;
+    const uint2* in = q.ray + part * q.part;
+    const uint32_t n0 = q.count[part].x, n1 = q.count[part].y;
+    for (uint32_t i = (uint32_t)lane; i < n0 + n1; i += 64) {
+        const uint2 e = in[i < n1 ? (int64_t)i : q.part - 1 - (int64_t)(i - n1)];
+        cov_replay<NM>(g, mats, (int64_t)e.x, e.y, acc);
     }
     // block reduction (wave shuffles, then the four waves through LDS), one
     // fp64 atomic per block and output
@@ -698,17 +712,40 @@ hipError_t launch_power_grad(const GradArgs& a, const MatTable& mats, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, hipStream_t s) {
-    if (a.count <= 0) return hipSuccess;
-    const int64_t need = (a.count + 255) / 256;
-    const int64_t grid = (int64_t)num_cu * kCovWaves;
-    const dim3 blocks((unsigned)(need < grid ? need : grid)), threads(256);
-    switch (a.nm) {
-        case 1: hipLaunchKernelGGL(coverage_grad_kernel<1>, blocks, threads, 0, s, a, mats); break;
-        case 2: hipLaunchKernelGGL(coverage_grad_kernel<2>, blocks, threads, 0, s, a, mats); break;
-        case 3: hipLaunchKernelGGL(coverage_grad_kernel<3>, blocks, threads, 0, s, a, mats); break;
-        case 4: hipLaunchKernelGGL(coverage_grad_kernel<4>, blocks, threads, 0, s, a, mats); break;
-        default: return hipErrorInvalidValue;
+namespace {
+int64_t cov_blocks(int64_t rays, int num_cu) {
+    return std::min<int64_t>((rays + 255) / 256, (int64_t)num_cu * kCovWaves);
+}
+int64_t cov_part(int64_t rays, int num_cu) {
+    const int64_t lanes = cov_blocks(rays, num_cu) * 256;
+    return (rays + lanes - 1) / lanes * 64;
+}
+}  // namespace
+
+size_t coverage_grad_scratch(int64_t rays, int num_cu) {
+    return (size_t)cov_blocks(rays, num_cu) * 4 * (size_t)(cov_part(rays, num_cu) + 1) * sizeof(uint2);
+}
+
+hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, int64_t chunk, void* scratch,
+                                hipStream_t s) {
+    for (int64_t first = 0; first < a.count; first += chunk) {
+        const int64_t n = std::min(chunk, a.count - first), nb = cov_blocks(n, num_cu);
+        CovQueue q;
+        q.part = cov_part(n, num_cu);
+        q.count = (uint2*)scratch;
+        q.ray = q.count + nb * 4;
+        const dim3 blocks((unsigned)nb), threads(256);
+        if (a.sc.nt <= kWalkTris)
+            hipLaunchKernelGGL(coverage_walk_kernel<true>, blocks, threads, 0, s, a, mats, first, n, q);
+        else
+            hipLaunchKernelGGL(coverage_walk_kernel<false>, blocks, threads, 0, s, a, mats, first, n, q);
+        switch (a.nm) {
+            case 1: hipLaunchKernelGGL(coverage_grad_kernel<1>, blocks, threads, 0, s, a, mats, q); break;
+            case 2: hipLaunchKernelGGL(coverage_grad_kernel<2>, blocks, threads, 0, s, a, mats, q); break;
+            case 3: hipLaunchKernelGGL(coverage_grad_kernel<3>, blocks, threads, 0, s, a, mats, q); break;
+            case 4: hipLaunchKernelGGL(coverage_grad_kernel<4>, blocks, threads, 0, s, a, mats, q); break;
+            default: return hipErrorInvalidValue;
+        }
     }
     return hipGetLastError();
 }

@@ -282,6 +282,7 @@ struct CovGradArgs {
     int64_t num_rays, begin, stride, count;
     int32_t max_depth;
     int32_t nm;
+    int32_t scatters;         // some material has diffuse reflections
     double tx[3];
     double R[9], Ryaw[9], Rpitch[9];  // tx orientation and its derivatives
     int32_t tx_pattern, tx_pol;
@@ -296,6 +297,11 @@ struct CovGradArgs {
     const double* hit_t;      // [max_depth+1][count]
     double* out;              // [2 nm + 3]: region sum, d/d(eps_r, sigma) per material, d/d yaw, d/d pitch
 };
-hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, hipStream_t s);
+// Rays taken at a time, and the device memory their queue needs (all may be
+// marked).  kCovCapturedChunk rays always fit what a context holds.
+constexpr int64_t kCovChunk = int64_t(1) << 24, kCovCapturedChunk = int64_t(1) << 16;
+size_t coverage_grad_scratch(int64_t rays, int num_cu);
+hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, int64_t chunk, void* scratch,
+                                hipStream_t s);
 
 }  // namespace rt

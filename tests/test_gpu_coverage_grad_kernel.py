@@ -16,8 +16,8 @@ pytestmark = [pytest.mark.gpu, requires_gpu]
 GRID = sg.Grid(-200.0, -200.0, 4.0, 100, 100, 1.5)
 
 
-def _scene(m, nm):
-    s = sg.diff_workload(num_rays=1000).scene
+def _scene(m, nm, city=False):
+    s = sg.make_city(0, 6) if city else sg.diff_workload(num_rays=1000).scene
     tri = (np.asarray(s.tri_mat) + 2 * (np.arange(len(s.tri_mat)) // 2 % 2)) % nm
     mats = [(4.0, 0.0625), (6.0, 0.03125), (3.0, 0.125), (5.0, 0.25)][:nm]   # exact in float32, steps below too
     return m.Scene(ctx(), s.V, s.F, tri.astype(np.int32), mats), np.array(mats)
@@ -34,12 +34,14 @@ def _tx(w, yaw=0.5, pitch=0.25):
 
 
 @pytest.mark.parametrize("scatter", [False, True])
-@pytest.mark.parametrize("nm, rays", [(1, 20_001), (2, 4_097), (3, 20_001), (4, 20_001)])
-def test_derivatives_match_differences_of_the_sum(nm, rays, scatter):
+@pytest.mark.parametrize("nm, rays, city", [(1, 20_001, False), (2, 4_097, False), (3, 20_001, False),
+                                            (4, 20_001, False), (2, 20_001, True)])
+def test_derivatives_match_differences_of_the_sum(nm, rays, city, scatter):
+    """city: more triangles than the walk of the geometry stages."""
     m = lib()
     w = sg.diff_workload(num_rays=rays)
     p = params(w)
-    sc, mats = _scene(m, nm)
+    sc, mats = _scene(m, nm, city)
     if scatter:
         sc.set_scattering([0.5] * nm, 3)
     out = _grad(m, sc, p, _tx(w))
@@ -67,7 +69,7 @@ def test_derivatives_match_differences_of_the_sum(nm, rays, scatter):
     assert (np.abs(got - ref) <= 1e-3 * scale).all()
 
 
-@pytest.mark.parametrize("rays", [1, 63, 65, 257, 10_007])
+@pytest.mark.parametrize("rays", [1, 63, 65, 257, 10_007, 200_003, 2 ** 24 + 1001])
 def test_parts_of_the_lattice_add_up(rays):
     m = lib()
     w = sg.diff_workload(num_rays=rays)
