@@ -117,7 +117,6 @@ __device__ __forceinline__ void load_ray(const char* __restrict__ p, int faces, 
     r.d = d3{a1.y, a2.x, a2.y};
     if (MODE & kModeCoverage) {
         const int4 f1 = reinterpret_cast<const int4*>(p)[4];
-        const int4 f2 = reinterpret_cast<const int4*>(p)[5];
         r.E[0] = __int_as_float(f0.x);
         r.E[1] = __int_as_float(f0.y);
         r.E[2] = __int_as_float(f0.z);
@@ -125,8 +124,8 @@ __device__ __forceinline__ void load_ray(const char* __restrict__ p, int faces, 
         r.E[4] = __int_as_float(f1.x);
         r.E[5] = __int_as_float(f1.y);
         r.excl = f1.z;
-        r.prefix = f1.w;
-        r.ray = f2.x;
+        r.prefix = -1;
+        r.ray = f1.w;
     } else if (MODE & kModeSphere) {
         r.prefix = -1;
         r.ray = -1;
@@ -152,8 +151,7 @@ __device__ __forceinline__ void store_ray(char* __restrict__ p, int faces, const
     q[2] = double2{r.d.y, r.d.z};
     if (MODE & kModeCoverage) {
         reinterpret_cast<float4*>(f)[0] = float4{r.E[0], r.E[1], r.E[2], r.E[3]};
-        f[1] = int4{__float_as_int(r.E[4]), __float_as_int(r.E[5]), r.excl, r.prefix};
-        f[2] = int4{r.ray, 0, 0, 0};
+        f[1] = int4{__float_as_int(r.E[4]), __float_as_int(r.E[5]), r.excl, r.ray};
     } else if (MODE & kModeSphere) {
         f[0] = int4{__float_as_int(r.s), (int)r.seq[0], (int)r.seq[1], (int)r.seq[2]};
         if (faces > 4) f[1] = int4{(int)r.seq[3], 0, 0, 0};

@@ -4,6 +4,7 @@ from types import SimpleNamespace
 
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime is loaded before the library's)
 
 import scenegen as sg
 from paper_2303_11103_amd import rt
