@@ -286,10 +286,12 @@ __device__ __forceinline__ Wedge load_pair(const PathArgs& a, int32_t r0, uint32
 // Pass 2: the exact tests in fp64, then the leg to the receiver, then, for the
 // survivors, the leg from the transmitter.  A wave collects survivors of the
 // first leg in LDS until it has 64, so that the second leg runs with full waves
-// too.  Bound by the any-hit traversals: 0.76 ms for the pairs of 1024 street
-// receivers and 129,768 wedges of a city (0.94 ms with the transmitter's leg
-// first, 1.40 ms that way with 12 instead of 16 waves per CU; blocks of 512
-// with 64 staged nodes leave room for two per CU).
+// too.  The first leg is traversed from the receiver: what blocks it mostly
+// stands in the receiver's street, and boxes are visited by distance from the
+// start.  Bound by the any-hit traversals: 0.51 ms for the pairs of 1024 street
+// receivers and 129,768 wedges of a city (0.76 ms from the wedge, 0.94 ms with
+// the transmitter's leg first, 1.40 ms that way with 12 instead of 16 waves per
+// CU; blocks of 512 with 64 staged nodes leave room for two per CU).
 constexpr int kLegBlock = 512, kLegNodes = 64;
 template <bool OVF>
 __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a, int32_t r0,
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
             d3 P;
             const Wedge w = load_pair(a, r0, it, P);
             EdgePoint pt;
-            ok = edge_point(w, S, P, pt) && !leg_blocked<kLegBlock, OVF>(a.sc, lds_nodes, n_lds, stack, pt.Q, P, w);
+            ok = edge_point(w, S, P, pt) && !leg_blocked<kLegBlock, OVF>(a.sc, lds_nodes, n_lds, stack, P, pt.Q, w);
         }
         const uint64_t m = __ballot(ok);
         if (ok) mine[have + __popcll(m & ((1ull << lane) - 1ull))] = it;
