@@ -198,18 +198,25 @@ __global__ __launch_bounds__(kBlock) void scatter_gather_kernel(ScatArgs a) {
 // (receiver, ray, depth) slot spent 806 us on 16 receivers and 400,000 rays of
 // depth 3, most lanes idle in each traversal; this takes 220 us.
 constexpr int kVisBlock = 512, kVisNodes = 64, kVisHits = 512;
+constexpr int kVisWaves = 512 * kVisBlock / 64;  // two blocks per CU
 template <bool OVF>
 __global__ __launch_bounds__(kVisBlock) void scatter_visibility_kernel(ScatArgs a) {
     __shared__ int32_t stack[kStack][kVisBlock];
     __shared__ Node lds_nodes[kVisNodes];
     __shared__ uint32_t held[kVisBlock / 64][128];
+    // hits a wave takes of one receiver: kVisHits, fewer where that leaves waves
+    // of a full chip without work (30,000 rays, 2 receivers: 45 -> 12 us)
+    const int64_t n = (int64_t)*a.num_hits;
+    const int64_t even = (a.nrx * n + kVisWaves - 1) / kVisWaves;
+    const int64_t hits = min((int64_t)kVisHits, max((int64_t)64, (even + 63) / 64 * 64));
+    const int64_t per = (n + hits - 1) / hits;
+    if ((int64_t)blockIdx.x * (kVisBlock / 64) >= a.nrx * per) return;
     const int n_lds = stage_nodes<kVisNodes>(a.sc, lds_nodes);
     const int lane = threadIdx.x & 63;
     uint32_t* mine = held[threadIdx.x >> 6];
-    const int64_t n = (int64_t)*a.num_hits, per = (n + kVisHits - 1) / kVisHits;
     const int64_t nwaves = (int64_t)gridDim.x * (kVisBlock / 64);
     for (int64_t item = ((int64_t)blockIdx.x * kVisBlock + threadIdx.x) >> 6; item < a.nrx * per; item += nwaves) {
-        const int64_t r = item / per, h0 = (item - r * per) * kVisHits, h1 = min(n, h0 + kVisHits);
+        const int64_t r = item / per, h0 = (item - r * per) * hits, h1 = min(n, h0 + hits);
         const d3 R{a.rx[3 * r], a.rx[3 * r + 1], a.rx[3 * r + 2]};
         int have = 0;
         auto trace = [&](int take) {
@@ -400,8 +407,8 @@ hipError_t launch_scatter_chunk(const ScatArgs& a, const MatTable& mats, hipStre
     hipLaunchKernelGGL(scatter_gather_kernel, dim3((unsigned)std::min<int64_t>((nrec + kGather - 1) / kGather, 65536)),
                        dim3(kBlock), 0, s, a);
     // two blocks per CU for the traversals
-    const int64_t waves = a.nrx * ((nrec + kVisHits - 1) / kVisHits);
-    const dim3 vgrid((unsigned)std::min<int64_t>((waves + kVisBlock / 64 - 1) / (kVisBlock / 64), 512));
+    const int64_t waves = std::min<int64_t>(a.nrx * ((nrec + 63) / 64), kVisWaves);
+    const dim3 vgrid((unsigned)((waves + kVisBlock / 64 - 1) / (kVisBlock / 64)));
     if (a.sc.stack_need > kStack)
         hipLaunchKernelGGL(scatter_visibility_kernel<true>, vgrid, dim3(kVisBlock), 0, s, a);
     else
