@@ -412,8 +412,8 @@ rt_status rt_paths_coef_grad(rt_ctx* ctx, rt_scene* scene, const rt_trace_params
  * element at the centre, devices at rest).
  *   H [ntx][nrx][T][nr_el][nt_el][K][2] (dev) float32.
  * RT_ERR_ARG for empty dimensions, fs <= 0 with T > 1, or non-finite
- * offsets or velocities.  Enqueued after a synchronous upload of the small
- * host arrays. */
+ * offsets or velocities.  Enqueued; the small host arrays are copied before
+ * the call returns. */
 rt_status rt_paths_cfr(rt_ctx* ctx, int32_t ntx, int32_t nrx, int32_t P, const float* a, const float* tau,
                        const float* aod, const float* aoa, const int32_t* depth, double freq_hz, int32_t K,
                        double spacing_hz, int32_t nt_el, const double* tx_el, int32_t nr_el, const double* rx_el,

@@ -1,6 +1,6 @@
 // First-order edge diffraction for gfx950 (paper Sec. II-B lists first-order
-// diffraction among the interactions of the tracer).  One thread handles one
-// (receiver, wedge) pair in fp64:
+// diffraction among the interactions of the tracer).  Per (receiver, wedge)
+// pair, in fp64:
 //   * diffraction point Q on the edge by Keller's law (equal angles of the
 //     incident and diffracted rays with the edge), inside the edge;
 //   * angles phi' (transmitter) and phi (receiver) about the edge, measured

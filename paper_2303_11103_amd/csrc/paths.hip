@@ -5,9 +5,9 @@
 // Sec. II-A: paths are returned as coefficients and delays).
 //
 // Candidates are the distinct face sequences stored in the prefix table
-// filled by the shoot-and-bounce kernels; one thread handles one
-// (receiver, candidate) pair in fp64: images, back-traced reflection points,
-// validity (segment parameter, front side, point inside the face), occlusion
+// filled by the shoot-and-bounce kernels.  For every (receiver, candidate)
+// pair, in fp64: images, back-traced reflection points, validity (segment
+// parameter, front side, point inside the face); for the valid ones occlusion
 // of every segment by an any-hit BVH traversal, then the field transfer
 // through the Fresnel reflections and the receive pattern.
 #include <algorithm>
