@@ -309,11 +309,11 @@ rt_status check_materials(const rt_material* mats, int32_t nm) {
     return RT_OK;
 }
 
-// Band permutation for coherent ray order: F = largest Fibonacci number
-// <= sqrt(64 pi count), G the one before it (0 disables).
-void band_perm(int64_t count, int64_t stride, int64_t& F, int64_t& G) {
-    F = G = 0;
-    if (stride != 1 || count < 256) return;
+// Band permutation for coherent ray order: f = largest Fibonacci number
+// <= sqrt(64 pi count), g the one before it (f = 0 disables).
+rt::Bands band_perm(int64_t count, int64_t stride) {
+    rt::Bands p{};
+    if (stride != 1 || count < 256) return p;
     double target = std::sqrt(64.0 * M_PI * (double)count);
     int64_t a = 1, b = 2;
     while ((double)(a + b) <= target) {
@@ -321,8 +321,11 @@ void band_perm(int64_t count, int64_t stride, int64_t& F, int64_t& G) {
         a = b;
         b = c;
     }
-    F = b;
-    G = a;
+    p.f = b;
+    p.g = a;
+    p.full = count / b * b;
+    p.inv = 1.0 / (double)b;
+    return p;
 }
 
 int grid_for(const rt_ctx* c) { return c->num_cu * 4; }
@@ -398,9 +401,7 @@ rt_status run_sbr(rt_ctx* c, rt_scene* s, const rt_trace_params* p, const rt_dev
     a.begin = p->ray_begin;
     a.stride = p->ray_stride;
     a.count = count;
-    band_perm(count, p->ray_stride, a.perm_f, a.perm_g);
-    a.perm_full = a.perm_f ? (count / a.perm_f) * a.perm_f : 0;
-    a.perm_inv = a.perm_f ? 1.0 / (double)a.perm_f : 0.0;
+    a.perm = band_perm(count, p->ray_stride);
     a.tmin = p->t_min;
     a.scat_seed = s->scat_seed;
     for (int i = 0; i < 3; ++i) a.tx[i] = tx->pos[i];
@@ -1158,6 +1159,7 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
         for (int64_t pos0 = 0; pos0 < count; pos0 += chunk) {
             sa.pos0 = pos0;
             sa.n = std::min<int64_t>(chunk, count - pos0);
+            sa.perm = band_perm(sa.n, p->ray_stride);
             RT_HIP(rt::launch_scatter_chunk(sa, mats, c->stream));
         }
         RT_HIP(rt::launch_scatter_tail(sa, c->stream));

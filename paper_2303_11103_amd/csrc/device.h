@@ -232,6 +232,42 @@ __device__ __forceinline__ d3 fib_dir(int64_t i, int64_t N) {
     return d3{rho * c, rho * s, z};
 }
 
+// Band permutation of traced positions (see banded): f, g consecutive Fibonacci
+// numbers (f = 0: identity), full the positions in whole bands, inv = 1 / f.
+struct Bands {
+    int64_t f, g, full;
+    double inv;
+};
+
+// q = floor(x / F), r = x - q F for 0 <= x < 2^52 and F < 2^26, using the
+// precomputed double 1/F and one correction step.
+__device__ __forceinline__ void divmod(int64_t x, int64_t F, double invF, int64_t& q, int64_t& r) {
+    q = (int64_t)((double)x * invF);
+    r = x - q * F;
+    if (r < 0) {
+        q -= 1;
+        r += F;
+    } else if (r >= F) {
+        q += 1;
+        r -= F;
+    }
+}
+
+// Traced position j -> lattice position.  With a band permutation, positions
+// are taken in bands of F consecutive indices (a thin latitude ring); inside
+// a band, rank r maps to offset r * G mod F (G the preceding Fibonacci
+// number), which walks the ring in azimuth order, so 64 consecutive positions
+// form a compact patch of directions.
+__device__ __forceinline__ int64_t banded(const Bands& p, int64_t j) {
+    if (p.f > 0 && j < p.full) {
+        int64_t b, r, q2, r2;
+        divmod(j, p.f, p.inv, b, r);
+        divmod(r * p.g, p.f, p.inv, q2, r2);
+        return b * p.f + r2;
+    }
+    return j;
+}
+
 // ---------------------------------------------------------------- Fresnel
 __device__ __forceinline__ void fresnel(const Mat& m, float cos_i, cf& r_perp, cf& r_par) {
     if (m.pec) {

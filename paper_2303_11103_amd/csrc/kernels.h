@@ -36,9 +36,7 @@ struct SbrArgs {
     int64_t begin, stride;
     int64_t count;      // traced rays (positions 0..count-1)
     int64_t pos0, chunk; // positions handled by this launch sequence: [pos0, pos0 + chunk)
-    int64_t perm_f, perm_g;  // band permutation (Fibonacci numbers F_m, F_{m-1}); 0 = identity
-    int64_t perm_full;       // positions below this are permuted (whole bands)
-    double perm_inv;         // 1 / F_m
+    Bands perm;         // order of the positions
     double tmin;
     uint64_t scat_seed;  // SplitMix64 seed of the diffuse-scattering draws
     double tx[3];
@@ -199,6 +197,7 @@ struct alignas(16) ScatHit {
 static_assert(sizeof(ScatHit) == 64, "scattering hit size");
 
 struct ScatArgs {
+    Bands perm;          // order in which a chunk's rays are traced
     DevScene sc;
     int64_t num_rays, begin, stride;
     int64_t pos0, n;          // lattice positions [pos0, pos0 + n) of this chunk

@@ -16,35 +16,6 @@
 namespace rt {
 namespace {
 
-// q = floor(x / F), r = x - q F for 0 <= x < 2^52 and F < 2^26, using the
-// precomputed double 1/F and one correction step.
-__device__ __forceinline__ void divmod(int64_t x, int64_t F, double invF, int64_t& q, int64_t& r) {
-    q = (int64_t)((double)x * invF);
-    r = x - q * F;
-    if (r < 0) {
-        q -= 1;
-        r += F;
-    } else if (r >= F) {
-        q += 1;
-        r -= F;
-    }
-}
-
-// Traced position j -> lattice position.  With a band permutation, positions
-// are taken in bands of F consecutive indices (a thin latitude ring); inside
-// a band, rank r maps to offset r * G mod F (G the preceding Fibonacci
-// number), which walks the ring in azimuth order, so 64 consecutive positions
-// form a compact patch of directions.
-__device__ __forceinline__ int64_t lattice_position(const SbrArgs& a, int64_t j) {
-    if (a.perm_f > 0 && j < a.perm_full) {
-        int64_t b, r, q2, r2;
-        divmod(j, a.perm_f, a.perm_inv, b, r);
-        divmod(r * a.perm_g, a.perm_f, a.perm_inv, q2, r2);
-        return b * a.perm_f + r2;
-    }
-    return j;
-}
-
 __device__ __forceinline__ uint32_t mix32(uint64_t k) {
     k ^= k >> 33;
     k *= 0xff51afd7ed558ccdull;
@@ -358,7 +329,7 @@ void sbr_bounce(SbrArgs a, MatTable mats) {
         int best = -1;
         if (active) {
             if (FIRST) {
-                const int64_t pos = lattice_position(a, a.pos0 + item);
+                const int64_t pos = banded(a.perm, a.pos0 + item);
                 st.d = fib_dir(a.begin + pos * a.stride, a.num_rays);
                 st.o = d3{a.tx[0], a.tx[1], a.tx[2]};
                 if (MODE & kModeCoverage) {
