@@ -445,7 +445,12 @@ rt_status rt_paths_cfr_adjoint(rt_ctx* ctx, int32_t ntx, int32_t nrx, int32_t P,
  *   region [ny][nx] (dev, nullable: every cell) uint8;
  *   out [2*nm + 3] (dev) float64 = (G, dG/d eps_r_0, dG/d sigma_0, ...,
  *   dG/d yaw, dG/d pitch), cleared first.
- * RT_ERR_ARG for more than 4 materials.  Enqueued, not synchronous. */
+ * RT_ERR_ARG for more than 4 materials.  Enqueued, not synchronous.  Calls of a
+ * context on different streams need no ordering by the caller (the scratch they
+ * share is handed on by an event).  May be recorded into a graph, also on a new
+ * context: a recorded call uses no scratch, so its graph stays valid whatever
+ * the context does later, as long as the scene and the arrays exist, and may be
+ * replayed beside other calls and other graphs. */
 rt_status rt_coverage_grad(rt_ctx* ctx, rt_scene* scene, const rt_trace_params* p, const rt_device* tx,
                            const rt_device* rx_ant, const rt_grid* grid, const uint8_t* region,
                            const int32_t* hit_tri, const double* hit_t, double* out);

@@ -56,6 +56,28 @@ hipError_t ensure(DevBuf& b, size_t bytes) {
     return e;
 }
 
+// Device memory of calls that shared none before and may run on any stream:
+// `done` was recorded behind the last use, and the next one waits for it on its
+// own stream (work on the same stream is in order by itself).
+struct Workspace {
+    DevBuf buf;
+    hipEvent_t done = nullptr;
+    bool used = false;
+};
+
+hipError_t begin_use(Workspace& w, size_t bytes, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (!w.done) e = hipEventCreateWithFlags(&w.done, hipEventDisableTiming);
+    if (e == hipSuccess && w.used) e = hipStreamWaitEvent(s, w.done, 0);
+    return e == hipSuccess ? ensure(w.buf, bytes) : e;
+}
+
+hipError_t end_use(Workspace& w, hipStream_t s) {
+    const hipError_t e = hipEventRecord(w.done, s);
+    w.used = w.used || e == hipSuccess;
+    return e;
+}
+
 // Pinned host buffer of one transfer; `done` was recorded behind the last copy
 // from it.
 struct Staging {
@@ -134,7 +156,7 @@ struct rt_ctx {
     DevBuf rx;         // double [nrx][3], then Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
-    DevBuf cov;        // coverage gradient: queue of marked rays (made with the context, see rt_coverage_grad)
+    Workspace cov;     // coverage gradient: queue of marked rays
     DevBuf image;      // image method: queue of (receiver, candidate) pairs
     DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
     DevBuf scat;       // scattered paths: points, masks, prefixes, counts of one chunk
@@ -510,11 +532,6 @@ rt_status rt_create(rt_ctx** out, int32_t device) {
     c->scratch = scr;
     int cu = 0;
     if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cu > 0) c->num_cu = cu;
-    const hipError_t e = ensure(c->cov, rt::coverage_grad_scratch(rt::kCovCapturedChunk, c->num_cu));
-    if (e != hipSuccess) {
-        delete c;
-        return fail(e == hipErrorOutOfMemory ? RT_ERR_OOM : RT_ERR_DEVICE, hipGetErrorString(e));
-    }
     *out = c;
     return RT_OK;
 }
@@ -524,8 +541,13 @@ rt_status rt_destroy(rt_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->paths,
-                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->cov, &c->diff})
+                      &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->diff})
         if (b->p) (void)hipFree(b->p);
+    for (Workspace* w : {&c->cov}) {
+        if (w->done) (void)hipEventSynchronize(w->done);  // its last use may be on another stream
+        if (w->done) (void)hipEventDestroy(w->done);
+        if (w->buf.p) (void)hipFree(w->buf.p);
+    }
     for (Staging& b : c->stage) {
         if (b.done) (void)hipEventSynchronize(b.done);  // its copy may be on another stream than the last
         if (b.done) (void)hipEventDestroy(b.done);
@@ -1275,14 +1297,24 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.hit_tri = hit_tri;
     a.hit_t = hit_t;
     a.out = out;
-    // under capture nothing can be allocated: if the queue is not there for the
-    // whole call, the rays go through what the context was made with
-    int64_t chunk = std::min(a.count, rt::kCovChunk);
+    // A recorded call uses no memory of the context: a graph is replayed when
+    // later calls have grown the queue, beside them or beside another replay.  Nor
+    // does one for whose queue there is no room.
+    const int64_t chunk = std::min(a.count, rt::kCovChunk);
+    const rt::MatTable mats = make_mats(s, p->freq_hz);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     RT_HIP(hipStreamIsCapturing(c->stream, &cap));
-    if (cap == hipStreamCaptureStatusNone) RT_HIP(ensure(c->cov, rt::coverage_grad_scratch(chunk, c->num_cu)));
-    else if (c->cov.bytes < rt::coverage_grad_scratch(chunk, c->num_cu)) chunk = std::min(chunk, rt::kCovCapturedChunk);
-    RT_HIP(rt::launch_coverage_grad(a, make_mats(s, p->freq_hz), c->num_cu, chunk, c->cov.p, c->stream));
+    hipError_t e = hipErrorOutOfMemory;
+    if (cap == hipStreamCaptureStatusNone)
+        e = begin_use(c->cov, rt::coverage_grad_scratch(chunk, c->num_cu), c->stream);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();  // the allocation's, if any
+        RT_HIP(rt::launch_coverage_grad(a, mats, c->num_cu, chunk, nullptr, c->stream));
+        return RT_OK;
+    }
+    RT_HIP(e);
+    RT_HIP(rt::launch_coverage_grad(a, mats, c->num_cu, chunk, c->cov.buf.p, c->stream));
+    RT_HIP(end_use(c->cov, c->stream));
     return RT_OK;
 }
 

@@ -298,8 +298,9 @@ struct CovGradArgs {
     double* out;              // [2 nm + 3]: region sum, d/d(eps_r, sigma) per material, d/d yaw, d/d pitch
 };
 // Rays taken at a time, and the device memory their queue needs (all may be
-// marked).  kCovCapturedChunk rays always fit what a context holds.
-constexpr int64_t kCovChunk = int64_t(1) << 24, kCovCapturedChunk = int64_t(1) << 16;
+// marked: 8 bytes a ray, 134 MB at most; 10^7 rays in chunks of 2^22 take 288
+// instead of 259 us).  Without scratch, one kernel that needs none (and no chunks).
+constexpr int64_t kCovChunk = int64_t(1) << 24;
 size_t coverage_grad_scratch(int64_t rays, int num_cu);
 hipError_t launch_coverage_grad(const CovGradArgs& a, const MatTable& mats, int num_cu, int64_t chunk, void* scratch,
                                 hipStream_t s);
