@@ -131,7 +131,10 @@ typedef struct {
 rt_status rt_create(rt_ctx** out, int32_t device);
 rt_status rt_destroy(rt_ctx* ctx);
 /* Enqueue all later work of this context on `hip_stream` (a hipStream_t, or
- * NULL for the null stream).  The stream must outlive its use. */
+ * NULL for the null stream).  The stream must outlive its use.  The calls of a
+ * context share its scratch: after a change of stream the caller orders the new
+ * stream behind the work still pending on the old one, unless an entry point
+ * says that it needs no order. */
 rt_status rt_set_stream(rt_ctx* ctx, void* hip_stream);
 /* Block until all work enqueued by this context has finished. */
 rt_status rt_synchronize(rt_ctx* ctx);
@@ -425,7 +428,9 @@ rt_status rt_paths_cfr(rt_ctx* ctx, int32_t ntx, int32_t nrx, int32_t P, const f
  *   g [ntx][nrx][P][2] (dev) float64 = sum over the (tx, rx) entries of
  *   conj(G) exp(j 2 pi phase), zero for empty slots,
  * so that dL = Re(g da) (the input of rt_paths_coef_grad).  Arguments as
- * rt_paths_cfr. */
+ * rt_paths_cfr.  Its partial sums (64 MiB at most) are handed from stream to
+ * stream by an event, so calls with the same element offsets and velocities need
+ * no order; where there is no room for them, a slower kernel does without. */
 rt_status rt_paths_cfr_adjoint(rt_ctx* ctx, int32_t ntx, int32_t nrx, int32_t P, const float* a, const float* tau,
                                const float* aod, const float* aoa, const int32_t* depth, double freq_hz, int32_t K,
                                double spacing_hz, int32_t nt_el, const double* tx_el, int32_t nr_el,

@@ -156,6 +156,7 @@ struct rt_ctx {
     DevBuf rx;         // double [nrx][3], then Antenna [nrx]
     DevBuf paths;      // unsorted path records
     DevBuf chan;       // channel responses: element offsets and velocities
+    Workspace adj;     // their adjoint: partial sums
     Workspace cov;     // coverage gradient: queue of marked rays
     DevBuf image;      // image method: queue of (receiver, candidate) pairs
     DevBuf diff;       // diffraction: queues of (receiver, wedge) pairs
@@ -543,7 +544,7 @@ rt_status rt_destroy(rt_ctx* c) {
     for (DevBuf* b : {&c->queue[0], &c->queue[1], &c->counters, &c->table, &c->cands, &c->rx, &c->paths,
                       &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->diff})
         if (b->p) (void)hipFree(b->p);
-    for (Workspace* w : {&c->cov}) {
+    for (Workspace* w : {&c->adj, &c->cov}) {
         if (w->done) (void)hipEventSynchronize(w->done);  // its last use may be on another stream
         if (w->done) (void)hipEventDestroy(w->done);
         if (w->buf.p) (void)hipFree(w->buf.p);
@@ -1322,13 +1323,12 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
 
 namespace {
 // Validates the channel-response arguments and stages the small host arrays
-// (element offsets, velocities) in the context's device buffer, followed by the
-// adjoint's scratch when `scratch` is given.
+// (element offsets, velocities) in the context's device buffer.
 rt_status cfr_setup(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, const float* a, const float* tau,
                     const float* aod, const float* aoa, const int32_t* depth, double freq_hz, int32_t K,
                     double spacing_hz, int32_t nt_el, const double* tx_el, int32_t nr_el, const double* rx_el,
                     const double* v_tx, const double* v_rx, int32_t T, double fs, const void* out_a,
-                    const void* out_b, rt::CfrArgs& cf, void** scratch = nullptr) {
+                    const void* out_b, rt::CfrArgs& cf) {
     if (!c || !a || !tau || !aod || !aoa || !depth) return fail(RT_ERR_ARG, "NULL argument");
     if (ntx < 1 || nrx < 1 || P < 1) return fail(RT_ERR_ARG, "ntx, nrx and P must be >= 1");
     if (!(freq_hz > 0) || !std::isfinite(freq_hz)) return fail(RT_ERR_ARG, "frequency must be positive");
@@ -1353,20 +1353,14 @@ rt_status cfr_setup(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, const float*
         if (!std::isfinite(v)) return fail(RT_ERR_ARG, "element offsets and velocities must be finite");
     if (!out_a || !out_b) return fail(RT_ERR_ARG, "NULL argument");
     RT_HIP(hipSetDevice(c->device));
-    cf = rt::CfrArgs{};
-    cf.npairs = (int64_t)ntx * nrx;
-    cf.P = P;
-    cf.K = K;
-    cf.T = T;
-    cf.nt_el = nt_el;
-    cf.nr_el = nr_el;
-    const size_t head = (h.size() * sizeof(double) + 15) / 16 * 16;
-    RT_HIP(ensure(c->chan, head + (scratch ? rt::cfr_adjoint_scratch(cf) : 0)));
-    if (scratch) *scratch = (char*)c->chan.p + head;
+    RT_HIP(ensure(c->chan, h.size() * sizeof(double)));
     const rt_status st = upload(c, c->chan.p, h.data(), h.size() * sizeof(double));
     if (st != RT_OK) return st;
     const double* d = (const double*)c->chan.p;
+    cf = rt::CfrArgs{};
+    cf.npairs = (int64_t)ntx * nrx;
     cf.nrx = nrx;
+    cf.P = P;
     cf.a = a;
     cf.tau = tau;
     cf.aod = aod;
@@ -1376,6 +1370,10 @@ rt_status cfr_setup(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, const float*
     cf.lambda = kC0 / freq_hz;
     cf.spacing = spacing_hz;
     cf.fs = T > 1 ? fs : 1.0;
+    cf.K = K;
+    cf.T = T;
+    cf.nt_el = nt_el;
+    cf.nr_el = nr_el;
     cf.tx_el = d;
     cf.rx_el = d + 3 * nt_el;
     cf.v_tx = d + 3 * (nt_el + nr_el);
@@ -1406,11 +1404,16 @@ rt_status rt_paths_cfr_adjoint(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, c
                                const double* rx_el, const double* v_tx, const double* v_rx, int32_t T, double fs,
                                const float* G, double* g) {
     rt::CfrArgs cf;
-    void* scratch = nullptr;
     rt_status st = cfr_setup(c, ntx, nrx, P, a, tau, aod, aoa, depth, freq_hz, K, spacing_hz, nt_el, tx_el, nr_el,
-                             rx_el, v_tx, v_rx, T, fs, G, g, cf, &scratch);
+                             rx_el, v_tx, v_rx, T, fs, G, g, cf);
     if (st != RT_OK) return st;
+    const size_t bytes = rt::cfr_adjoint_scratch(cf);
+    hipError_t e = bytes ? begin_use(c->adj, bytes, c->stream) : hipSuccess;
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+    else RT_HIP(e);
+    void* scratch = bytes && e == hipSuccess ? c->adj.buf.p : nullptr;
     RT_HIP(rt::launch_cfr_adjoint(cf, G, g, scratch, c->stream));
+    if (scratch) RT_HIP(end_use(c->adj, c->stream));
     return RT_OK;
 }
 

@@ -299,11 +299,16 @@ __global__ __launch_bounds__(kCfrBlock) void cfr_adjoint_kernel(CfrArgs c, const
 // outputs: 16 waves on the whole chip, a sine and five more for the unit
 // vectors per output.
 constexpr int kAdjSlots = 64, kAdjRows = 8;
+struct AdjPlan {
+    int64_t rows, rows_per, row_parts, k_tiles, slot_tiles;
+    int64_t parts;        // row_parts * k_tiles
+    int64_t tile0, tiles;  // slot tiles (link * slot_tiles + tile of the link) of this launch
+    int km;
+};
 template <int KM>
 __global__ __launch_bounds__(kCfrBlock) void cfr_adjoint_tile_kernel(CfrArgs c, const float* __restrict__ G,
-                                                                     double* __restrict__ part, int64_t rows,
-                                                                     int64_t rows_per, int64_t row_parts,
-                                                                     int64_t k_tiles, int64_t slot_tiles) {
+                                                                     double* __restrict__ g, double* __restrict__ part,
+                                                                     AdjPlan a) {
     constexpr int KT = 16 * KM, PM = kAdjSlots / 16;
     __shared__ PathTerm terms[kAdjSlots];
     __shared__ int slots[kAdjSlots];
@@ -311,14 +316,14 @@ __global__ __launch_bounds__(kCfrBlock) void cfr_adjoint_tile_kernel(CfrArgs c, 
     __shared__ cd Lf[kAdjRows][kAdjSlots];
     __shared__ cd Gf[kAdjRows][KT];
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int64_t nslots = c.npairs * c.P;
-    for (int64_t b = blockIdx.x; b < c.npairs * slot_tiles * row_parts * k_tiles; b += gridDim.x) {
-        const int64_t part_at = b % (row_parts * k_tiles), rp = part_at / k_tiles;
-        const int64_t s0 = b / (row_parts * k_tiles) % slot_tiles * kAdjSlots;
-        const int64_t pair = b / (row_parts * k_tiles) / slot_tiles;
-        const int k0 = (int)(part_at % k_tiles) * KT;
-        double2u* out = reinterpret_cast<double2u*>(part) + part_at * nslots + pair * c.P;
-        if (tid < kAdjSlots && s0 + tid < c.P && c.depth[pair * c.P + s0 + tid] < 0) out[s0 + tid] = double2u{0.0, 0.0};
+    const int64_t rows = a.rows;
+    for (int64_t b = blockIdx.x; b < a.tiles * a.parts; b += gridDim.x) {
+        const int64_t part_at = b % a.parts, rp = part_at / a.k_tiles, t = b / a.parts;
+        const int64_t s0 = (a.tile0 + t) % a.slot_tiles * kAdjSlots, pair = (a.tile0 + t) / a.slot_tiles;
+        const int k0 = (int)(part_at % a.k_tiles) * KT;
+        double2u* out = a.parts == 1 ? reinterpret_cast<double2u*>(g) + pair * c.P + s0
+                                     : reinterpret_cast<double2u*>(part) + (part_at * a.tiles + t) * kAdjSlots;
+        if (tid < kAdjSlots && s0 + tid < c.P && c.depth[pair * c.P + s0 + tid] < 0) out[tid] = double2u{0.0, 0.0};
         const int n = gather_terms<kAdjSlots>(c, pair, s0, terms, slots, wave_n);
         if (n == 0) continue;
         cd acc[PM][KM];
@@ -327,8 +332,8 @@ __global__ __launch_bounds__(kCfrBlock) void cfr_adjoint_tile_kernel(CfrArgs c, 
 #pragma unroll
             for (int u = 0; u < KM; ++u) acc[m][u] = cd{0.0, 0.0};
         const float2u* Gp = reinterpret_cast<const float2u*>(G) + pair * rows * c.K;
-        const int64_t r_end = min(rows, (rp + 1) * rows_per);
-        for (int64_t r0 = rp * rows_per; r0 < r_end; r0 += kAdjRows) {
+        const int64_t r_end = min(rows, (rp + 1) * a.rows_per);
+        for (int64_t r0 = rp * a.rows_per; r0 < r_end; r0 += kAdjRows) {
             const int nr = (int)min((int64_t)kAdjRows, r_end - r0);
             for (int e = tid; e < nr * KT; e += kCfrBlock) {
                 const int r = e / KT, k = e % KT;
@@ -383,18 +388,20 @@ __global__ __launch_bounds__(kCfrBlock) void cfr_adjoint_tile_kernel(CfrArgs c, 
                 sum.re += __shfl_xor(sum.re, off);
                 sum.im += __shfl_xor(sum.im, off);
             }
-            if (tx == 0 && p < n) out[slots[p]] = double2u{sum.re, sum.im};
+            if (tx == 0 && p < n) out[slots[p] - s0] = double2u{sum.re, sum.im};
         }
         __syncthreads();
     }
 }
 
-__global__ void cfr_parts_kernel(const double2u* __restrict__ part, int64_t parts, int64_t n,
-                                 double2u* __restrict__ g) {
+__global__ void cfr_parts_kernel(const double2u* __restrict__ part, AdjPlan a, int64_t P, double2u* __restrict__ g) {
+    const int64_t n = a.tiles * kAdjSlots;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t tile = a.tile0 + i / kAdjSlots, slot = tile % a.slot_tiles * kAdjSlots + i % kAdjSlots;
+        if (slot >= P) continue;
         double2u s = part[i];
-        for (int64_t p = 1; p < parts; ++p) s += part[p * n + i];
-        g[i] = s;
+        for (int64_t p = 1; p < a.parts; ++p) s += part[p * n + i];
+        g[tile / a.slot_tiles * P + slot] = s;
     }
 }
 
@@ -409,13 +416,11 @@ bool use_tiles(const CfrArgs& c, int64_t rows) {
 }
 
 // Row ranges of the adjoint: enough blocks to fill the chip (2048), at least
-// 32 rows each.
-struct AdjPlan {
-    int64_t rows, rows_per, row_parts, k_tiles, slot_tiles;
-    int km;
-};
+// 32 rows each.  Where one part per tile does not do, as many tiles at a time as
+// their partial sums fit kAdjScratch (one at least).
+constexpr int64_t kAdjScratch = int64_t(64) << 20, kAdjTileBytes = kAdjSlots * (int64_t)sizeof(double2u);
 AdjPlan adjoint_plan(const CfrArgs& c) {
-    AdjPlan p;
+    AdjPlan p{};
     p.rows = (int64_t)c.T * c.nr_el * c.nt_el;
     p.km = c.K > 64 ? 8 : c.K > 32 ? 4 : c.K > 16 ? 2 : 1;
     p.k_tiles = ceil_div(c.K, 16 * p.km);
@@ -424,6 +429,9 @@ AdjPlan adjoint_plan(const CfrArgs& c) {
     const int64_t want = std::max<int64_t>(1, std::min<int64_t>(ceil_div(2048, blocks), p.rows / 32));
     p.rows_per = ceil_div(ceil_div(p.rows, want), kAdjRows) * kAdjRows;
     p.row_parts = ceil_div(p.rows, p.rows_per);
+    p.parts = p.row_parts * p.k_tiles;
+    p.tiles = c.npairs * p.slot_tiles;
+    if (p.parts > 1) p.tiles = std::min(p.tiles, std::max<int64_t>(1, kAdjScratch / (p.parts * kAdjTileBytes)));
     return p;
 }
 
@@ -433,8 +441,7 @@ dim3 grid_of(int64_t blocks) { return dim3((unsigned)std::min<int64_t>(blocks, 1
 
 size_t cfr_adjoint_scratch(const CfrArgs& c) {
     const AdjPlan p = adjoint_plan(c);
-    if (!use_tiles(c, p.rows) || p.row_parts * p.k_tiles == 1) return 0;
-    return (size_t)(p.row_parts * p.k_tiles * c.npairs * c.P) * sizeof(double2u);
+    return use_tiles(c, p.rows) && p.parts > 1 ? (size_t)(p.tiles * p.parts * kAdjTileBytes) : 0;
 }
 
 hipError_t launch_cfr(const CfrArgs& c, hipStream_t s) {
@@ -459,21 +466,22 @@ hipError_t launch_cfr(const CfrArgs& c, hipStream_t s) {
 hipError_t launch_cfr_adjoint(const CfrArgs& c, const float* G, double* g, void* scratch, hipStream_t s) {
     const int64_t n = c.npairs * c.P;
     if (n <= 0) return hipSuccess;
-    const AdjPlan p = adjoint_plan(c);
-    if (use_tiles(c, p.rows)) {
-        const int64_t parts = p.row_parts * p.k_tiles;
-        double* part = parts == 1 ? g : (double*)scratch;
+    AdjPlan p = adjoint_plan(c);
+    if (use_tiles(c, p.rows) && (p.parts == 1 || scratch)) {
+        const int64_t all = c.npairs * p.slot_tiles, step = p.tiles;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid_of(c.npairs * p.slot_tiles * parts), dim3(kCfrBlock), 0, s, c, G, part,
-                               p.rows, p.rows_per, p.row_parts, p.k_tiles, p.slot_tiles);
+            hipLaunchKernelGGL(kernel, grid_of(p.tiles * p.parts), dim3(kCfrBlock), 0, s, c, G, g, (double*)scratch, p);
         };
-        if (p.km == 8) go(cfr_adjoint_tile_kernel<8>);
-        else if (p.km == 4) go(cfr_adjoint_tile_kernel<4>);
-        else if (p.km == 2) go(cfr_adjoint_tile_kernel<2>);
-        else go(cfr_adjoint_tile_kernel<1>);
-        if (parts > 1)
-            hipLaunchKernelGGL(cfr_parts_kernel, grid_of(ceil_div(n, 256)), dim3(256), 0, s,
-                               (const double2u*)scratch, parts, n, (double2u*)g);
+        for (p.tile0 = 0; p.tile0 < all; p.tile0 += step) {
+            p.tiles = std::min(step, all - p.tile0);
+            if (p.km == 8) go(cfr_adjoint_tile_kernel<8>);
+            else if (p.km == 4) go(cfr_adjoint_tile_kernel<4>);
+            else if (p.km == 2) go(cfr_adjoint_tile_kernel<2>);
+            else go(cfr_adjoint_tile_kernel<1>);
+            if (p.parts > 1)
+                hipLaunchKernelGGL(cfr_parts_kernel, grid_of(ceil_div(p.tiles * kAdjSlots, 256)), dim3(256), 0, s,
+                                   (const double2u*)scratch, p, (int64_t)c.P, (double2u*)g);
+        }
     } else {
         const int64_t blocks = ceil_div(c.P, kCfrBlock);
         hipLaunchKernelGGL(cfr_adjoint_kernel, grid_of(c.npairs * blocks), dim3(kCfrBlock), 0, s, c, G, g,

@@ -270,8 +270,8 @@ struct CfrArgs {
     int64_t total;            // entries of H
 };
 hipError_t launch_cfr(const CfrArgs& c, hipStream_t s);
-// scratch: cfr_adjoint_scratch(c) bytes of partial sums, 16-byte aligned (may
-// be null when that is 0).
+// scratch: cfr_adjoint_scratch(c) bytes of partial sums, 16-byte aligned; without,
+// a kernel that needs none (a sine per output and path).
 size_t cfr_adjoint_scratch(const CfrArgs& c);
 hipError_t launch_cfr_adjoint(const CfrArgs& c, const float* G, double* g, void* scratch, hipStream_t s);
 
