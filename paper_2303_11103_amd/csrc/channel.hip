@@ -415,6 +415,21 @@ bool use_tiles(const CfrArgs& c, int64_t rows) {
     return rows >= kTileMinRows && rows * c.K >= kTileMinOut;
 }
 
+// Whether the responses of all links take tiles.  A tile is 2048 outputs or more
+// and its block works through the paths alone: with 64 paths a link at least
+// 115 us for up to 16 subcarriers, 65 for up to 32, 50 beyond, however few tiles
+// there are, while a sine per output fills the chip and takes 23 us for up to
+// 65,000 outputs, 54 for 230,000 and 180 for 10^6.  The lines lie where the two
+// meet (one and 16 links, 64 paths, sines / tiles): 16 subcarriers 96 / 116 us at
+// 460,000 outputs, 128 / 116 at 690,000; 32 subcarriers 47 / 58 at 260,000, 97 /
+// 78 at 520,000; 64 and 128 subcarriers 29 / 47 and 29 / 42 at 130,000, 97 / 58
+// and 99 / 51 at 520,000.  Below five subcarriers a tile's 16 columns are mostly
+// empty (four, 10^6 outputs: 180 / 224 us).
+bool responses_take_tiles(const CfrArgs& c, int64_t rows) {
+    if (!use_tiles(c, rows) || c.K < 5) return false;
+    return c.total >= (c.K > 32 ? int64_t(1) << 18 : c.K > 16 ? int64_t(3) << 17 : int64_t(5) << 17);
+}
+
 // Row ranges of the adjoint: enough blocks to fill the chip (2048), at least
 // 32 rows each.  Where one part per tile does not do, as many tiles at a time as
 // their partial sums fit kAdjScratch (one at least).
@@ -447,7 +462,7 @@ size_t cfr_adjoint_scratch(const CfrArgs& c) {
 hipError_t launch_cfr(const CfrArgs& c, hipStream_t s) {
     if (c.total <= 0) return hipSuccess;
     const int64_t rows = (int64_t)c.T * c.nr_el * c.nt_el;
-    if (use_tiles(c, rows)) {
+    if (responses_take_tiles(c, rows)) {
         auto go = [&](auto kernel, int km, int rm) {
             const int64_t rt = ceil_div(rows, 16 * rm), kt = ceil_div(c.K, 16 * km);
             hipLaunchKernelGGL(kernel, grid_of(c.npairs * rt * kt), dim3(kCfrBlock), 0, s, c, rows, rt, kt);
