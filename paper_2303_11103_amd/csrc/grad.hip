@@ -5,7 +5,7 @@
 //
 // Input: the paths of one transmitter as face sequences (the checkpoint kept
 // by the forward pass).  A few lanes per (rx, path) recompute the path in
-// fp64 and differentiates its power |a|^2:
+// fp64 and differentiate its power |a|^2:
 //   * transmitter position (x, y, z) and orientation (yaw, pitch) with
 //     forward-mode dual numbers, a tangent per lane, through the images,
 //     reflection points, directions, length, Fresnel coefficients, field
@@ -18,7 +18,8 @@
 //     dr_par/deta = cos (eta - 2 sin^2) / (s (eta cos + s)^2),
 //     deta/deps_r = 1, deta/dsigma = -j / (eps0 w).
 // Power derivatives dP/dtheta = 2 Re(conj(a) da/dtheta) are contracted with
-// the upstream adjoint dL/dP_r and accumulated with fp64 atomics.
+// the upstream adjoint dL/dP_r and summed per block in LDS, then with fp64
+// atomics.
 #include <algorithm>
 
 #include "traverse.h"
@@ -250,12 +251,16 @@ __device__ __forceinline__ cd cdotv(const cd* g, d3 v) {
 // kPathLanes lanes per path slot, one transmitter parameter each: most slots
 // are empty and the launch lasts as long as one path, so a path is spread over
 // lanes instead of carrying five tangents through one (6.6 KB of private arrays
-// per lane).  256 receivers x 128 slots, depth 3: 93 -> 36 us.
-constexpr int kPathLanes = 8;
-__global__ void power_grad_kernel(GradArgs g, MatTable mats) {
-    const int64_t item = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kPathLanes;
-    const int theta = threadIdx.x % kPathLanes;
-    if (item >= (int64_t)g.nrx * g.P || theta >= kTheta) return;
+// per lane).  The sums go to LDS first: with an atomic on a few addresses of
+// memory per path and parameter, those bound full lists, the more so as lanes of
+// different parameters cannot be summed within an instruction.  Depth 3, 256
+// receivers x 128 slots, one in fifty full: five tangents a lane 93 us, one 36;
+// 4096 receivers x 64 full slots: 7.6 and 10.3 ms, with the sums in LDS 0.86.
+constexpr int kPathLanes = 8, kGradBlock = 128;
+// Adds the derivatives of path slot `item` to out ([2 nm + 5], as g.grad): the
+// transmitter parameter theta, and with theta 0 the materials.
+__device__ __forceinline__ void power_grad_path(const GradArgs& g, const MatTable& mats, int64_t item, int theta,
+                                                double* out) {
     const int r = (int)(item / g.P);
     const int K = g.depth[item];
     if (K < 0 || K > g.fd || K > kMaxK) return;  // empty slot (or not a path of this depth range)
@@ -370,7 +375,6 @@ __global__ void power_grad_kernel(GradArgs g, MatTable mats) {
     const C a{pr.re * amp, pr.im * amp};
     const double gre = g.coef_adj ? g.coef_adj[2 * item] : 2.0 * w_up * a.re.v;
     const double gim = g.coef_adj ? g.coef_adj[2 * item + 1] : -2.0 * w_up * a.im.v;
-    double* out = g.grad;
     const int base = 2 * g.nm;
     atomicAdd(out + base + theta, gre * a.re.d[0] - gim * a.im.d[0]);
     if (theta != 0) return;
@@ -397,6 +401,19 @@ __global__ void power_grad_kernel(GradArgs g, MatTable mats) {
         gv[1] = cadd(cmulr(p1, e1.y), cmulr(p2, e2.y));
         gv[2] = cadd(cmulr(p1, e1.z), cmulr(p2, e2.z));
     }
+}
+
+__global__ __launch_bounds__(kGradBlock) void power_grad_kernel(GradArgs g, MatTable mats) {
+    __shared__ double sum[2 * kMaxMaterials + kTheta];
+    const int outs = 2 * g.nm + kTheta;
+    for (int i = threadIdx.x; i < outs; i += kGradBlock) sum[i] = 0.0;
+    __syncthreads();
+    const int64_t item = ((int64_t)blockIdx.x * kGradBlock + threadIdx.x) / kPathLanes;
+    const int theta = threadIdx.x % kPathLanes;
+    if (item < (int64_t)g.nrx * g.P && theta < kTheta) power_grad_path(g, mats, item, theta, sum);
+    __syncthreads();
+    for (int i = threadIdx.x; i < outs; i += kGradBlock)
+        if (sum[i] != 0.0) atomicAdd(g.grad + i, sum[i]);
 }
 
 // ------------------------------------------------------------------ coverage
@@ -755,9 +772,9 @@ void coverage_grad_direct_kernel(CovGradArgs g, MatTable mats) {
 
 hipError_t launch_power_grad(const GradArgs& a, const MatTable& mats, hipStream_t s) {
     const int64_t n = (int64_t)a.nrx * a.P * kPathLanes;
-    const int64_t blocks = (n + 127) / 128;
+    const int64_t blocks = (n + kGradBlock - 1) / kGradBlock;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(power_grad_kernel, dim3((unsigned)blocks), dim3(128), 0, s, a, mats);
+    hipLaunchKernelGGL(power_grad_kernel, dim3((unsigned)blocks), dim3(kGradBlock), 0, s, a, mats);
     return hipGetLastError();
 }
 
