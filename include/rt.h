@@ -131,10 +131,10 @@ typedef struct {
 rt_status rt_create(rt_ctx** out, int32_t device);
 rt_status rt_destroy(rt_ctx* ctx);
 /* Enqueue all later work of this context on `hip_stream` (a hipStream_t, or
- * NULL for the null stream).  The stream must outlive its use.  The calls of a
- * context share its scratch: after a change of stream the caller orders the new
- * stream behind the work still pending on the old one, unless an entry point
- * says that it needs no order. */
+ * NULL for the null stream).  The stream must outlive the work that is
+ * enqueued on it.  The calls of a context share its scratch: after a change of
+ * stream the caller orders the new stream behind the work still pending on the
+ * old one, unless an entry point says that it needs no order. */
 rt_status rt_set_stream(rt_ctx* ctx, void* hip_stream);
 /* Block until all work enqueued by this context has finished. */
 rt_status rt_synchronize(rt_ctx* ctx);

@@ -56,26 +56,40 @@ hipError_t ensure(DevBuf& b, size_t bytes) {
     return e;
 }
 
-// Device memory of calls that shared none before and may run on any stream:
-// `done` was recorded behind the last use, and the next one waits for it on its
-// own stream (work on the same stream is in order by itself).
+// Device memory of calls that shared none before and may run on any stream.
+// Work on one stream is in order by itself; on the first change of stream the
+// new one waits for the old one, and from then on `done` is recorded behind each
+// use (3 to 5 us of the stream, which a program with one stream does not pay)
+// and waited for before the next.
 struct Workspace {
     DevBuf buf;
     hipEvent_t done = nullptr;
-    bool used = false;
+    hipStream_t last = nullptr;  // stream of the last use
+    bool used = false, shared = false;
 };
 
-hipError_t begin_use(Workspace& w, size_t bytes, hipStream_t s) {
+// False when the memory cannot be had now (no room, or the stream of the last use
+// is being captured or gone): the caller does without.
+bool begin_use(Workspace& w, size_t bytes, hipStream_t s) {
     hipError_t e = hipSuccess;
-    if (!w.done) e = hipEventCreateWithFlags(&w.done, hipEventDisableTiming);
-    if (e == hipSuccess && w.used) e = hipStreamWaitEvent(s, w.done, 0);
-    return e == hipSuccess ? ensure(w.buf, bytes) : e;
+    if (w.used && !w.shared && s != w.last) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        e = hipStreamIsCapturing(w.last, &cap);
+        if (e == hipSuccess && cap != hipStreamCaptureStatusNone) return false;
+        if (e == hipSuccess && !w.done) e = hipEventCreateWithFlags(&w.done, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(w.done, w.last);
+        w.shared = e == hipSuccess;
+    }
+    if (e == hipSuccess && w.shared) e = hipStreamWaitEvent(s, w.done, 0);
+    if (e == hipSuccess) e = ensure(w.buf, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
 }
 
 hipError_t end_use(Workspace& w, hipStream_t s) {
-    const hipError_t e = hipEventRecord(w.done, s);
-    w.used = w.used || e == hipSuccess;
-    return e;
+    w.last = s;
+    w.used = true;
+    return w.shared ? hipEventRecord(w.done, s) : hipSuccess;
 }
 
 // Pinned host buffer of one transfer; `done` was recorded behind the last copy
@@ -545,7 +559,7 @@ rt_status rt_destroy(rt_ctx* c) {
                       &c->pairs, &c->pair_rx, &c->rgrid, &c->chan, &c->scat, &c->image, &c->diff})
         if (b->p) (void)hipFree(b->p);
     for (Workspace* w : {&c->adj, &c->cov}) {
-        if (w->done) (void)hipEventSynchronize(w->done);  // its last use may be on another stream
+        if (w->shared) (void)hipEventSynchronize(w->done);  // its last use may be on another stream
         if (w->done) (void)hipEventDestroy(w->done);
         if (w->buf.p) (void)hipFree(w->buf.p);
     }
@@ -1299,23 +1313,15 @@ rt_status rt_coverage_grad(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
     a.hit_t = hit_t;
     a.out = out;
     // A recorded call uses no memory of the context: a graph is replayed when
-    // later calls have grown the queue, beside them or beside another replay.  Nor
-    // does one for whose queue there is no room.
+    // later calls have grown the queue, beside them or beside another replay.
     const int64_t chunk = std::min(a.count, rt::kCovChunk);
     const rt::MatTable mats = make_mats(s, p->freq_hz);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     RT_HIP(hipStreamIsCapturing(c->stream, &cap));
-    hipError_t e = hipErrorOutOfMemory;
-    if (cap == hipStreamCaptureStatusNone)
-        e = begin_use(c->cov, rt::coverage_grad_scratch(chunk, c->num_cu), c->stream);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();  // the allocation's, if any
-        RT_HIP(rt::launch_coverage_grad(a, mats, c->num_cu, chunk, nullptr, c->stream));
-        return RT_OK;
-    }
-    RT_HIP(e);
-    RT_HIP(rt::launch_coverage_grad(a, mats, c->num_cu, chunk, c->cov.buf.p, c->stream));
-    RT_HIP(end_use(c->cov, c->stream));
+    const bool queued = cap == hipStreamCaptureStatusNone &&
+                        begin_use(c->cov, rt::coverage_grad_scratch(chunk, c->num_cu), c->stream);
+    RT_HIP(rt::launch_coverage_grad(a, mats, c->num_cu, chunk, queued ? c->cov.buf.p : nullptr, c->stream));
+    if (queued) RT_HIP(end_use(c->cov, c->stream));
     return RT_OK;
 }
 
@@ -1408,12 +1414,9 @@ rt_status rt_paths_cfr_adjoint(rt_ctx* c, int32_t ntx, int32_t nrx, int32_t P, c
                              rx_el, v_tx, v_rx, T, fs, G, g, cf);
     if (st != RT_OK) return st;
     const size_t bytes = rt::cfr_adjoint_scratch(cf);
-    hipError_t e = bytes ? begin_use(c->adj, bytes, c->stream) : hipSuccess;
-    if (e == hipErrorOutOfMemory) (void)hipGetLastError();
-    else RT_HIP(e);
-    void* scratch = bytes && e == hipSuccess ? c->adj.buf.p : nullptr;
-    RT_HIP(rt::launch_cfr_adjoint(cf, G, g, scratch, c->stream));
-    if (scratch) RT_HIP(end_use(c->adj, c->stream));
+    const bool sums = bytes && begin_use(c->adj, bytes, c->stream);
+    RT_HIP(rt::launch_cfr_adjoint(cf, G, g, sums ? c->adj.buf.p : nullptr, c->stream));
+    if (sums) RT_HIP(end_use(c->adj, c->stream));
     return RT_OK;
 }
 

@@ -57,7 +57,7 @@ def test_recorded_gradient_equals_the_eager_one_after_larger_calls(rays, nm, cit
 def test_gradients_on_two_streams_do_not_mix():
     m = lib()
     c = m.Context(0)
-    cases = [_case(m, c, rays, nm) for rays, nm in ((700_001, 2), (90_001, 3))]
+    cases = [_case(m, c, rays, nm) for rays, nm in ((1_700_001, 2), (600_001, 3))]
     want = [m.coverage_grad(c, s, p, tx, GRID, *rec).cpu().numpy() for s, p, tx, rec in cases]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     torch.cuda.synchronize()
