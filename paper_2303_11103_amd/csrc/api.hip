@@ -1082,7 +1082,16 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
     const size_t rec_bytes = per * (2 + 8 + 1 + 2 + 2) * sizeof(float) + per * 3 * sizeof(int32_t) +
                              (size_t)nrx * sizeof(uint32_t);
     RT_HIP(ensure(c->paths, rec_bytes));
-    RT_HIP(ensure(c->diff, rt::diffraction_scratch(nrx, s->dev.num_wedges)));
+    // fewer receivers at a time where there is no room for the queues of all
+    int64_t most = rt::kDiffQueuePairs;
+    rt::DiffPlan plan = rt::diffraction_plan(nrx, s->dev.num_wedges, most);
+    hipError_t e;
+    while ((e = ensure(c->diff, rt::diffraction_scratch(plan))) == hipErrorOutOfMemory && plan.chunk > 1) {
+        (void)hipGetLastError();
+        most = std::min(most, plan.chunk * s->dev.num_wedges) / 2;
+        plan = rt::diffraction_plan(nrx, s->dev.num_wedges, most);
+    }
+    RT_HIP(e);
     if ((st = stage_receivers(c, rx, nrx)) != RT_OK) return st;
     char* base = (char*)c->paths.p;
     rt::PathArgs pa{};
@@ -1108,14 +1117,22 @@ rt_status rt_compute_diffraction(rt_ctx* c, rt_scene* s, double freq_hz, const r
     for (int t = 0; t < ntx; ++t) {
         for (int i = 0; i < 3; ++i) pa.tx[i] = tx[t].pos[i];
         pa.tx_ant = make_antenna(tx + t);
-        const void* back = nullptr;
-        RT_HIP(hipMemsetAsync(pa.counts, 0, (size_t)nrx * sizeof(uint32_t), c->stream));
-        RT_HIP(rt::launch_diffraction_paths(pa, mats, c->diff.p, c->stream));
         const size_t off = (size_t)t * per;
-        RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
-                                     depth_sorted, wedge + off, num_paths + (size_t)t * nrx, c->stream));
-        if ((st = read_back(c, num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t), &back)) != RT_OK) return st;
-        for (int i = 0; i < nrx; ++i) worst = std::max(worst, ((const int32_t*)back)[i]);
+        const int32_t* found = nullptr;
+        bool over = true;
+        while (over) {
+            const void* back = nullptr;
+            RT_HIP(hipMemsetAsync(pa.counts, 0, (size_t)nrx * sizeof(uint32_t), c->stream));
+            RT_HIP(rt::launch_diffraction_paths(pa, mats, plan, c->diff.p, c->stream));
+            RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
+                                         depth_sorted, wedge + off, num_paths + (size_t)t * nrx, c->stream));
+            if ((st = read_back(c, num_paths + (size_t)t * nrx, (size_t)nrx * sizeof(int32_t), &back)) != RT_OK)
+                return st;
+            found = (const int32_t*)back;
+            over = std::any_of(found, found + nrx, [](int32_t n) { return n < 0; });
+            if (over) plan = rt::diffraction_sure(plan, s->dev.num_wedges);
+        }
+        for (int i = 0; i < nrx; ++i) worst = std::max(worst, found[i]);
     }
     if (worst > P)
         return fail(RT_ERR_CAPACITY, "a receiver has " + std::to_string(worst) +

@@ -209,7 +209,7 @@ __device__ void diffracted_path(const MatTable& mats, double lambda, d3 S, const
 constexpr int kDiffRx = 64;
 __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, int32_t r0, int32_t r1,
                                                                     int32_t wedge_tiles, uint32_t* __restrict__ queue,
-                                                                    uint32_t* __restrict__ count) {
+                                                                    uint32_t room, uint32_t* __restrict__ count) {
     __shared__ double rx[kDiffRx][3];
     __shared__ uint32_t wave_n[kBlock / 64];
     __shared__ uint32_t start;
@@ -272,7 +272,8 @@ __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, 
     while (keep) {
         const int r = __ffsll((long long)keep) - 1;
         keep &= keep - 1;
-        queue[at++] = (uint32_t)(rb - r0 + r) * (uint32_t)a.sc.num_wedges + (uint32_t)wi;
+        if (at < room) queue[at] = (uint32_t)(rb - r0 + r) * (uint32_t)a.sc.num_wedges + (uint32_t)wi;
+        ++at;
     }
 }
 
@@ -295,9 +296,9 @@ __device__ __forceinline__ Wedge load_pair(const PathArgs& a, int32_t r0, uint32
 constexpr int kLegBlock = 512, kLegNodes = 64;
 template <bool OVF>
 __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a, int32_t r0,
-                                                                     const uint32_t* __restrict__ queue,
+                                                                     const uint32_t* __restrict__ queue, uint32_t room,
                                                                      const uint32_t* __restrict__ count,
-                                                                     uint32_t* __restrict__ out,
+                                                                     uint32_t* __restrict__ out, uint32_t out_room,
                                                                      uint32_t* __restrict__ out_count) {
     __shared__ int32_t stack[kStack][kLegBlock];
     __shared__ Node lds_nodes[kLegNodes];
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
     const int lane = threadIdx.x & 63;
     uint32_t* mine = held[threadIdx.x >> 6];
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
-    const int64_t n = (int64_t)*count;
+    const int64_t n = (int64_t)min(*count, room);
     const int64_t nwaves = (int64_t)gridDim.x * (kLegBlock / 64);
     int have = 0;  // survivors of the first leg in `mine` (the same in every lane)
     auto second_leg = [&](int take) {
@@ -324,8 +325,8 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
         if (m) {
             uint32_t b = 0;
             if (lane == 0) b = atomicAdd(out_count, (uint32_t)__popcll(m));
-            b = __shfl(b, 0);
-            if (ok) out[b + __popcll(m & ((1ull << lane) - 1ull))] = it;
+            b = __shfl(b, 0) + __popcll(m & ((1ull << lane) - 1ull));
+            if (ok && b < out_room) out[b] = it;
         }
     };
     for (int64_t base = ((int64_t)blockIdx.x * (kLegBlock / 64) + (threadIdx.x >> 6)) * 64; base < n; base += nwaves * 64) {
@@ -346,12 +347,17 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
     if (have) second_leg(have);
 }
 
-// Pass 3: coefficients of the pairs that have a path.
+// Pass 3: coefficients of the pairs that have a path.  count: pairs that passed
+// the filter and pairs that passed the legs; more than fitted their queue are
+// reported by the top bit of the first receiver's count.
 __global__ __launch_bounds__(kBlock) void diffraction_paths_kernel(PathArgs a, MatTable mats, int32_t r0,
                                                                    const uint32_t* __restrict__ queue,
+                                                                   uint32_t filter_room, uint32_t room,
                                                                    const uint32_t* __restrict__ count) {
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
-    const uint32_t n = *count;
+    const uint32_t n = min(count[1], room);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (count[0] > filter_room || count[1] > room))
+        atomicOr(a.counts + r0, 0x80000000u);
     for (uint32_t item = blockIdx.x * kBlock + threadIdx.x; item < n; item += gridDim.x * kBlock) {
         const int r = r0 + (int)(queue[item] / (uint32_t)a.sc.num_wedges);
         const int wi = (int)(queue[item] % (uint32_t)a.sc.num_wedges);
@@ -424,44 +430,53 @@ hipError_t launch_coverage_diffraction(const DevScene& sc, const MatTable& mats,
     return hipGetLastError();
 }
 
-namespace {
-// Receivers handled together: their pairs must fit the queue even if all survive.
-int64_t diffraction_rx_chunk(int64_t nrx, int64_t nw) {
-    const int64_t most = std::max<int64_t>(1, kDiffQueuePairs / nw);
-    return std::min<int64_t>(nrx, most > kDiffRx ? most / kDiffRx * kDiffRx : most);
-}
-}  // namespace
-
-size_t diffraction_scratch(int64_t nrx, int64_t num_wedges) {
-    if (nrx <= 0 || num_wedges <= 0) return 0;
-    const size_t pairs = (size_t)(diffraction_rx_chunk(nrx, num_wedges) * num_wedges);
-    return 256 + 2 * pairs * sizeof(uint32_t);
+DiffPlan diffraction_plan(int64_t nrx, int64_t num_wedges, int64_t most) {
+    DiffPlan p{0, 0, 0};
+    if (nrx <= 0 || num_wedges <= 0) return p;
+    p.chunk = std::max<int64_t>(1, most / num_wedges);
+    p.chunk = std::min<int64_t>(nrx, p.chunk > kDiffRx ? p.chunk / kDiffRx * kDiffRx : p.chunk);
+    const int64_t pairs = p.chunk * num_wedges;
+    const bool part = pairs > kDiffWholePairs && p.chunk >= 8;
+    p.filtered = part ? pairs / 4 : pairs;
+    p.clear = part ? pairs / 8 : pairs;
+    return p;
 }
 
-hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s) {
+DiffPlan diffraction_sure(const DiffPlan& p, int64_t num_wedges) {
+    const int64_t chunk = std::min(p.chunk, (p.filtered + p.clear) / 2 / std::max<int64_t>(1, num_wedges));
+    return DiffPlan{chunk, chunk * num_wedges, chunk * num_wedges};
+}
+
+size_t diffraction_scratch(const DiffPlan& p) {
+    return p.chunk ? 256 + (size_t)(p.filtered + p.clear) * sizeof(uint32_t) : 0;
+}
+
+hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, const DiffPlan& plan, void* scratch,
+                                    hipStream_t s) {
     const int64_t nw = a.sc.num_wedges;
     if (a.nrx <= 0 || nw <= 0) return hipSuccess;
-    const int64_t chunk = diffraction_rx_chunk(a.nrx, nw);
+    const int64_t chunk = plan.chunk;
+    const uint32_t room0 = (uint32_t)plan.filtered, room1 = (uint32_t)plan.clear;
     uint32_t* count = (uint32_t*)scratch;
     uint32_t* q0 = (uint32_t*)((char*)scratch + 256);
-    uint32_t* q1 = q0 + chunk * nw;
+    uint32_t* q1 = q0 + plan.filtered;
     for (int64_t r0 = 0; r0 < a.nrx; r0 += chunk) {
         const int64_t r1 = std::min<int64_t>(a.nrx, r0 + chunk), pairs = (r1 - r0) * nw;
         hipError_t e = launch_fill_u32(count, 0u, 2, s);
         if (e != hipSuccess) return e;
         const int64_t wt = (nw + kBlock - 1) / kBlock, rt = (r1 - r0 + kDiffRx - 1) / kDiffRx;
         hipLaunchKernelGGL(diffraction_filter_kernel, dim3((unsigned)(wt * rt)), dim3(kBlock), 0, s, a, (int32_t)r0,
-                           (int32_t)r1, (int32_t)wt, q0, count);
+                           (int32_t)r1, (int32_t)wt, q0, room0, count);
         // two blocks of 76 KB per CU for the traversals
         const dim3 grid((unsigned)std::min<int64_t>((pairs + kLegBlock - 1) / kLegBlock, 256 * 2));
         if (a.sc.stack_need > kStack)
-            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, count,
-                               q1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, room0,
+                               count, q1, room1, count + 1);
         else
-            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, count,
-                               q1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, room0,
+                               count, q1, room1, count + 1);
         hipLaunchKernelGGL(diffraction_paths_kernel, dim3((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 512)),
-                           dim3(kBlock), 0, s, a, mats, (int32_t)r0, q1, count + 1);
+                           dim3(kBlock), 0, s, a, mats, (int32_t)r0, q1, room0, room1, count);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -161,12 +161,24 @@ hipError_t launch_extract_candidates(const uint64_t* table, uint64_t cap, int32_
 size_t image_scratch(int64_t items);
 hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, void* scratch, hipStream_t s);
 // First-order diffraction: the valid (receiver, wedge) paths into the unsorted
-// records of a (depth = 1, faces[0] = wedge id, fd = 1).  scratch:
-// diffraction_scratch(nrx, num_wedges) bytes, at most two queues of
-// kDiffQueuePairs pairs (or of one receiver's).
-constexpr int64_t kDiffQueuePairs = int64_t(1) << 27;
-size_t diffraction_scratch(int64_t nrx, int64_t num_wedges);
-hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, void* scratch, hipStream_t s);
+// records of a (depth = 1, faces[0] = wedge id, fd = 1).  `chunk` receivers at a
+// time, their pairs at most `most` (or one receiver's), in two queues: pairs that
+// pass the filter and pairs whose legs are clear.  For street receivers of a city
+// 2% and 1 in 8,000 do, of a street canyon 16% pass the filter, so beyond
+// kDiffWholePairs pairs the queues have room for a quarter and an eighth (200 MB
+// for 2^27 pairs, where all would take 1.07 GB; smaller chunks cost a launch's
+// tail each: 1024 receivers x 129,768 wedges at 2^27, 2^26, 2^25 pairs 0.96, 1.12,
+// 1.37 ms).  If that does not do, the top bit of some receiver's count is set: the
+// paths are not whole, and the plan diffraction_sure has room for every pair.
+constexpr int64_t kDiffQueuePairs = int64_t(1) << 27, kDiffWholePairs = int64_t(1) << 22;
+struct DiffPlan {
+    int64_t chunk, filtered, clear;
+};
+DiffPlan diffraction_plan(int64_t nrx, int64_t num_wedges, int64_t most);
+DiffPlan diffraction_sure(const DiffPlan& p, int64_t num_wedges);
+size_t diffraction_scratch(const DiffPlan& p);
+hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, const DiffPlan& plan, void* scratch,
+                                    hipStream_t s);
 // Diffraction part of a coverage map: gain[c] += sum over wedges of |a|^2 of the
 // diffracted path from tx to the centre of cell c (one thread per cell).
 hipError_t launch_coverage_diffraction(const DevScene& sc, const MatTable& mats, double lambda, const double* tx,
