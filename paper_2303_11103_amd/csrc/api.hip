@@ -994,8 +994,15 @@ rt_status rt_compute_paths(rt_ctx* c, rt_scene* s, const rt_trace_params* p, con
         for (int k = 0; k < 3; ++k) pa.tx[k] = tx[t].pos[k];
         pa.tx_ant = make_antenna(tx + t);
         const int64_t items = sphere ? (int64_t)nrx + (int64_t)hc[0] : (int64_t)nrx * ((int64_t)hc[0] + 1);
-        RT_HIP(ensure(c->image, rt::image_scratch(items)));
-        RT_HIP(rt::launch_image_paths(pa, mats, items, c->image.p, c->stream));
+        // fewer pairs at a time where there is no room for the queue of all
+        int64_t chunk = std::min(items, rt::kImageChunk);
+        hipError_t e;
+        while ((e = ensure(c->image, rt::image_scratch(chunk))) == hipErrorOutOfMemory && chunk > 1) {
+            (void)hipGetLastError();
+            chunk = (chunk + 1) / 2;
+        }
+        RT_HIP(e);
+        RT_HIP(rt::launch_image_paths(pa, mats, items, chunk, c->image.p, c->stream));
         const size_t off = (size_t)t * per;
         RT_HIP(rt::launch_sort_paths(pa, nrx, a + 2 * off, T + 8 * off, tau + off, aod + 2 * off, aoa + 2 * off,
                                      depth + off, faces + (size_t)fd * off, num_paths + (size_t)t * nrx, c->stream));
@@ -1163,14 +1170,26 @@ rt_status rt_compute_scattering(rt_ctx* c, rt_scene* s, const rt_trace_params* p
                                                                      sizeof(int32_t) + (nrx * 12 + 63) / 64);
     int64_t chunk = std::min<int64_t>(int64_t(1) << 20, std::max<int64_t>(64, (int64_t(1) << 30) / per_ray));
     chunk = std::min<int64_t>(chunk, count);
-    const int64_t nrec_pad = (chunk * std::max(D, 1) + 63) / 64 * 64;
-    const int64_t nwords = nrec_pad / 64;
-    const size_t pts_bytes = (size_t)chunk * std::max(D, 1) * sizeof(rt::ScatPoint);
-    const size_t mask_bytes = (size_t)nrx * nwords * sizeof(uint64_t);
-    const size_t pre_bytes = ((size_t)nrx * nwords * sizeof(uint32_t) + 255) / 256 * 256;
-    const size_t hits_bytes = (size_t)nrec_pad * sizeof(rt::ScatHit), hit_bytes = (size_t)nrec_pad * sizeof(int32_t);
+    int64_t nrec_pad = 0, nwords = 0;
+    size_t pts_bytes = 0, mask_bytes = 0, pre_bytes = 0, hits_bytes = 0, hit_bytes = 0;
     const size_t cnt_bytes = (size_t)nrx * sizeof(int64_t) + sizeof(int64_t);
-    RT_HIP(ensure(c->scat, pts_bytes + hits_bytes + hit_bytes + mask_bytes + pre_bytes + cnt_bytes));
+    auto reserve = [&] {
+        nrec_pad = (chunk * std::max(D, 1) + 63) / 64 * 64;
+        nwords = nrec_pad / 64;
+        pts_bytes = (size_t)chunk * std::max(D, 1) * sizeof(rt::ScatPoint);
+        mask_bytes = (size_t)nrx * nwords * sizeof(uint64_t);
+        pre_bytes = ((size_t)nrx * nwords * sizeof(uint32_t) + 255) / 256 * 256;
+        hits_bytes = (size_t)nrec_pad * sizeof(rt::ScatHit);
+        hit_bytes = (size_t)nrec_pad * sizeof(int32_t);
+        return ensure(c->scat, pts_bytes + hits_bytes + hit_bytes + mask_bytes + pre_bytes + cnt_bytes);
+    };
+    // fewer rays at a time where there is no room for the records of all
+    hipError_t e;
+    while ((e = reserve()) == hipErrorOutOfMemory && chunk > 64) {
+        (void)hipGetLastError();
+        chunk = std::max<int64_t>(64, chunk / 2);
+    }
+    RT_HIP(e);
     if ((st = stage_receivers(c, rx, nrx)) != RT_OK) return st;
     char* buf = (char*)c->scat.p;
     rt::ScatArgs sa{};

@@ -157,9 +157,12 @@ hipError_t launch_extract_pairs(const uint64_t* pairs, uint64_t pairs_cap, const
                                 int32_t* out_rx, uint32_t* count, uint32_t max_out, hipStream_t s);
 hipError_t launch_extract_candidates(const uint64_t* table, uint64_t cap, int32_t max_depth, Cand* out,
                                      uint32_t* count, uint32_t max_out, hipStream_t s);
-// Device memory launch_image_paths needs for `items` (receiver, candidate) pairs.
-size_t image_scratch(int64_t items);
-hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, void* scratch, hipStream_t s);
+// Image method over `items` (receiver, candidate) pairs, `chunk` at a time (all of
+// a chunk may have a path); scratch: image_scratch(chunk) bytes.
+constexpr int64_t kImageChunk = int64_t(1) << 22;
+size_t image_scratch(int64_t chunk);
+hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, int64_t chunk, void* scratch,
+                              hipStream_t s);
 // First-order diffraction: the valid (receiver, wedge) paths into the unsorted
 // records of a (depth = 1, faces[0] = wedge id, fd = 1).  `chunk` receivers at a
 // time, their pairs at most `most` (or one receiver's), in two queues: pairs that

@@ -455,12 +455,9 @@ hipError_t launch_extract_pairs(const uint64_t* pairs, uint64_t pairs_cap, const
 }
 
 namespace {
-// Items whose survivors share one queue (all may survive).
-constexpr int64_t kImageChunk = int64_t(1) << 22;
-
 template <int D>
-hipError_t image_passes(const PathArgs& a, const MatTable& mats, int64_t items, uint32_t* scratch, hipStream_t s) {
-    const int64_t chunk = std::min(items, kImageChunk);
+hipError_t image_passes(const PathArgs& a, const MatTable& mats, int64_t items, int64_t chunk, uint32_t* scratch,
+                        hipStream_t s) {
     uint32_t *count = scratch, *queue = scratch + 64, *blocked = queue + chunk;
     for (int64_t first = 0; first < items; first += chunk) {
         const int64_t n = std::min(chunk, items - first);
@@ -481,15 +478,16 @@ hipError_t image_passes(const PathArgs& a, const MatTable& mats, int64_t items, 
 }
 }  // namespace
 
-size_t image_scratch(int64_t items) { return (64 + 2 * (size_t)std::min(items, kImageChunk)) * sizeof(uint32_t); }
+size_t image_scratch(int64_t chunk) { return (64 + 2 * (size_t)chunk) * sizeof(uint32_t); }
 
-hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, void* scratch, hipStream_t s) {
+hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t items, int64_t chunk, void* scratch,
+                              hipStream_t s) {
     if (items <= 0) return hipSuccess;
     uint32_t* q = (uint32_t*)scratch;
-    if (a.max_depth <= 1) return image_passes<1>(a, mats, items, q, s);
-    if (a.max_depth <= 3) return image_passes<3>(a, mats, items, q, s);
-    if (a.max_depth <= 5) return image_passes<5>(a, mats, items, q, s);
-    return image_passes<kMaxK>(a, mats, items, q, s);
+    if (a.max_depth <= 1) return image_passes<1>(a, mats, items, chunk, q, s);
+    if (a.max_depth <= 3) return image_passes<3>(a, mats, items, chunk, q, s);
+    if (a.max_depth <= 5) return image_passes<5>(a, mats, items, chunk, q, s);
+    return image_passes<kMaxK>(a, mats, items, chunk, q, s);
 }
 
 hipError_t launch_sort_paths(const PathArgs& a, int32_t nrx, float* a_out, float* T_out, float* tau_out,
