@@ -34,8 +34,9 @@ rt_status fail(rt_status code, const std::string& msg) {
 
 constexpr double kEps0 = 8.8541878128e-12;
 constexpr double kC0 = 299792458.0;
-// Rays per launch sequence.  The two ray queues of a chunk take 2 x 12.9 GB at
-// 2^27 rays (a 1e8-ray lattice in one sequence of max_depth + 1 launches).
+// Rays per launch sequence.  The two ray queues of a chunk take 2 x 10.7 GB at
+// 2^27 rays of a map, 2 x 8.6 GB of paths (a 1e8-ray lattice in one sequence of
+// max_depth + 1 launches).
 constexpr int64_t kChunk = int64_t(1) << 27;
 
 struct DevBuf {
@@ -387,11 +388,15 @@ int64_t region_capacity_by_depth(const rt_ctx* c, int64_t chunk) {
 
 // Whether the first two bounces of a map merge the deposits of a wave per cell:
 // when the cell under the transmitter, the densest, gets enough of them.
-// Merging costs about 1 us per 10^6 rays of a launch.  Measured without / with:
-// street canyon (770 triangles, 60 m above the plane), 10^7 rays, 221 in that
-// cell, 332 / 311 us for the first bounce; 3 x 10^6 rays, 95 in it, 122 / 125;
-// 14 triangles, 8.5 m above, where tracing is cheap: 33 in it 27.3 / 26.3 us a
-// map, 110 in it 42 / 33.
+// Merging costs about 1 us per 10^6 rays of a launch, 1 to 2% of a map.  Measured
+// without / with, us a map of depth 1 (rays in that cell): 14 triangles, where
+// tracing is cheap, 29 / 26 (64), 49 / 35 (160), 187 / 82 (640); one city block of
+// 90 triangles 39.4 / 40.5 (96), 44.7 / 44.3 (128), 52 / 50 (160), 159 / 118 (640);
+// cities of 366 to 3,222 triangles 1% slower to 2% faster (224), 2 to 10% faster
+// (640); of 35,000 and 220,000, which tracing bounds, within 1.5% up to 640.
+// First bounce of the street canyon (770 triangles) from a roof's edge, 122 / 125
+// (95) and 332 / 311 (221); from the middle of the roof, which shades the cell,
+// the rule misjudges and merging costs 2% at any number.
 int merge_deposits(const rt_scene* s, const rt_device* tx, const rt_grid* g, int64_t count) {
     constexpr double kDense = 160.0, kDenseCheap = 32.0;
     constexpr size_t kCheapTris = 64;

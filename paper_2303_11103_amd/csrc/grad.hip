@@ -443,10 +443,6 @@ __global__ __launch_bounds__(kGradBlock) void power_grad_kernel(GradArgs g, MatT
 // scene one kernel for all took 220 registers.  Bound by fp64 arithmetic; 10^7
 // rays of depth 3 over the street canyon's 770 triangles: 1380 us as one
 // kernel of one thread per ray -> 170 (walk) + 151 us (replay).
-__device__ __forceinline__ cd dot3(const cd* v, d3 u) {
-    return cd{v[0].re * u.x + v[1].re * u.y + v[2].re * u.z, v[0].im * u.x + v[1].im * u.y + v[2].im * u.z};
-}
-
 constexpr int kCovWaves = 3;  // of the replay per SIMD: 168 registers; both grids are three blocks per CU
 constexpr int kWalkTris = 1024;
 

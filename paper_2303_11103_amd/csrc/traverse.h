@@ -7,7 +7,7 @@
 
 namespace rt {
 
-constexpr int kBlock = 256;       // block size of kernels that do not stage nodes
+constexpr int kBlock = 256;       // block size of most kernels beside the shoot-and-bounce ones
 constexpr int kStack = kStackEntries;
 constexpr int kLdsNodes = 128;    // top BVH nodes (breadth-first order) staged in LDS, 16 KB
 // Conservative slab interval: a box is entered when near <= far (1 + 3e-6).
