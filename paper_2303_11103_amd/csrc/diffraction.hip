@@ -206,10 +206,13 @@ __device__ void diffracted_path(const MatTable& mats, double lambda, d3 S, const
 // fp64, against bounds 4e-6 (8 times the worst rounding) of their products.
 // The transmitter's side is tested once per wedge.  Each thread gathers its
 // wedge's receivers in a 64-bit mask, so the queue takes one atomic per block.
-constexpr int kDiffRx = 64;
+// `room` stands with the integers, which are loaded at the start: behind the
+// pointers its load came into the serial step at the end (182 -> 190 us).
+constexpr int kDiffRx = 64, kDiffSpill = kDiffRx * kBlock;  // entries behind the queue for a block without room
 __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, int32_t r0, int32_t r1,
-                                                                    int32_t wedge_tiles, uint32_t* __restrict__ queue,
-                                                                    uint32_t room, uint32_t* __restrict__ count) {
+                                                                    int32_t wedge_tiles, uint32_t room,
+                                                                    uint32_t* __restrict__ queue,
+                                                                    uint32_t* __restrict__ count) {
     __shared__ double rx[kDiffRx][3];
     __shared__ uint32_t wave_n[kBlock / 64];
     __shared__ uint32_t start;
@@ -266,14 +269,14 @@ __global__ __launch_bounds__(kBlock) void diffraction_filter_kernel(PathArgs a, 
             sum += c;
         }
         start = sum ? atomicAdd(count, sum) : 0u;
+        if (sum > room || start > room - sum) start = room;  // behind the queue: none of it is read then
     }
     __syncthreads();
     uint32_t at = start + wave_n[wv] + incl - n;
     while (keep) {
         const int r = __ffsll((long long)keep) - 1;
         keep &= keep - 1;
-        if (at < room) queue[at] = (uint32_t)(rb - r0 + r) * (uint32_t)a.sc.num_wedges + (uint32_t)wi;
-        ++at;
+        queue[at++] = (uint32_t)(rb - r0 + r) * (uint32_t)a.sc.num_wedges + (uint32_t)wi;
     }
 }
 
@@ -295,10 +298,11 @@ __device__ __forceinline__ Wedge load_pair(const PathArgs& a, int32_t r0, uint32
 // CU; blocks of 512 with 64 staged nodes leave room for two per CU).
 constexpr int kLegBlock = 512, kLegNodes = 64;
 template <bool OVF>
-__global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a, int32_t r0,
-                                                                     const uint32_t* __restrict__ queue, uint32_t room,
+__global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a, int32_t r0, uint32_t room,
+                                                                     uint32_t out_room,
+                                                                     const uint32_t* __restrict__ queue,
                                                                      const uint32_t* __restrict__ count,
-                                                                     uint32_t* __restrict__ out, uint32_t out_room,
+                                                                     uint32_t* __restrict__ out,
                                                                      uint32_t* __restrict__ out_count) {
     __shared__ int32_t stack[kStack][kLegBlock];
     __shared__ Node lds_nodes[kLegNodes];
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
     const int lane = threadIdx.x & 63;
     uint32_t* mine = held[threadIdx.x >> 6];
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
-    const int64_t n = (int64_t)min(*count, room);
+    const int64_t n = *count > room ? 0 : (int64_t)*count;
     const int64_t nwaves = (int64_t)gridDim.x * (kLegBlock / 64);
     int have = 0;  // survivors of the first leg in `mine` (the same in every lane)
     auto second_leg = [&](int take) {
@@ -325,8 +329,8 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
         if (m) {
             uint32_t b = 0;
             if (lane == 0) b = atomicAdd(out_count, (uint32_t)__popcll(m));
-            b = __shfl(b, 0) + __popcll(m & ((1ull << lane) - 1ull));
-            if (ok && b < out_room) out[b] = it;
+            b = __builtin_amdgcn_readfirstlane(b);
+            if (b + (uint32_t)__popcll(m) <= out_room && ok) out[b + __popcll(m & ((1ull << lane) - 1ull))] = it;
         }
     };
     for (int64_t base = ((int64_t)blockIdx.x * (kLegBlock / 64) + (threadIdx.x >> 6)) * 64; base < n; base += nwaves * 64) {
@@ -348,16 +352,16 @@ __global__ __launch_bounds__(kLegBlock) void diffraction_legs_kernel(PathArgs a,
 }
 
 // Pass 3: coefficients of the pairs that have a path.  count: pairs that passed
-// the filter and pairs that passed the legs; more than fitted their queue are
-// reported by the top bit of the first receiver's count.
+// the filter and pairs that passed the legs; where more than fitted their queue,
+// the first receiver's count says so and nothing of the queue is read.
 __global__ __launch_bounds__(kBlock) void diffraction_paths_kernel(PathArgs a, MatTable mats, int32_t r0,
                                                                    const uint32_t* __restrict__ queue,
                                                                    uint32_t filter_room, uint32_t room,
                                                                    const uint32_t* __restrict__ count) {
     const d3 S{a.tx[0], a.tx[1], a.tx[2]};
-    const uint32_t n = min(count[1], room);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && (count[0] > filter_room || count[1] > room))
-        atomicOr(a.counts + r0, 0x80000000u);
+    const bool over = count[0] > filter_room || count[1] > room;
+    if (over && blockIdx.x == 0 && threadIdx.x == 0) a.counts[r0] = 0x80000000u;
+    const uint32_t n = over ? 0u : count[1];
     for (uint32_t item = blockIdx.x * kBlock + threadIdx.x; item < n; item += gridDim.x * kBlock) {
         const int r = r0 + (int)(queue[item] / (uint32_t)a.sc.num_wedges);
         const int wi = (int)(queue[item] % (uint32_t)a.sc.num_wedges);
@@ -448,7 +452,7 @@ DiffPlan diffraction_sure(const DiffPlan& p, int64_t num_wedges) {
 }
 
 size_t diffraction_scratch(const DiffPlan& p) {
-    return p.chunk ? 256 + (size_t)(p.filtered + p.clear) * sizeof(uint32_t) : 0;
+    return p.chunk ? 256 + (size_t)(p.filtered + kDiffSpill + p.clear) * sizeof(uint32_t) : 0;
 }
 
 hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, const DiffPlan& plan, void* scratch,
@@ -459,22 +463,22 @@ hipError_t launch_diffraction_paths(const PathArgs& a, const MatTable& mats, con
     const uint32_t room0 = (uint32_t)plan.filtered, room1 = (uint32_t)plan.clear;
     uint32_t* count = (uint32_t*)scratch;
     uint32_t* q0 = (uint32_t*)((char*)scratch + 256);
-    uint32_t* q1 = q0 + plan.filtered;
+    uint32_t* q1 = q0 + plan.filtered + kDiffSpill;
     for (int64_t r0 = 0; r0 < a.nrx; r0 += chunk) {
         const int64_t r1 = std::min<int64_t>(a.nrx, r0 + chunk), pairs = (r1 - r0) * nw;
         hipError_t e = launch_fill_u32(count, 0u, 2, s);
         if (e != hipSuccess) return e;
         const int64_t wt = (nw + kBlock - 1) / kBlock, rt = (r1 - r0 + kDiffRx - 1) / kDiffRx;
         hipLaunchKernelGGL(diffraction_filter_kernel, dim3((unsigned)(wt * rt)), dim3(kBlock), 0, s, a, (int32_t)r0,
-                           (int32_t)r1, (int32_t)wt, q0, room0, count);
+                           (int32_t)r1, (int32_t)wt, room0, q0, count);
         // two blocks of 76 KB per CU for the traversals
         const dim3 grid((unsigned)std::min<int64_t>((pairs + kLegBlock - 1) / kLegBlock, 256 * 2));
         if (a.sc.stack_need > kStack)
-            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, room0,
-                               count, q1, room1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<true>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, room0, room1,
+                               q0, count, q1, count + 1);
         else
-            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, q0, room0,
-                               count, q1, room1, count + 1);
+            hipLaunchKernelGGL(diffraction_legs_kernel<false>, grid, dim3(kLegBlock), 0, s, a, (int32_t)r0, room0, room1,
+                               q0, count, q1, count + 1);
         hipLaunchKernelGGL(diffraction_paths_kernel, dim3((unsigned)std::min<int64_t>((pairs + kBlock - 1) / kBlock, 512)),
                            dim3(kBlock), 0, s, a, mats, (int32_t)r0, q1, room0, room1, count);
         if ((e = hipGetLastError()) != hipSuccess) return e;

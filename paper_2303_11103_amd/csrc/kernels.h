@@ -171,8 +171,8 @@ hipError_t launch_image_paths(const PathArgs& a, const MatTable& mats, int64_t i
 // kDiffWholePairs pairs the queues have room for a quarter and an eighth (200 MB
 // for 2^27 pairs, where all would take 1.07 GB; smaller chunks cost a launch's
 // tail each: 1024 receivers x 129,768 wedges at 2^27, 2^26, 2^25 pairs 0.96, 1.12,
-// 1.37 ms).  If that does not do, the top bit of some receiver's count is set: the
-// paths are not whole, and the plan diffraction_sure has room for every pair.
+// 1.37 ms).  If that does not do, some receiver's count is 2^31: the paths are not
+// whole, and the plan diffraction_sure has room for every pair.
 constexpr int64_t kDiffQueuePairs = int64_t(1) << 27, kDiffWholePairs = int64_t(1) << 22;
 struct DiffPlan {
     int64_t chunk, filtered, clear;
